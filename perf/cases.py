@@ -1,0 +1,305 @@
+"""Workloads whose time is measured, each one pass through the public entry points.
+
+Four kinds of call, which are what a program on this library spends its time in:
+
+  psi    psi_stats then psi_grads with variances S: one training step of the
+         statistics (the forward direction, then the backward one with upstream
+         gradients dL/dpsi0, dL/dPsi1, dL/dPsi2)
+  known  the same pair of calls with known inputs (S = None)
+  bound  one evaluation of the GP-LVM bound with every gradient, as the fits call it
+  regr   the same with known inputs (the sparse GP regression bound)
+
+Shapes and distributions are those of the named workloads of
+``paper_1410_4984_amd/synth.py`` and of the bound's benchmark and fits; the
+remaining listed cases are odd sizes inside the documented limits.  Inputs are
+drawn on the device from the seed.  The workspace is kept by the caller, as the
+fits and the benchmark keep it; the outputs are allocated by the calls.
+"""
+from __future__ import annotations
+
+import math
+
+import torch
+
+import paper_1410_4984_amd as gpps
+
+DEV = "cuda:0"
+DT = {"f32": torch.float32, "f64": torch.float64}
+
+
+def listed():
+    return [
+        # the smallest statistics a toy model asks for: launches and host time
+        {"name": "tiny", "kind": "psi", "dtype": "f32", "N": 200, "M": 10, "Q": 2, "data": "normal"},
+        # a small data set, or one minibatch
+        {"name": "small", "kind": "psi", "dtype": "f32", "N": 5000, "M": 50, "Q": 10, "data": "normal"},
+        # an ordinary data set: clustered latents, inducing inputs picked from them
+        {"name": "medium", "kind": "psi", "dtype": "f32", "N": 50000, "M": 100, "Q": 10,
+         "data": "clustered"},
+        # the benchmark's headline shape
+        {"name": "large", "kind": "psi", "dtype": "f32", "N": 100000, "M": 256, "Q": 20, "data": "normal"},
+        # one row chunk of the million-row workload
+        {"name": "stress_chunk", "kind": "psi", "dtype": "f32", "N": 131072, "M": 512, "Q": 30,
+         "data": "normal"},
+        # odd sizes, with more inducing inputs than the named workloads have
+        {"name": "many_inducing", "kind": "psi", "dtype": "f32", "N": 3001, "M": 700, "Q": 12,
+         "data": "clustered"},
+        # double precision, the fits' default type, at the ordinary and the headline shape
+        {"name": "medium_f64", "kind": "psi", "dtype": "f64", "N": 50000, "M": 100, "Q": 10,
+         "data": "clustered"},
+        {"name": "large_f64", "kind": "psi", "dtype": "f64", "N": 100000, "M": 256, "Q": 20,
+         "data": "normal"},
+        # a row chunk of the million-row workload's shape in double precision
+        {"name": "stress_f64", "kind": "psi", "dtype": "f64", "N": 4096, "M": 512, "Q": 30,
+         "data": "normal"},
+        # one optimiser evaluation at the paper's experiment shape
+        {"name": "gplvm_bound", "kind": "bound", "dtype": "f64", "N": 64000, "M": 100, "Q": 1, "D": 3,
+         "data": "curve"},
+        # sparse GP regression: its statistics at the headline shape ...
+        {"name": "known_large", "kind": "known", "dtype": "f32", "N": 100000, "M": 256, "Q": 20,
+         "data": "normal"},
+        # ... and one optimiser evaluation of a small regression fit
+        {"name": "regression_bound", "kind": "regr", "dtype": "f64", "N": 3000, "M": 25, "Q": 1, "D": 2,
+         "data": "curve"},
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    """One more case: N 200 .. 131,072, M 10 .. 700 (bounds: 512), Q 1 .. 40."""
+    kind = rng.choice(["psi", "psi", "psi", "psi", "known", "bound", "regr"])
+    case = {"kind": kind, "dtype": rng.choice(["f32", "f32", "f64"]), "N": _log_int(rng, 200, 131072)}
+    if kind in ("bound", "regr"):
+        # the fits run in double precision, by default on a low-dimensional latent space
+        case.update(dtype="f64", M=_log_int(rng, 10, 300), Q=1, D=rng.randint(1, 12), data="curve")
+        most = 64000 * 300.0 ** 2
+        case["N"] = max(200, min(case["N"], int(most / case["M"] ** 2)))
+        return case
+    case.update(M=_log_int(rng, 10, 700), Q=rng.randint(1, 40), data=rng.choice(["normal", "clustered"]))
+    # no costlier than the listed ones of its type and range
+    if kind == "psi":
+        if case["dtype"] == "f32" and case["M"] <= 512 and case["Q"] <= 30:
+            most = 131072 * 512.0 ** 2 * 30
+        else:
+            most = 4096 * 512.0 ** 2 * 30
+        case["N"] = max(200, min(case["N"], int(most / (case["M"] ** 2 * max(case["Q"], 8)))))
+    return case
+
+
+# ------------------------------------------------------------------ inputs
+
+def _inputs(case, seed):
+    g = torch.Generator(device=DEV).manual_seed(int(seed))
+    f64 = torch.float64
+
+    def rand(*shape):
+        return torch.rand(*shape, generator=g, device=DEV, dtype=f64)
+
+    def randn(*shape):
+        return torch.randn(*shape, generator=g, device=DEV, dtype=f64)
+
+    N, M, Q, kind = case["N"], case["M"], case["Q"], case["kind"]
+    p = {}
+    if case["data"] == "curve":
+        # a one-dimensional latent seen through smooth functions plus noise; evenly
+        # spaced inducing inputs, a lengthscale near their spacing (well conditioned)
+        x = 6.0 * rand(N, 1) - 3.0
+        w, ph = 0.5 + 2.0 * rand(1, case["D"]), 6.0 * rand(1, case["D"])
+        p["mu"] = x
+        p["S"] = 0.05 + 0.45 * rand(N, Q)
+        p["Z"] = torch.linspace(-3.0, 3.0, M, device=DEV, dtype=f64)[:, None].repeat(1, Q)
+        p["Z"] = p["Z"] + 0.1 * (6.0 / M) * randn(M, Q)
+        p["Y"] = torch.sin(w * x + ph) + 0.05 * randn(N, case["D"])
+        p["l"] = [float(6.0 / M)] * Q
+        p["sigma_f2"], p["beta"], p["jitter"] = 1.0, 100.0, 1e-4
+    elif case["data"] == "clustered":
+        centres = 3.0 * randn(3, Q)
+        at = torch.randint(0, 3, (N,), generator=g, device=DEV)
+        p["mu"] = centres[at] + randn(N, Q)
+        p["S"] = torch.exp(math.log(1e-3) * rand(N, Q))
+        p["Z"] = p["mu"][torch.randint(0, N, (M,), generator=g, device=DEV)] + 0.1 * randn(M, Q)
+        p["l"] = (0.5 + 1.5 * rand(Q)).tolist()
+        p["sigma_f2"] = 1.0
+    else:
+        p["mu"] = randn(N, Q)
+        p["S"] = 0.01 + 0.49 * rand(N, Q)
+        p["Z"] = randn(M, Q)
+        p["l"] = (0.5 + 1.5 * rand(Q)).tolist()
+        p["sigma_f2"] = 1.3
+    if kind in ("psi", "known"):
+        p["dL_dpsi0"] = 0.7
+        p["dL_dPsi1"] = randn(N, M)
+        A = randn(M, M)
+        p["dL_dPsi2"] = 0.5 * (A + A.T)
+    if kind in ("known", "regr"):
+        p["S"] = None
+    dt = DT[case["dtype"]]
+    for k, v in p.items():
+        if isinstance(v, torch.Tensor):
+            p[k] = v.to(dt).contiguous()
+    # hyper-parameters at the call's precision, so that both sides use the same values
+    p["l"] = torch.tensor(p["l"], dtype=dt).double().tolist()
+    p["sigma_f2"] = float(torch.tensor(p["sigma_f2"], dtype=dt))
+    if "dL_dpsi0" in p:
+        p["dL_dpsi0"] = float(torch.tensor(p["dL_dpsi0"], dtype=dt))
+    return p
+
+
+def prepare(case, seed):
+    p = _inputs(case, seed)
+    dt, N, M, Q = DT[case["dtype"]], case["N"], case["M"], case["Q"]
+    if case["kind"] in ("bound", "regr"):
+        n = gpps.bound_workspace_bytes(dt, N, M, Q, case["D"])
+    else:
+        n = gpps.workspace_bytes(dt, N, M, Q)
+    p["workspace"] = torch.empty(n, dtype=torch.uint8, device=DEV)
+    p["kind"] = case["kind"]
+    return p
+
+
+def run(s):
+    if s["kind"] in ("bound", "regr"):
+        out = gpps.bound(s["mu"], s["S"], s["Z"], s["Y"], s["sigma_f2"], s["l"], s["beta"], s["jitter"],
+                         workspace=s["workspace"])
+        return {k: v for k, v in out.items() if v is not None}
+    psi0, Psi1, Psi2 = gpps.psi_stats(s["mu"], s["S"], s["Z"], s["sigma_f2"], s["l"],
+                                      workspace=s["workspace"])
+    out = gpps.psi_grads(s["mu"], s["S"], s["Z"], s["sigma_f2"], s["l"], s["dL_dpsi0"], s["dL_dPsi1"],
+                         s["dL_dPsi2"], workspace=s["workspace"])
+    out = {k: v for k, v in out.items() if v is not None}
+    return {"psi0": psi0, "Psi1": Psi1, "Psi2": Psi2, **out}
+
+
+# ------------------------------------------------------------------ work and tolerance
+
+def work(case):
+    N, M, Q = case["N"], case["M"], case["Q"]
+    e = 4 if case["dtype"] == "f32" else 8
+    pairs = M * (M + 1) // 2
+    rows = (4 if case["kind"] in ("psi", "bound") else 2) * N * Q   # mu, S and their gradients
+    if case["kind"] in ("bound", "regr"):
+        nbytes = rows + N * case["D"] + 2 * M * Q
+    else:
+        nbytes = rows + 2 * N * M + 2 * M * M + 2 * M * Q           # + Psi1, dL/dPsi1, Psi2, dL/dPsi2
+    if case["kind"] in ("psi", "bound"):
+        # per datapoint and unique pair: the exponent's Q products twice, both sides of
+        # the weighted sums, and one exponential in each direction
+        flops = N * pairs * (8 * Q + 2)
+    else:
+        flops = N * (2 * pairs + 2 * M * M + 8 * M * Q)
+    return {"bytes": e * nbytes, "flops": flops}
+
+
+def tolerance(case):
+    # about four times the largest difference from exact() over these shapes: 7.6e-6 in
+    # float32 (dZ, a difference of two larger sums), 9e-15 in float64 statistics (with
+    # room for exponents up to ~1e2 summed in another order), 5e-12 in the bounds, whose
+    # M x M algebra amplifies rounding by the conditioning of Kmm and A
+    if case["dtype"] == "f32":
+        return {"rel": 3e-5, "max": 2e-3}
+    if case["kind"] in ("bound", "regr"):
+        return {"rel": 1e-9, "max": 1e-7}
+    return {"rel": 1e-12, "max": 1e-10}
+
+
+# ------------------------------------------------------------------ 64-bit values
+
+def _psi_exact(mu, S, Z, sf2, l, G0, G1, G2, want):
+    """The closed forms and their derivatives in plain torch, row chunk by row chunk.
+    want = "stats" or "grads"."""
+    N, Q = mu.shape
+    M = Z.shape[0]
+    l = torch.tensor(l, dtype=torch.float64, device=mu.device)
+    il2 = 1.0 / l ** 2
+    if S is None:
+        S = torch.zeros_like(mu)
+    dz = Z[:, None, :] - Z[None, :, :]
+    C = -0.25 * (dz * dz * il2).sum(-1)
+    B = max(1, min(N, (1 << 27) // (M * M), (1 << 27) // (M * Q)))
+    if want == "stats":
+        Psi1 = torch.empty((N, M), dtype=torch.float64, device=mu.device)
+        Psi2 = torch.zeros((M, M), dtype=torch.float64, device=mu.device)
+    else:
+        G2s = 0.5 * (G2 + G2.T)
+        dmu, dS = torch.empty_like(mu), torch.empty_like(mu)
+        dZ, dl, dsf = torch.zeros_like(Z), torch.zeros_like(l), G0 * N
+    for i in range(0, N, B):
+        s, x = S[i:i + B], mu[i:i + B]
+        w1, w2 = 1.0 / (l ** 2 + s), 1.0 / (l ** 2 + 2.0 * s)
+        lp1 = math.log(sf2) - 0.5 * torch.log1p(s * il2).sum(-1)
+        lp2 = 2.0 * math.log(sf2) - 0.5 * torch.log1p(2.0 * s * il2).sum(-1)
+        d = x[:, None, :] - Z[None, :, :]
+        P1 = torch.exp(lp1[:, None] - 0.5 * (d * d * w1[:, None, :]).sum(-1))
+        b = -0.25 * (d * d * w2[:, None, :]).sum(-1)
+        E = torch.matmul(d * (-0.5 * w2)[:, None, :], d.transpose(1, 2).contiguous())
+        E += b[:, :, None]
+        E += b[:, None, :]
+        E += C[None]
+        E += lp2[:, None, None]
+        P2 = E.exp_()
+        if want == "stats":
+            Psi1[i:i + B] = P1
+            Psi2 += P2.sum(0)
+            continue
+        t = (G1[i:i + B] * P1)[:, :, None]
+        W = P2.mul_(G2s[None])
+        r = W.sum(-1)[:, :, None]
+        V = torch.matmul(W, d)                       # sum_m' W d_m'
+        a1, a2, sv = w1[:, None, :], w2[:, None, :], s[:, None, :]
+        dr, d2 = d * r, d * d
+        dmu[i:i + B] = (-2.0 * a2 * dr - t * d * a1).sum(1)
+        dS[i:i + B] = (a2 ** 2 * d * (dr + V) - a2 * r + 0.5 * t * (d2 * a1 ** 2 - a1)).sum(1)
+        dZ += (a2 * (dr + V) - (V - dr) * il2 + t * d * a1).sum(0)
+        dl += (2.0 * sv * a2 / l * r + d * (dr - V) * il2 / l + l * a2 ** 2 * d * (dr + V)
+               + t * (sv * a1 / l + l * d2 * a1 ** 2)).sum((0, 1))
+        dsf = dsf + float((2.0 * r.sum() + t.sum()) / sf2)
+    if want == "stats":
+        return torch.full((1,), N * sf2, dtype=torch.float64, device=mu.device), Psi1, Psi2
+    return {"dmu": dmu, "dS": dS, "dZ": dZ,
+            "dsigma_f2": torch.tensor([dsf], dtype=torch.float64, device=mu.device), "dl": dl}
+
+
+def exact(case, seed):
+    p = _inputs(case, seed)
+    p = {k: (v.double() if isinstance(v, torch.Tensor) else v) for k, v in p.items()}
+    mu, S, Z, sf2, l = p["mu"], p["S"], p["Z"], p["sigma_f2"], p["l"]
+    if case["kind"] in ("psi", "known"):
+        psi0, Psi1, Psi2 = _psi_exact(mu, S, Z, sf2, l, None, None, None, "stats")
+        g = _psi_exact(mu, S, Z, sf2, l, p["dL_dpsi0"], p["dL_dPsi1"], p["dL_dPsi2"], "grads")
+        if S is None:
+            del g["dS"]
+        return {"psi0": psi0, "Psi1": Psi1, "Psi2": Psi2, **g}
+    # the bound: its M x M part on the host, differentiated by autograd; the statistics'
+    # gradients from the closed forms above
+    N, D, M = case["N"], case["D"], case["M"]
+    psi0, Psi1, Psi2 = _psi_exact(mu, S, Z, sf2, l, None, None, None, "stats")
+    Y = p["Y"]
+    host = [v.cpu().requires_grad_() for v in (psi0, Psi2, Psi1.T @ Y, Z)]
+    host += [torch.tensor(v, dtype=torch.float64).requires_grad_() for v in (sf2, l, p["beta"])]
+    h0, hP2, hPY, hZ, hsf, hl, hb = host
+    dz = (hZ[:, None, :] - hZ[None, :, :]) / hl
+    K = hsf * torch.exp(-0.5 * (dz * dz).sum(-1)) + p["jitter"] * torch.eye(M, dtype=torch.float64)
+    A = K + hb * hP2
+    LK, LA = torch.linalg.cholesky(K), torch.linalg.cholesky(A)
+    L = (-0.5 * N * D * math.log(2.0 * math.pi) + 0.5 * N * D * torch.log(hb)
+         + D * torch.log(torch.diagonal(LK)).sum() - D * torch.log(torch.diagonal(LA)).sum()
+         - 0.5 * hb * float((Y * Y).sum())
+         + 0.5 * hb ** 2 * (hPY * torch.cholesky_solve(hPY, LA)).sum()
+         - 0.5 * hb * D * h0[0] + 0.5 * hb * D * torch.trace(torch.cholesky_solve(hP2, LK)))
+    g0, gP2, gPY, gZ, gsf, gl, gb = torch.autograd.grad(L, host)
+    g = _psi_exact(mu, S, Z, sf2, l, float(g0), Y @ gPY.to(DEV).T, gP2.to(DEV), "grads")
+    value = float(L.detach())
+    if S is not None:
+        value -= 0.5 * float((mu * mu + S - torch.log(S) - 1.0).sum())
+        g["dmu"] = g["dmu"] - mu
+        g["dS"] = g["dS"] - 0.5 * (1.0 - 1.0 / S)
+    else:
+        del g["dS"]
+    one = lambda v: torch.tensor([float(v)], dtype=torch.float64)  # noqa: E731
+    g["dZ"] = g["dZ"] + gZ.to(DEV)
+    g["dl"] = g["dl"] + gl.to(DEV)
+    g["dsigma_f2"] = g["dsigma_f2"] + float(gsf)
+    return {"L": one(value), "dbeta": one(gb), **g}
