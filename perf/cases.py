@@ -84,7 +84,7 @@ def draw(rng):
         if case["dtype"] == "f32" and case["M"] <= 512 and case["Q"] <= 30:
             most = 131072 * 512.0 ** 2 * 30
         else:
-            most = 4096 * 512.0 ** 2 * 30
+            most = 1600 * 512.0 ** 2 * 30
         case["N"] = max(200, min(case["N"], int(most / (case["M"] ** 2 * max(case["Q"], 8)))))
     return case
 
