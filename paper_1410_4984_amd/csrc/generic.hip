@@ -158,6 +158,10 @@ Plan make_plan(const Shape &s, size_t elem) {
     p.off_rowp =
         take(elem * std::max({p.rr * p.row_blocks, p.pmb * p.pchunks, p.wmb * p.wchunks}) * (s.Q + 1));
     p.off_rowg = take(elem * std::max({p.rr, p.pmb, p.wmb}) * s.N * s.Q * 2);
+    // the double-precision matrix kernels re-carve the region behind the per-row
+    // tables; it grows to what they want as long as the call's workspace stays
+    // within GPPS_SCRATCH_BYTES (the allocation-free entry point takes no more)
+    if (elem == 8) o = std::max(o, std::min(p.off_p2 + f64_region_bytes(s), size_t(GPPS_SCRATCH_BYTES) - 256));
     p.total = o;
     return p;
 }
@@ -166,52 +170,100 @@ template <typename T>
 T *at(void *ws, size_t off) { return reinterpret_cast<T *>(static_cast<char *>(ws) + off); }
 
 // ---------------------------------------------------------------- per-row tables
+// One thread per (row, dimension) for the reciprocals and logarithms, then one per
+// row for its sums over q, in the order of q.  One thread per row took its 2 Q
+// logarithms one after another: 60 us at N = 100,000, Q = 20 in fp64, and 15 us
+// of latency in the smallest calls.
+constexpr int kPreElems = 1024;   // (row, dimension) pairs per workgroup
+
 template <typename T>
-__global__ void rows_pre_kernel(const int *__restrict__ gate, int64_t N, int Q, const T *__restrict__ S, Hyp<T> h,
-                                T *__restrict__ w1, T *__restrict__ w2, T *__restrict__ lp1,
-                                T *__restrict__ lp2) {
+__global__ __launch_bounds__(256) void rows_pre_kernel(const int *__restrict__ gate, int64_t N, int Q, int rows,
+                                                       const T *__restrict__ S, Hyp<T> h,
+                                                       T *__restrict__ w1, T *__restrict__ w2,
+                                                       T *__restrict__ lp1, T *__restrict__ lp2) {
     if (gate && gate[0] == 0) return;
-    int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= N) return;
-    T a = h.log_sf2, b = T(2) * h.log_sf2;
-    for (int q = 0; q < Q; ++q) {
-        T s = S[n * Q + q];
-        T l2 = h.l2[q];
-        w1[n * Q + q] = T(1) / (l2 + s);
-        w2[n * Q + q] = T(1) / (l2 + T(2) * s);
-        a -= T(0.5) * dlog1p(s / l2);
-        b -= T(0.5) * dlog1p(T(2) * s / l2);
+    __shared__ T sl1[kPreElems], sl2[kPreElems];
+    const int64_t n0 = (int64_t)blockIdx.x * rows;
+    const int cnt = (int)min<int64_t>(rows, N - n0);
+    for (int i = threadIdx.x; i < cnt * Q; i += 256) {
+        const T s = S[n0 * Q + i], l2 = h.l2[i % Q];
+        w1[n0 * Q + i] = T(1) / (l2 + s);
+        w2[n0 * Q + i] = T(1) / (l2 + T(2) * s);
+        sl1[i] = dlog1p(s / l2);
+        sl2[i] = dlog1p(T(2) * s / l2);
     }
-    lp1[n] = a;
-    lp2[n] = b;
+    __syncthreads();
+    for (int i = threadIdx.x; i < 2 * cnt; i += 256) {
+        const int r = i >> 1;
+        const T *sl = (i & 1 ? sl2 : sl1) + r * Q;
+        T a = (i & 1 ? T(2) : T(1)) * h.log_sf2;
+        for (int q = 0; q < Q; ++q) a -= T(0.5) * sl[q];
+        (i & 1 ? lp2 : lp1)[n0 + r] = a;
+    }
 }
 
 // ---------------------------------------------------------------- Psi1 (Alg. 1, Psi)
+// 64 x 64 blocks of (n, m), a thread 4 x 4 of them, 16 dimensions staged in LDS at a
+// time: twelve LDS reads serve the 48 operations of a dimension.  One thread per
+// entry, reading its rows from memory, waited for each of its loads: 967 us at
+// N = 100,000, M = 256, Q = 20 in fp64, against 0.1 ms of arithmetic and stores.
+constexpr int kPsi1Tile = 64, kPsi1Q = 16;
+
 template <typename T>
-__global__ void psi1_kernel(const int *__restrict__ gate, int64_t N, int M, int Q, const T *__restrict__ mu,
-                            const T *__restrict__ Z, const T *__restrict__ w1,
-                            const T *__restrict__ lp1, T *__restrict__ Psi1) {
+__global__ __launch_bounds__(256) void psi1_kernel(const int *__restrict__ gate, int64_t N, int M, int Q,
+                                                   const T *__restrict__ mu, const T *__restrict__ Z,
+                                                   const T *__restrict__ w1, const T *__restrict__ lp1,
+                                                   T *__restrict__ Psi1) {
     if (gate && gate[0] == 0) return;
-    // grid-stride over the N x M entries (the grid is capped, so that a call
-    // whose gate is closed dispatches few workgroups)
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N * M;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        int64_t n;
-        int m;
-        if (i <= 0x7fffffff) {  // 32-bit division where the index fits
-            const unsigned u = (unsigned)i, nn = u / (unsigned)M;
-            n = nn;
-            m = (int)(u - nn * (unsigned)M);
-        } else {
-            n = i / M;
-            m = (int)(i - n * M);
+    __shared__ T sx[kPsi1Tile][kPsi1Q + 1], sw[kPsi1Tile][kPsi1Q + 1], sz[kPsi1Tile][kPsi1Q + 1];
+    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+    const int m0 = blockIdx.x * kPsi1Tile;
+    // row tiles blockIdx.y, blockIdx.y + gridDim.y, ... (the grid is capped, so that
+    // a call whose gate is closed dispatches few workgroups)
+    for (int64_t n0 = (int64_t)blockIdx.y * kPsi1Tile; n0 < N; n0 += (int64_t)gridDim.y * kPsi1Tile) {
+        T s[4][4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) s[i][j] = 0;
+        for (int q0 = 0; q0 < Q; q0 += kPsi1Q) {
+            const int qn = min(kPsi1Q, Q - q0);
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < kPsi1Tile * kPsi1Q / 256; ++u) {
+                const int i = tid + u * 256, r = i / kPsi1Q, q = min(i % kPsi1Q, qn - 1);
+                const int64_t n = min<int64_t>(n0 + r, N - 1);
+                sx[r][i % kPsi1Q] = mu[n * Q + q0 + q];
+                sw[r][i % kPsi1Q] = w1[n * Q + q0 + q];
+                sz[r][i % kPsi1Q] = Z[(int64_t)min(m0 + r, M - 1) * Q + q0 + q];
+            }
+            __syncthreads();
+            for (int q = 0; q < qn; ++q) {
+                T z[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) z[j] = sz[tx + 16 * j][q];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const T x = sx[4 * ty + i][q], w = sw[4 * ty + i][q];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const T d = x - z[j];
+                        s[i][j] += d * d * w;
+                    }
+                }
+            }
         }
-        T s = 0;
-        for (int q = 0; q < Q; ++q) {
-            T d = mu[n * Q + q] - Z[(int64_t)m * Q + q];
-            s += d * d * w1[n * Q + q];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int64_t n = n0 + 4 * ty + i;
+            if (n >= N) break;
+            const T l = lp1[n];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int m = m0 + tx + 16 * j;
+                if (m < M) Psi1[n * M + m] = dexp(l - T(0.5) * s[i][j]);
+            }
         }
-        Psi1[i] = dexp(lp1[n] - T(0.5) * s);
     }
 }
 
@@ -1337,8 +1389,10 @@ template <typename T>
 void rows_pre(const Shape &s, const Plan &p, const T *S, const Hyp<T> &h, void *ws,
               const int *gate, hipStream_t st) {
     TimedScope ts(st, "generic_rows_pre");
-    rows_pre_kernel<T><<<(unsigned)cdiv(s.N, 256), 256, 0, st>>>(gate, 
-        s.N, (int)s.Q, S, h, at<T>(ws, p.off_w1), at<T>(ws, p.off_w2), at<T>(ws, p.off_lp1),
+    // few rows a workgroup where there are few: at least a workgroup per CU
+    const int64_t rows = std::max<int64_t>(1, std::min(kPreElems / s.Q, cdiv(s.N, 256)));
+    rows_pre_kernel<T><<<(unsigned)cdiv(s.N, rows), 256, 0, st>>>(gate,
+        s.N, (int)s.Q, (int)rows, S, h, at<T>(ws, p.off_w1), at<T>(ws, p.off_w2), at<T>(ws, p.off_lp1),
         at<T>(ws, p.off_lp2));
 }
 
@@ -1356,8 +1410,15 @@ hipError_t generic_psi_stats(const Shape &s, const T *mu, const T *S, const T *Z
     const T *lp1 = at<T>(ws, p.off_lp1), *lp2 = at<T>(ws, p.off_lp2);
     if (Psi1) {
         TimedScope ts(st, "generic_psi1");
-        psi1_kernel<T><<<(unsigned)std::min<int64_t>(cdiv(s.N * s.M, 256), kGridCap), 256, 0, st>>>(gate, s.N, (int)s.M, (int)s.Q,
-                                                                       mu, Z, w1, lp1, Psi1);
+        const int64_t mt = cdiv(s.M, kPsi1Tile), nt = cdiv(s.N, kPsi1Tile);
+        const dim3 g((unsigned)mt, (unsigned)std::min(nt, std::max<int64_t>(1, kGridCap / mt)));
+        psi1_kernel<T><<<g, 256, 0, st>>>(gate, s.N, (int)s.M, (int)s.Q, mu, Z, w1, lp1, Psi1);
+    }
+    if constexpr (sizeof(T) == 8) {
+        const size_t budget = p.total - p.off_p2;
+        if (f64_stats_fit(s, budget))
+            return f64_psi2(s, mu, Z, w2, lp2, h, psi0, Psi2, accumulate, at<char>(ws, p.off_p2),
+                            budget, st);
     }
     T *partial = at<T>(ws, p.off_p2);
     switch (fwd_qm(s.Q)) {
@@ -1385,6 +1446,25 @@ hipError_t generic_psi_grads(const Shape &s, const T *mu, const T *S, const T *Z
     rows_pre<T>(s, p, S, h, ws, gate, st);
     const T *w1 = at<T>(ws, p.off_w1), *w2 = at<T>(ws, p.off_w2);
     const T *lp1 = at<T>(ws, p.off_lp1), *lp2 = at<T>(ws, p.off_lp2);
+    const int64_t total = s.M * s.Q + s.Q + 1;
+    if constexpr (sizeof(T) == 8) {
+        const F64GradPlan f = f64_grad_plan(s, p.total - p.off_p2);
+        if (f.ok) {
+            char *region = at<char>(ws, p.off_p2);
+            const hipError_t e = f64_psi2_grads(s, f, mu, S, Z, w1, w2, lp1, lp2, h, G1, G2, dmu, dS,
+                                                region, st);
+            if (e != hipSuccess) return e;
+            TimedScope ts(st, "generic_grad_reduce");
+            if (f.groups > 1)
+                grad_rows_reduce_kernel<T><<<(unsigned)std::min<int64_t>(cdiv(s.N * s.Q, 256), kGridCap),
+                                             256, 0, st>>>(gate, s.N * s.Q, f.groups,
+                                                           at<T>(region, f.off_rowg), dmu, dS);
+            grad_reduce_kernel<T><<<(unsigned)std::min<int64_t>(total, kGridCap), 256, 0, st>>>(
+                gate, s.N, (int)s.M, (int)s.Q, f.chunks, f.chunks * f.groups, at<T>(region, f.off_colp),
+                at<T>(region, f.off_rowp), dL_dpsi0, dZ, dsf2, dl, accumulate);
+            return hipGetLastError();
+        }
+    }
     T *G2s = nullptr;
     if (G2) {
         G2s = at<T>(ws, p.off_g2s);
@@ -1431,7 +1511,6 @@ hipError_t generic_psi_grads(const Shape &s, const T *mu, const T *S, const T *Z
             }
 #undef GPPS_PAIRS
         }
-        const int64_t total = s.M * s.Q + s.Q + 1;
         TimedScope ts(st, "generic_grad_reduce");
         grad_rows_reduce_kernel<T><<<(unsigned)std::min<int64_t>(cdiv(s.N * s.Q, 256), kGridCap), 256, 0, st>>>(gate, 
             s.N * s.Q, (int)p.pmb, rowg, dmu, dS);
@@ -1470,7 +1549,6 @@ hipError_t generic_psi_grads(const Shape &s, const T *mu, const T *S, const T *Z
             }
 #undef GPPS_WIDE
         }
-        const int64_t total = s.M * s.Q + s.Q + 1;
         TimedScope ts(st, "generic_grad_reduce");
         grad_rows_reduce_kernel<T><<<(unsigned)std::min<int64_t>(cdiv(s.N * s.Q, 256), kGridCap), 256, 0, st>>>(gate,
             s.N * s.Q, (int)p.wmb, rowg, dmu, dS);
@@ -1489,7 +1567,6 @@ hipError_t generic_psi_grads(const Shape &s, const T *mu, const T *S, const T *Z
         launch_grads<T, 32>(s, p, mu, S, Z, w1, w2, lp1, lp2, h, G1, G2s, rowg, colpart, rowpart, gate, st);
     else
         launch_grads<T, 64>(s, p, mu, S, Z, w1, w2, lp1, lp2, h, G1, G2s, rowg, colpart, rowpart, gate, st);
-    const int64_t total = s.M * s.Q + s.Q + 1;
     TimedScope ts(st, "generic_grad_reduce");
     grad_rows_reduce_kernel<T><<<(unsigned)std::min<int64_t>(cdiv(s.N * s.Q, 256), kGridCap), 256, 0, st>>>(gate, s.N * s.Q, (int)p.rr,
                                                                               rowg, dmu, dS);

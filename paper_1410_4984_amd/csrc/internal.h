@@ -66,6 +66,38 @@ hipError_t generic_psi_grads(const Shape &s, const T *mu, const T *S, const T *Z
                              T *dS, T *dZ, T *dsf2, T *dl, int accumulate, void *ws,
                              const int *gate, hipStream_t st);
 
+// ---------------------------------------------------------------- double precision
+// Psi2 and its gradients in F64 on the matrix cores.  They take the generic path's
+// per-row tables and reduces, and the part of its workspace behind the tables
+// (`budget` bytes at `ws`): the plans fit their chunks to it, so that the path
+// needs no more workspace than the vector kernels it replaces.
+// They are taken where they measured faster than the vector kernels (us per call at
+// N = 64,000, vector / matrix): statistics 297 / 483 at M = 100, Q = 1, 458 / 489 at
+// Q = 4 and 569 / 555 at Q = 5, but 1684 / 1425 at M = 200, Q = 4; gradients
+// 607 / 1098 at M = 100, Q = 1, 1041 / 1102 at Q = 2 and 1848 / 1108 at Q = 4, but
+// 5755 / 4365 at M = 256, Q = 2.  Small Q pads the products' four dimensions, and the
+// vector kernels' symmetric form takes one exponential per unordered pair.
+bool f64_stats_wanted(const Shape &s);
+bool f64_grads_wanted(const Shape &s);
+size_t f64_region_bytes(const Shape &s);   // the region with which no plan is cut short
+bool f64_stats_fit(const Shape &s, size_t budget);
+hipError_t f64_psi2(const Shape &s, const double *mu, const double *Z, const double *w2,
+                    const double *lp2, const Hyp<double> &h, double *psi0, double *Psi2,
+                    int accumulate, void *ws, size_t budget, hipStream_t st);
+
+struct F64GradPlan {
+    bool ok;                          // the region holds it
+    int64_t chunks, rows;             // row chunks, rows per chunk
+    int groups, nw, wrows, nwin;      // workgroups per chunk, waves, z rows staged, windows
+    size_t lds;
+    size_t off_gc, off_rowg, off_colp, off_rowp, end;
+};
+F64GradPlan f64_grad_plan(const Shape &s, size_t budget);
+hipError_t f64_psi2_grads(const Shape &s, const F64GradPlan &p, const double *mu, const double *S,
+                          const double *Z, const double *w1, const double *w2, const double *lp1,
+                          const double *lp2, const Hyp<double> &h, const double *G1,
+                          const double *G2, double *dmu, double *dS, void *ws, hipStream_t st);
+
 // ---------------------------------------------------------------- matrix-core path
 // F32 only: per-datapoint Gram blocks and W * D products on MFMA, exp on VALU.
 // route: a device word outside the workspace regions of both paths; the call
