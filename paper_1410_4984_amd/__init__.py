@@ -223,7 +223,9 @@ def psi_stats(mu, S, Z, sigma_f2, l, *, want_psi1=True, accumulate=False, out=No
     _dev_tensor(Z, "Z", dtype, (M, Q), device)
     lh = _host_l(l, Q)
     if out is None:
-        psi0 = torch.zeros(1, dtype=dtype, device=device)
+        # overwritten unless the call accumulates: a fill costs a launch each
+        new = torch.zeros if accumulate else torch.empty
+        psi0 = new(1, dtype=dtype, device=device)
         Psi1 = torch.empty((N, M), dtype=dtype, device=device) if want_psi1 else None
         Psi2 = torch.empty((M, M), dtype=dtype, device=device)
     else:
@@ -263,11 +265,12 @@ def psi_grads(mu, S, Z, sigma_f2, l, dL_dpsi0, dL_dPsi1, dL_dPsi2, *, accumulate
         _dev_tensor(dL_dPsi2, "dL_dPsi2", dtype, (M, M), device)
     lh = _host_l(l, Q)
     if out is None:
+        new = torch.zeros if accumulate else torch.empty   # overwritten unless accumulating
         out = {"dmu": torch.empty((N, Q), dtype=dtype, device=device),
                "dS": None if S is None else torch.empty((N, Q), dtype=dtype, device=device),
-               "dZ": torch.zeros((M, Q), dtype=dtype, device=device),
-               "dsigma_f2": torch.zeros(1, dtype=dtype, device=device),
-               "dl": torch.zeros(Q, dtype=dtype, device=device)}
+               "dZ": new((M, Q), dtype=dtype, device=device),
+               "dsigma_f2": new(1, dtype=dtype, device=device),
+               "dl": new(Q, dtype=dtype, device=device)}
     else:
         for k, shp in (("dmu", (N, Q)), ("dS", (N, Q)), ("dZ", (M, Q)), ("dsigma_f2", (1,)),
                        ("dl", (Q,))):
@@ -377,7 +380,8 @@ def psi_stats_views(mu, S, Zs, sigma_f2s, ls, *, want_psi1=True, accumulate=Fals
     import torch
     dtype, device, N, Q, V, Ms, lh, sf = _views_common(mu, S, Zs, sigma_f2s, ls)
     if out is None:
-        out = [(torch.zeros(1, dtype=dtype, device=device),
+        new = torch.zeros if accumulate else torch.empty
+        out = [(new(1, dtype=dtype, device=device),
                 torch.empty((N, M), dtype=dtype, device=device) if want_psi1 else None,
                 torch.empty((M, M), dtype=dtype, device=device)) for M in Ms]
     need = views_workspace_bytes(dtype, N, Ms, Q)
@@ -409,11 +413,12 @@ def psi_grads_views(mu, S, Zs, sigma_f2s, ls, dL_dpsi0s, dL_dPsi1s, dL_dPsi2s, *
         if G2[v] is not None:
             _dev_tensor(G2[v], f"dL_dPsi2[{v}]", dtype, (Ms[v], Ms[v]), device)
     if out is None:
+        new = torch.zeros if accumulate else torch.empty
         out = {"dmu": torch.empty((N, Q), dtype=dtype, device=device),
                "dS": None if S is None else torch.empty((N, Q), dtype=dtype, device=device),
-               "dZ": [torch.zeros((M, Q), dtype=dtype, device=device) for M in Ms],
-               "dsigma_f2": [torch.zeros(1, dtype=dtype, device=device) for _ in Ms],
-               "dl": [torch.zeros(Q, dtype=dtype, device=device) for _ in Ms]}
+               "dZ": [new((M, Q), dtype=dtype, device=device) for M in Ms],
+               "dsigma_f2": [new(1, dtype=dtype, device=device) for _ in Ms],
+               "dl": [new(Q, dtype=dtype, device=device) for _ in Ms]}
     need = views_workspace_bytes(dtype, N, Ms, Q)
     if need == 0:
         raise GppsError(2, status_string(2))

@@ -34,6 +34,7 @@
 #include <type_traits>
 
 #include "internal.h"
+#include "psi1.h"
 
 namespace gpps {
 namespace {
@@ -300,16 +301,26 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2) void psi2_fwd_kernel(
     }
 }
 
-// Psi2[m, m'] = 2^C sum over chunks, in chunk order; both triangles and psi0.
-// One workgroup per tile of a task, one thread per entry.
+// Workgroups below tasks A C: Psi2[m, m'] = 2^C sum over chunks, in chunk order, one
+// tile of a task each, one thread per entry; both triangles and psi0.  The
+// workgroups past them compute Psi1.
 __global__ __launch_bounds__(256) void psi2_fwd_reduce_kernel(
-    int64_t N, int M, int Q, int nb, int A, int CB, int cmax,
+    int64_t N, int M, int Q, int nb, int A, int CB, int cmax, int tasks,
     const double *__restrict__ partial, const double *__restrict__ Z, Hyp<double> h,
-    double *__restrict__ psi0, double *__restrict__ Psi2, int accumulate) {
-    const int tile = blockIdx.y;
-    if (blockIdx.x == 0 && tile == 0 && threadIdx.x == 0)
+    double *__restrict__ psi0, double *__restrict__ Psi2, int accumulate,
+    const double *__restrict__ mu, const double *__restrict__ w1, const double *__restrict__ lp1,
+    double *__restrict__ Psi1) {
+    __shared__ Psi1Lds<double> s_p1;
+    const unsigned rblocks = tasks * A * CB;
+    if (blockIdx.x >= rblocks) {
+        psi1_blocks<double>(s_p1, blockIdx.x - rblocks, gridDim.x - rblocks, N, M, Q, mu, Z, w1, lp1, Psi1,
+                            [](double x) { return exp(x); });
+        return;
+    }
+    const int tile = blockIdx.x % (A * CB);
+    if (blockIdx.x == 0 && threadIdx.x == 0)
         psi0[0] = (accumulate ? psi0[0] : 0.0) + (double)N * h.sf2;
-    const FwdTask task = fwd_task(N, nb, A, CB, cmax, -1, blockIdx.x);
+    const FwdTask task = fwd_task(N, nb, A, CB, cmax, -1, blockIdx.x / (A * CB));
     const int cb = task.cb + tile % CB, rb = task.rb + tile / CB, chunks = task.chunks;
     if (cb >= nb || rb >= nb || cb > rb) return;
     const int lane = threadIdx.x & 63, v = threadIdx.x >> 6;
@@ -338,26 +349,6 @@ __global__ __launch_bounds__(256) void psi2_fwd_reduce_kernel(
 }
 
 // ---------------------------------------------------------------- gradient
-// Gc[m][m'] = (G2 + G2^T)/2 o 2^C over nb 16 x nb 16 entries, zero outside M x M.
-__global__ __launch_bounds__(256) void f64_sym_kernel(int M, int Mp, int Q,
-                                                      const double *__restrict__ G2,
-                                                      const double *__restrict__ Z, Hyp<double> h,
-                                                      double *__restrict__ Gc) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= Mp * Mp) return;
-    const int m = i / Mp, mp = i - m * Mp;
-    double v = 0.0;
-    if (m < M && mp < M) {
-        double C = 0.0;
-        for (int q = 0; q < Q; ++q) {
-            const double dz = Z[(int64_t)m * Q + q] - Z[(int64_t)mp * Q + q];
-            C -= dz * dz / (4.0 * h.l2[q]);
-        }
-        v = 0.5 * (G2[(int64_t)m * M + mp] + G2[(int64_t)mp * M + m]) * exp(C);
-    }
-    Gc[i] = v;
-}
-
 template <int CTRL>
 __device__ inline double rotate16(double x) {
     const long long b = __double_as_longlong(x);
@@ -888,9 +879,10 @@ bool f64_stats_fit(const Shape &s, size_t budget) {
     return f64_stats_wanted(s) && fwd_geo(s, budget).cmax >= 1;
 }
 
-hipError_t f64_psi2(const Shape &s, const double *mu, const double *Z, const double *w2,
-                    const double *lp2, const Hyp<double> &h, double *psi0, double *Psi2,
-                    int accumulate, void *ws, size_t budget, hipStream_t st) {
+hipError_t f64_psi2(const Shape &s, const double *mu, const double *Z, const double *w1,
+                    const double *w2, const double *lp1, const double *lp2, const Hyp<double> &h,
+                    double *psi0, double *Psi1, double *Psi2, int accumulate, void *ws, size_t budget,
+                    hipStream_t st) {
     const FwdGeo f = fwd_geo(s, budget);
     double *partial = static_cast<double *>(ws);
     const unsigned grid = (unsigned)cdiv(f.waves, kFwdWaves);
@@ -908,13 +900,14 @@ hipError_t f64_psi2(const Shape &s, const double *mu, const double *Z, const dou
         }
 #undef GPPS_F64_FWD
     }
-    TimedScope ts(st, "f64_psi2_reduce");
-    psi2_fwd_reduce_kernel<<<dim3((unsigned)f.tasks, (unsigned)(f.a * f.c)), 256, 0, st>>>(
-        s.N, (int)s.M, (int)s.Q, f.nb, f.a, f.c, f.cmax, partial, Z, h, psi0, Psi2, accumulate);
+    TimedScope ts(st, "f64_psi2_reduce_psi1");
+    psi2_fwd_reduce_kernel<<<(unsigned)(f.tasks * f.a * f.c + psi1_grid(s.N, s.M, Psi1, 4096)), 256, 0, st>>>(
+        s.N, (int)s.M, (int)s.Q, f.nb, f.a, f.c, f.cmax, f.tasks, partial, Z, h, psi0, Psi2, accumulate, mu,
+        w1, lp1, Psi1);
     return hipGetLastError();
 }
 
-// Region: Gc [Mp x Mp], row gradients [groups][2][N][Q] (only when groups > 1),
+// Region: Gc = (G2 + G2^T)/2 o 2^C [Mp x Mp], row gradients [groups][2][N][Q] (only when groups > 1),
 // dZ slabs [chunks][M][Q], row sums [chunks][groups][Q + 1].
 F64GradPlan f64_grad_plan(const Shape &s, size_t budget) {
     F64GradPlan p{};
@@ -952,15 +945,8 @@ F64GradPlan f64_grad_plan(const Shape &s, size_t budget) {
 hipError_t f64_psi2_grads(const Shape &s, const F64GradPlan &p, const double *mu, const double *S,
                           const double *Z, const double *w1, const double *w2, const double *lp1,
                           const double *lp2, const Hyp<double> &h, const double *G1,
-                          const double *G2, double *dmu, double *dS, void *ws, hipStream_t st) {
-    const int nb = (int)cdiv(s.M, 16), Mp = nb * 16;
-    double *Gc = nullptr;
-    if (G2) {
-        Gc = dbl(ws, p.off_gc);
-        TimedScope ts(st, "f64_sym");
-        f64_sym_kernel<<<(unsigned)cdiv((int64_t)Mp * Mp, 256), 256, 0, st>>>((int)s.M, Mp, (int)s.Q, G2,
-                                                                            Z, h, Gc);
-    }
+                          const double *Gc, double *dmu, double *dS, void *ws, hipStream_t st) {
+    const int nb = (int)cdiv(s.M, 16);
     // one group of columns writes dmu and dS themselves
     double *om = p.groups > 1 ? dbl(ws, p.off_rowg) : dmu;
     double *os = p.groups > 1 ? om + s.N * s.Q : dS;

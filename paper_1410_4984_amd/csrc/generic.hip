@@ -28,6 +28,7 @@
 #include <algorithm>
 
 #include "internal.h"
+#include "psi1.h"
 
 namespace gpps {
 namespace {
@@ -70,6 +71,9 @@ inline int wide_qh(int64_t Q, size_t elem) {
     return 0;
 }
 
+// The largest workspace before the route word that gpps_psi_stats_noalloc takes.
+constexpr size_t kScratchRoom = size_t(GPPS_SCRATCH_BYTES) - 256;
+
 struct Plan {
     int64_t tiles_edge;              // pair tiles per edge (Psi2 reduce)
     int64_t pblocks;                 // forward: blocks of 256 unique pairs
@@ -94,12 +98,14 @@ struct Plan {
         total;
 };
 
-Plan make_plan(const Shape &s, size_t elem) {
+Plan carve(const Shape &s, size_t elem, bool few_rows) {
     Plan p{};
     p.tiles_edge = cdiv(s.M, kPairTile);
     p.pblocks = cdiv(s.P, 256 * fwd_ppt(s.Q, elem));
-    int64_t nc2 = cdiv(s.N, 256);
+    // 256 rows a chunk, fewer where the chunks are too few for the chip (a chunk's rows
+    // are summed one after another: 55 us for 200 rows of Q = 20 in one chunk)
     int64_t cap2 = std::max<int64_t>(1, 2048 / p.pblocks);
+    int64_t nc2 = std::max(cdiv(s.N, 256), few_rows ? std::min(cdiv(s.N, 16), cdiv(256, p.pblocks)) : 0);
     p.nc2 = std::max<int64_t>(1, std::min(nc2, cap2));
     p.rows2 = cdiv(s.N, p.nc2);
     p.nc2 = cdiv(s.N, p.rows2);
@@ -161,28 +167,74 @@ Plan make_plan(const Shape &s, size_t elem) {
     // the double-precision matrix kernels re-carve the region behind the per-row
     // tables; it grows to what they want as long as the call's workspace stays
     // within GPPS_SCRATCH_BYTES (the allocation-free entry point takes no more)
-    if (elem == 8) o = std::max(o, std::min(p.off_p2 + f64_region_bytes(s), size_t(GPPS_SCRATCH_BYTES) - 256));
+    if (elem == 8) o = std::max(o, std::min(p.off_p2 + f64_region_bytes(s), kScratchRoom));
     p.total = o;
     return p;
+}
+
+Plan make_plan(const Shape &s, size_t elem) {
+    // the forward's short chunks, unless their partial sums would take the call past
+    // the allocation-free entry point's scratch
+    const Plan p = carve(s, elem, true);
+    return p.total <= kScratchRoom ? p : carve(s, elem, false);
 }
 
 template <typename T>
 T *at(void *ws, size_t off) { return reinterpret_cast<T *>(static_cast<char *>(ws) + off); }
 
 // ---------------------------------------------------------------- per-row tables
-// One thread per (row, dimension) for the reciprocals and logarithms, then one per
-// row for its sums over q, in the order of q.  One thread per row took its 2 Q
-// logarithms one after another: 60 us at N = 100,000, Q = 20 in fp64, and 15 us
-// of latency in the smallest calls.
+// Workgroups below rblocks: one thread per (row, dimension) for the reciprocals and
+// logarithms, then one per row for its sums over q, in the order of q.  One thread
+// per row took its 2 Q logarithms one after another: 60 us at N = 100,000, Q = 20
+// in fp64 (30 us here), and 15 us of latency in the smallest calls.  The workgroups
+// past them lay out the symmetric part of dL/dPsi2 (a launch less per call):
+//   kSymPlain  G2s[m][m'] = (G2 + G2^T)/2
+//   kSymCirc   Gc[k][m] = G2s[m][(m + k) mod M], k = 0 .. M/2: the symmetric pairs
+//              kernel reads the pair (m, m + k) of every thread m as one coalesced row
+//   kSymPadded G2s o exp(-sum_q (z_m - z_m')^2 / (4 l^2)), zero-padded to Mp x Mp (the
+//              double-precision matrix kernels)
 constexpr int kPreElems = 1024;   // (row, dimension) pairs per workgroup
+enum SymMode { kSymNone, kSymPlain, kSymCirc, kSymPadded };
 
 template <typename T>
-__global__ __launch_bounds__(256) void rows_pre_kernel(const int *__restrict__ gate, int64_t N, int Q, int rows,
-                                                       const T *__restrict__ S, Hyp<T> h,
-                                                       T *__restrict__ w1, T *__restrict__ w2,
-                                                       T *__restrict__ lp1, T *__restrict__ lp2) {
+__global__ __launch_bounds__(256) void pre_kernel(const int *__restrict__ gate, int *__restrict__ mark,
+                                                  int64_t N, int Q, int rows,
+                                                  unsigned rblocks, const T *__restrict__ S, Hyp<T> h,
+                                                  T *__restrict__ w1, T *__restrict__ w2,
+                                                  T *__restrict__ lp1, T *__restrict__ lp2, int mode,
+                                                  int M, int Mp, const T *__restrict__ G2,
+                                                  const T *__restrict__ Z, T *__restrict__ G2s) {
     if (gate && gate[0] == 0) return;
+    if (mark && blockIdx.x == 0 && threadIdx.x == 0) mark[0] = 1;
     __shared__ T sl1[kPreElems], sl2[kPreElems];
+    if (blockIdx.x >= rblocks) {
+        const int64_t i = (int64_t)(blockIdx.x - rblocks) * 256 + threadIdx.x;
+        if (mode == kSymCirc) {
+            if (i >= (int64_t)(M / 2 + 1) * M) return;
+            const int k = (int)(i / M), m = (int)(i - (int64_t)k * M);
+            int mp = m + k;
+            if (mp >= M) mp -= M;
+            G2s[i] = T(0.5) * (G2[(int64_t)m * M + mp] + G2[(int64_t)mp * M + m]);
+            return;
+        }
+        const int W = mode == kSymPadded ? Mp : M;
+        if (i >= (int64_t)W * W) return;
+        const int m = (int)(i / W), mp = (int)(i - (int64_t)m * W);
+        T v = 0;
+        if (m < M && mp < M) {
+            v = T(0.5) * (G2[(int64_t)m * M + mp] + G2[(int64_t)mp * M + m]);
+            if (mode == kSymPadded) {
+                T C = 0;
+                for (int q = 0; q < Q; ++q) {
+                    const T dz = Z[(int64_t)m * Q + q] - Z[(int64_t)mp * Q + q];
+                    C -= dz * dz / (T(4) * h.l2[q]);
+                }
+                v *= dexp(C);
+            }
+        }
+        G2s[i] = v;
+        return;
+    }
     const int64_t n0 = (int64_t)blockIdx.x * rows;
     const int cnt = (int)min<int64_t>(rows, N - n0);
     for (int i = threadIdx.x; i < cnt * Q; i += 256) {
@@ -199,71 +251,6 @@ __global__ __launch_bounds__(256) void rows_pre_kernel(const int *__restrict__ g
         T a = (i & 1 ? T(2) : T(1)) * h.log_sf2;
         for (int q = 0; q < Q; ++q) a -= T(0.5) * sl[q];
         (i & 1 ? lp2 : lp1)[n0 + r] = a;
-    }
-}
-
-// ---------------------------------------------------------------- Psi1 (Alg. 1, Psi)
-// 64 x 64 blocks of (n, m), a thread 4 x 4 of them, 16 dimensions staged in LDS at a
-// time: twelve LDS reads serve the 48 operations of a dimension.  One thread per
-// entry, reading its rows from memory, waited for each of its loads: 967 us at
-// N = 100,000, M = 256, Q = 20 in fp64, against 0.1 ms of arithmetic and stores.
-constexpr int kPsi1Tile = 64, kPsi1Q = 16;
-
-template <typename T>
-__global__ __launch_bounds__(256) void psi1_kernel(const int *__restrict__ gate, int64_t N, int M, int Q,
-                                                   const T *__restrict__ mu, const T *__restrict__ Z,
-                                                   const T *__restrict__ w1, const T *__restrict__ lp1,
-                                                   T *__restrict__ Psi1) {
-    if (gate && gate[0] == 0) return;
-    __shared__ T sx[kPsi1Tile][kPsi1Q + 1], sw[kPsi1Tile][kPsi1Q + 1], sz[kPsi1Tile][kPsi1Q + 1];
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    const int m0 = blockIdx.x * kPsi1Tile;
-    // row tiles blockIdx.y, blockIdx.y + gridDim.y, ... (the grid is capped, so that
-    // a call whose gate is closed dispatches few workgroups)
-    for (int64_t n0 = (int64_t)blockIdx.y * kPsi1Tile; n0 < N; n0 += (int64_t)gridDim.y * kPsi1Tile) {
-        T s[4][4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) s[i][j] = 0;
-        for (int q0 = 0; q0 < Q; q0 += kPsi1Q) {
-            const int qn = min(kPsi1Q, Q - q0);
-            __syncthreads();
-#pragma unroll
-            for (int u = 0; u < kPsi1Tile * kPsi1Q / 256; ++u) {
-                const int i = tid + u * 256, r = i / kPsi1Q, q = min(i % kPsi1Q, qn - 1);
-                const int64_t n = min<int64_t>(n0 + r, N - 1);
-                sx[r][i % kPsi1Q] = mu[n * Q + q0 + q];
-                sw[r][i % kPsi1Q] = w1[n * Q + q0 + q];
-                sz[r][i % kPsi1Q] = Z[(int64_t)min(m0 + r, M - 1) * Q + q0 + q];
-            }
-            __syncthreads();
-            for (int q = 0; q < qn; ++q) {
-                T z[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) z[j] = sz[tx + 16 * j][q];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const T x = sx[4 * ty + i][q], w = sw[4 * ty + i][q];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const T d = x - z[j];
-                        s[i][j] += d * d * w;
-                    }
-                }
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int64_t n = n0 + 4 * ty + i;
-            if (n >= N) break;
-            const T l = lp1[n];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int m = m0 + tx + 16 * j;
-                if (m < M) Psi1[n * M + m] = dexp(l - T(0.5) * s[i][j]);
-            }
-        }
     }
 }
 
@@ -394,15 +381,25 @@ __global__ __launch_bounds__(256) void psi2_partial_kernel(const int *__restrict
         if (valid[k]) partial[(int64_t)blockIdx.y * P + t0 + k * 256] = acc[k];
 }
 
-// Fixed-order sum of the chunk partials; writes both triangles and psi0.
+// Workgroups below edge^2: fixed-order sum of the chunk partials (16 x 16 pairs
+// each); both triangles and psi0.  The workgroups past them compute Psi1.
 template <typename T>
-__global__ void psi2_reduce_kernel(const int *__restrict__ gate, int64_t N, int M, int64_t P, int64_t nchunks,
-                                   const T *__restrict__ partial, Hyp<T> h, T *__restrict__ psi0,
-                                   T *__restrict__ Psi2, int accumulate) {
+__global__ __launch_bounds__(256) void psi2_reduce_kernel(
+    const int *__restrict__ gate, int64_t N, int M, int Q, int64_t P, int edge, int64_t nchunks,
+    const T *__restrict__ partial, Hyp<T> h, T *__restrict__ psi0, T *__restrict__ Psi2, int accumulate,
+    const T *__restrict__ mu, const T *__restrict__ Z, const T *__restrict__ w1,
+    const T *__restrict__ lp1, T *__restrict__ Psi1) {
     if (gate && gate[0] == 0) return;
-    const int mp = blockIdx.x * kPairTile + threadIdx.x % kPairTile;
-    const int m = blockIdx.y * kPairTile + threadIdx.x / kPairTile;
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0)
+    __shared__ Psi1Lds<T> s_p1;
+    if (blockIdx.x >= (unsigned)(edge * edge)) {
+        psi1_blocks<T>(s_p1, blockIdx.x - edge * edge, gridDim.x - edge * edge, N, M, Q, mu, Z, w1, lp1,
+                       Psi1, [](T x) { return dexp(x); });
+        return;
+    }
+    const int bx = blockIdx.x % edge, by = blockIdx.x / edge;
+    const int mp = bx * kPairTile + threadIdx.x % kPairTile;
+    const int m = by * kPairTile + threadIdx.x / kPairTile;
+    if (blockIdx.x == 0 && threadIdx.x == 0)
         psi0[0] = (accumulate ? psi0[0] : T(0)) + T(N) * h.sf2;
     if (m >= M || mp >= M || m > mp) return;
     const int64_t p = pair_index(m, mp, M);
@@ -423,37 +420,15 @@ __global__ void psi2_reduce_kernel(const int *__restrict__ gate, int64_t N, int 
 }
 
 // ---------------------------------------------------------------- gradients (Alg. 2)
-template <typename T>
-__global__ void sym_kernel(const int *__restrict__ gate, int M, const T *__restrict__ G2, T *__restrict__ G2s) {
-    if (gate && gate[0] == 0) return;
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (int64_t)M * M) return;
-    int m = (int)(i / M), mp = (int)(i - (int64_t)m * M);
-    G2s[i] = T(0.5) * (G2[(int64_t)m * M + mp] + G2[(int64_t)mp * M + m]);
-}
-
-// Gc[k][m] = G2s[m][(m + k) mod M], k = 0 .. M/2: the symmetric pairs kernel
-// reads the pair (m, m + k) of every thread m as one coalesced row.
-template <typename T>
-__global__ void circ_kernel(const int *__restrict__ gate, int M, const T *__restrict__ G2s, T *__restrict__ Gc) {
-    if (gate && gate[0] == 0) return;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (int64_t)(M / 2 + 1) * M) return;
-    const int k = (int)(i / M), m = (int)(i - (int64_t)k * M);
-    int mp = m + k;
-    if (mp >= M) mp -= M;
-    Gc[i] = G2s[(int64_t)m * M + mp];
-}
-
 // One thread per datapoint and range r of pair rows (m = r, r + rr, ...; the
 // Psi1 terms in the column tiles t = r, r + rr, ...): partial dmu_n, dS_n of the
-// range (rowg[r][2][N][Q]) and per-block partials of dl and dsf2.
+// range (om, os: [r][2][N][Q]) and per-block partials of dl and dsf2.
 template <typename T, int QM>
 __global__ __launch_bounds__(kRowBlock) void grad_rows_kernel(const int *__restrict__ gate, 
     int64_t N, int M, int Q, int rr, const T *__restrict__ mu, const T *__restrict__ S,
     const T *__restrict__ Z, const T *__restrict__ w1, const T *__restrict__ w2,
     const T *__restrict__ lp1, const T *__restrict__ lp2, Hyp<T> h, const T *__restrict__ G1,
-    const T *__restrict__ G2s, T *__restrict__ rowg, T *__restrict__ rowpart) {
+    const T *__restrict__ G2s, T *__restrict__ om, T *__restrict__ os, T *__restrict__ rowpart) {
     if (gate && gate[0] == 0) return;
     const int range = blockIdx.y;
     __shared__ T s_g1[kRowBlock][kRowBlock + 1];
@@ -547,7 +522,7 @@ __global__ __launch_bounds__(kRowBlock) void grad_rows_kernel(const int *__restr
     }
 
     if (valid) {
-        T *pm = rowg + ((int64_t)range * 2) * N * Q, *ps = pm + N * Q;
+        T *pm = om + ((int64_t)range * 2) * N * Q, *ps = os + ((int64_t)range * 2) * N * Q;
 #pragma unroll
         for (int q = 0; q < QM; ++q)
             if (q < Q) {
@@ -584,7 +559,8 @@ __global__ __launch_bounds__(kRowBlock) void grad_rows_kernel(const int *__restr
 // One workgroup per (block of inducing inputs, row chunk), one thread per m, the
 // Z table in LDS: dZ_m stays in the thread's registers over the chunk, and per
 // row the dmu / dS contributions are summed over the block's m (wave
-// butterflies, then the waves in order) into rowg[m-block][2][N][Q].
+// butterflies, then the waves in order) into om and os: [m-block][2][N][Q], or dmu and
+// dS themselves where one m-block holds all of M.
 // Ordered form (SYM = false): thread m evaluates W for every (m, m').
 // Symmetric form (SYM = true, the workgroup holds all M): each unordered pair
 // is evaluated once.  Thread m takes the pairs (m, m + k mod M) for k = 0 ..
@@ -598,7 +574,7 @@ __global__ __launch_bounds__(256) void grad_pairs_kernel(const int *__restrict__
     const T *__restrict__ S, const T *__restrict__ Z, const T *__restrict__ w1t,
     const T *__restrict__ w2t, const T *__restrict__ lp1, const T *__restrict__ lp2, Hyp<T> h,
     const T *__restrict__ G1, const T *__restrict__ G2s, const T *__restrict__ Gc,
-    T *__restrict__ rowg, T *__restrict__ colpart, T *__restrict__ rowpart) {
+    T *__restrict__ om, T *__restrict__ os, T *__restrict__ colpart, T *__restrict__ rowpart) {
     if (gate && gate[0] == 0) return;
     extern __shared__ double gp_smem[];
     T *sz = reinterpret_cast<T *>(gp_smem);  // [M][QM], zero beyond Q
@@ -756,8 +732,8 @@ __global__ __launch_bounds__(256) void grad_pairs_kernel(const int *__restrict__
             const int k = tid < Q ? tid : QM + (tid - Q);
             T v = 0;
             for (int w = 0; w < nw; ++w) v += red[b][w][k];
-            const int part = tid < Q ? 0 : 1, q = tid < Q ? tid : tid - Q;
-            rowg[(((int64_t)blockIdx.x * 2 + part) * N + n) * Q + q] = v;
+            const int q = tid < Q ? tid : tid - Q;
+            (tid < Q ? om : os)[((int64_t)blockIdx.x * 2 * N + n) * Q + q] = v;
         }
     }
     if (valid) {
@@ -800,7 +776,7 @@ __global__ __launch_bounds__(512) void grad_pairs_slots_kernel(const int *__rest
     const T *__restrict__ S, const T *__restrict__ Z, const T *__restrict__ w1t,
     const T *__restrict__ w2t, const T *__restrict__ lp1, const T *__restrict__ lp2, Hyp<T> h,
     const T *__restrict__ G1, const T *__restrict__ G2s, const T *__restrict__ Gc,
-    T *__restrict__ rowg, T *__restrict__ colpart, T *__restrict__ rowpart) {
+    T *__restrict__ om, T *__restrict__ os, T *__restrict__ colpart, T *__restrict__ rowpart) {
     if (gate && gate[0] == 0) return;
     extern __shared__ double gs_smem[];
     T *sz = reinterpret_cast<T *>(gs_smem);        // [M][QM], zero beyond Q
@@ -953,8 +929,7 @@ __global__ __launch_bounds__(512) void grad_pairs_slots_kernel(const int *__rest
                 for (int off = 16; off >= 1; off >>= 1) v += __shfl_xor(v, off);
                 const int64_t nn = r0 + it * R + sl;
                 if (u == 0 && nn < r1) {
-                    const int part = j < Q ? 0 : 1, q = j < Q ? j : j - Q;
-                    rowg[((int64_t)part * N + nn) * Q + q] = v;
+                    (j < Q ? om : os)[nn * Q + (j < Q ? j : j - Q)] = v;
                 }
             }
         }
@@ -994,23 +969,6 @@ __global__ __launch_bounds__(512) void grad_pairs_slots_kernel(const int *__rest
                 rowpart[blk * (Q + 1) + (k < QM ? k : Q)] = s2;
             }
         }
-    }
-}
-
-// dmu, dS: the row kernel's range partials summed in range order.
-template <typename T>
-__global__ void grad_rows_reduce_kernel(const int *__restrict__ gate, int64_t NQ, int rr, const T *__restrict__ rowg,
-                                        T *__restrict__ dmu, T *__restrict__ dS) {
-    if (gate && gate[0] == 0) return;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < NQ;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        T a = 0, b = 0;
-        for (int r = 0; r < rr; ++r) {
-            a += rowg[(int64_t)(2 * r) * NQ + i];
-            b += rowg[(int64_t)(2 * r + 1) * NQ + i];
-        }
-        dmu[i] = a;
-        dS[i] = b;
     }
 }
 
@@ -1110,49 +1068,89 @@ __global__ __launch_bounds__(kColBlock) void grad_cols_kernel(const int *__restr
     }
 }
 
-// Fixed-order reduction of the gradient partials into dZ, dl, dsf2: one
-// workgroup per output; thread t sums partials t, t + 256, ..., then a fixed
-// tree combines the 256 sums.
+// Fixed-order reductions of the gradient partials, one launch.  Workgroups below
+// rb: dmu, dS, the nblk partials [nblk][2][N][Q] in block order (none where the
+// kernel before wrote them itself).  Then zb workgroups for dZ: with `wide` 32
+// entries each, 8 groups of 32 threads taking partials g, g + 8, ... (coalesced) and
+// the 8 group sums in order; else one entry at a time, thread t taking partials t,
+// t + 256, ... and a fixed tree (few entries of many partials).  Then one per dl_q
+// and one for dsf2, by the tree.
 template <typename T>
-__global__ __launch_bounds__(256) void grad_reduce_kernel(const int *__restrict__ gate, int64_t N, int M, int Q, int64_t ncol,
-                                                          int64_t nrow, const T *__restrict__ colpart,
-                                                          const T *__restrict__ rowpart, T dL_dpsi0,
-                                                          T *__restrict__ dZ, T *__restrict__ dsf2,
-                                                          T *__restrict__ dl, int accumulate) {
+__global__ __launch_bounds__(256) void grad_finish_kernel(
+    const int *__restrict__ gate, int64_t N, int M, int Q, unsigned rb, int nblk,
+    const T *__restrict__ rowg, T *__restrict__ dmu, T *__restrict__ dS, unsigned zb, int wide,
+    int64_t ncol, int64_t nrow, const T *__restrict__ colpart, const T *__restrict__ rowpart,
+    T dL_dpsi0, T *__restrict__ dZ, T *__restrict__ dsf2, T *__restrict__ dl, int accumulate) {
     if (gate && gate[0] == 0) return;
     __shared__ T red[256];
-    const int64_t MQ = (int64_t)M * Q;
-    // outputs i = blockIdx.x, blockIdx.x + gridDim.x, ... (the grid is capped)
-    for (int64_t i = blockIdx.x; i < MQ + Q + 1; i += gridDim.x) {
-        T s = 0;
-        if (i < MQ) {
-            for (int64_t c = threadIdx.x; c < ncol; c += 256) s += colpart[c * MQ + i];
-        } else {
-            const int k = (int)(i - MQ);  // k < Q: dl_k; k == Q: dsf2
-            for (int64_t b = threadIdx.x; b < nrow; b += 256) s += rowpart[b * (Q + 1) + k];
+    const int t = threadIdx.x;
+    if (blockIdx.x < rb) {
+        const int64_t NQ = N * Q;
+        for (int64_t i = (int64_t)blockIdx.x * 256 + t; i < NQ; i += (int64_t)rb * 256) {
+            T a = 0, b = 0;
+            for (int r = 0; r < nblk; ++r) {
+                a += rowg[(int64_t)(2 * r) * NQ + i];
+                b += rowg[(int64_t)(2 * r + 1) * NQ + i];
+            }
+            dmu[i] = a;
+            dS[i] = b;
         }
+        return;
+    }
+    const int64_t MQ = (int64_t)M * Q;
+    auto tree = [&](T s) {
         __syncthreads();
-        red[threadIdx.x] = s;
+        red[t] = s;
         __syncthreads();
         for (int w = 128; w >= 1; w >>= 1) {
-            if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+            if (t < w) red[t] += red[t + w];
             __syncthreads();
         }
-        if (threadIdx.x != 0) continue;
-        s = red[0];
-        if (i < MQ) {
-            dZ[i] = (accumulate ? dZ[i] : T(0)) + s;
-        } else if (i < MQ + Q) {
-            dl[i - MQ] = (accumulate ? dl[i - MQ] : T(0)) + s;
-        } else {
-            s += dL_dpsi0 * T(N);
-            dsf2[0] = (accumulate ? dsf2[0] : T(0)) + s;
+        return red[0];
+    };
+    const unsigned b = blockIdx.x - rb;
+    if (b < zb) {
+        if (wide) {
+            const int o = t & 31, g = t >> 5;
+            for (int64_t i0 = (int64_t)b * 32; i0 < MQ; i0 += (int64_t)zb * 32) {
+                const int64_t i = min(i0 + o, MQ - 1);
+                T s = 0;
+#pragma unroll 8
+                for (int64_t c = g; c < ncol; c += 8) s += colpart[c * MQ + i];
+                __syncthreads();
+                red[t] = s;
+                __syncthreads();
+                if (g == 0 && i0 + o < MQ) {
+                    T v = 0;
+                    for (int k = 0; k < 8; ++k) v += red[k * 32 + o];
+                    dZ[i] = (accumulate ? dZ[i] : T(0)) + v;
+                }
+            }
+            return;
         }
+        for (int64_t i = b; i < MQ; i += zb) {
+            T s = 0;
+            for (int64_t c = t; c < ncol; c += 256) s += colpart[c * MQ + i];
+            s = tree(s);
+            if (t == 0) dZ[i] = (accumulate ? dZ[i] : T(0)) + s;
+        }
+        return;
+    }
+    const int k = (int)(b - zb);  // k < Q: dl_k; k == Q: dsf2
+    T s = 0;
+    for (int64_t c = t; c < nrow; c += 256) s += rowpart[c * (Q + 1) + k];
+    s = tree(s);
+    if (t != 0) return;
+    if (k < Q) {
+        dl[k] = (accumulate ? dl[k] : T(0)) + s;
+    } else {
+        s += dL_dpsi0 * T(N);
+        dsf2[0] = (accumulate ? dsf2[0] : T(0)) + s;
     }
 }
 
 // Wide form of the ordered pairs gradient, for Q past the pairs kernel's
-// register budget (same outputs as grad_pairs_kernel with SYM = false: rowg,
+// register budget (same outputs as grad_pairs_kernel with SYM = false: om, os,
 // colpart, rowpart).  Two lanes of a wave share an inducing input m (lanes l
 // and l + 32) and each holds QH of its dimensions (lane half hh takes
 // q = hh QH .. hh QH + QH - 1), which halves the per-dimension registers (z,
@@ -1171,7 +1169,7 @@ __global__ __launch_bounds__(256) void grad_wide_kernel(const int *__restrict__ 
     int64_t N, int M, int Q, int64_t rows_per_chunk, const T *__restrict__ mu,
     const T *__restrict__ S, const T *__restrict__ Z, const T *__restrict__ w1t,
     const T *__restrict__ w2t, const T *__restrict__ lp1, const T *__restrict__ lp2, Hyp<T> h,
-    const T *__restrict__ G1, const T *__restrict__ G2s, T *__restrict__ rowg,
+    const T *__restrict__ G1, const T *__restrict__ G2s, T *__restrict__ om, T *__restrict__ os,
     T *__restrict__ colpart, T *__restrict__ rowpart) {
     if (gate && gate[0] == 0) return;
     constexpr int QM = 2 * QH;
@@ -1325,7 +1323,7 @@ __global__ __launch_bounds__(256) void grad_wide_kernel(const int *__restrict__ 
             const int part = tid < Q ? 0 : 1, q = tid < Q ? tid : tid - Q;
             T v = 0;
             for (int w = 0; w < 4; ++w) v += red[b][w][part * QM + q];
-            rowg[(((int64_t)blockIdx.x * 2 + part) * N + n) * Q + q] = v;
+            (part == 0 ? om : os)[((int64_t)blockIdx.x * 2 * N + n) * Q + q] = v;
         }
     }
     if (valid) {
@@ -1370,12 +1368,12 @@ void launch_psi2_partial(const Shape &s, const Plan &p, const T *mu, const T *Z,
 template <typename T, int QM>
 void launch_grads(const Shape &s, const Plan &p, const T *mu, const T *S, const T *Z,
                   const T *w1, const T *w2, const T *lp1, const T *lp2, const Hyp<T> &h,
-                  const T *G1, const T *G2s, T *rowg, T *colpart, T *rowpart, const int *gate,
+                  const T *G1, const T *G2s, T *om, T *os, T *colpart, T *rowpart, const int *gate,
                   hipStream_t st) {
     {
         TimedScope ts(st, "generic_grad_rows");
         grad_rows_kernel<T, QM><<<dim3((unsigned)p.row_blocks, (unsigned)p.rr), kRowBlock, 0, st>>>(gate, 
-            s.N, (int)s.M, (int)s.Q, (int)p.rr, mu, S, Z, w1, w2, lp1, lp2, h, G1, G2s, rowg,
+            s.N, (int)s.M, (int)s.Q, (int)p.rr, mu, S, Z, w1, w2, lp1, lp2, h, G1, G2s, om, os,
             rowpart);
     }
     dim3 grid((unsigned)p.col_blocks, (unsigned)p.ncc, (unsigned)p.cr);
@@ -1385,15 +1383,37 @@ void launch_grads(const Shape &s, const Plan &p, const T *mu, const T *S, const 
                                                          G2s, colpart);
 }
 
+// The per-row tables, and the symmetric part of dL/dPsi2 as `mode` asks.
 template <typename T>
-void rows_pre(const Shape &s, const Plan &p, const T *S, const Hyp<T> &h, void *ws,
-              const int *gate, hipStream_t st) {
-    TimedScope ts(st, "generic_rows_pre");
+void pre(const Shape &s, const Plan &p, const T *S, const Hyp<T> &h, void *ws, const int *gate,
+         int *mark, hipStream_t st, int mode = kSymNone, const T *G2 = nullptr, const T *Z = nullptr,
+         T *G2s = nullptr) {
     // few rows a workgroup where there are few: at least a workgroup per CU
     const int64_t rows = std::max<int64_t>(1, std::min(kPreElems / s.Q, cdiv(s.N, 256)));
-    rows_pre_kernel<T><<<(unsigned)cdiv(s.N, rows), 256, 0, st>>>(gate,
-        s.N, (int)s.Q, (int)rows, S, h, at<T>(ws, p.off_w1), at<T>(ws, p.off_w2), at<T>(ws, p.off_lp1),
-        at<T>(ws, p.off_lp2));
+    const int64_t rb = cdiv(s.N, rows), Mp = cdiv(s.M, 16) * 16;
+    const int64_t n = mode == kSymNone ? 0
+                      : mode == kSymCirc ? (s.M / 2 + 1) * s.M
+                      : mode == kSymPadded ? Mp * Mp : s.M * s.M;
+    TimedScope ts(st, "generic_pre");
+    pre_kernel<T><<<(unsigned)(rb + cdiv(n, 256)), 256, 0, st>>>(
+        gate, mark, s.N, (int)s.Q, (int)rows, (unsigned)rb, S, h, at<T>(ws, p.off_w1), at<T>(ws, p.off_w2),
+        at<T>(ws, p.off_lp1), at<T>(ws, p.off_lp2), mode, (int)s.M, (int)Mp, G2, Z, G2s);
+}
+
+// nblk > 1: dmu and dS from rowg's partials; else the caller's kernel wrote them.
+template <typename T>
+void finish(const Shape &s, int64_t nblk, const T *rowg, T *dmu, T *dS, int64_t ncol, int64_t nrow,
+            const T *colpart, const T *rowpart, T dL_dpsi0, T *dZ, T *dsf2, T *dl, int accumulate,
+            const int *gate, hipStream_t st) {
+    const int64_t rb = nblk > 1 ? std::min<int64_t>(cdiv(s.N * s.Q, 256), kGridCap) : 0;
+    // 32 entries a workgroup once that leaves four workgroups per CU (the tree reads
+    // one value per partial and lane group: 82 us against 20 at 5,120 entries of 1,024)
+    const int wide = s.M * s.Q >= 2048 || ncol <= 32;
+    const int64_t zb = std::min<int64_t>(wide ? cdiv(s.M * s.Q, 32) : s.M * s.Q, kGridCap);
+    TimedScope ts(st, "generic_grad_finish");
+    grad_finish_kernel<T><<<(unsigned)(rb + zb + s.Q + 1), 256, 0, st>>>(
+        gate, s.N, (int)s.M, (int)s.Q, (unsigned)rb, (int)nblk, rowg, dmu, dS, (unsigned)zb, wide, ncol,
+        nrow, colpart, rowpart, dL_dpsi0, dZ, dsf2, dl, accumulate);
 }
 
 }  // namespace
@@ -1403,22 +1423,16 @@ size_t generic_workspace_bytes(const Shape &s, size_t elem) { return make_plan(s
 template <typename T>
 hipError_t generic_psi_stats(const Shape &s, const T *mu, const T *S, const T *Z,
                              const Hyp<T> &h, T *psi0, T *Psi1, T *Psi2, int accumulate,
-                             void *ws, const int *gate, hipStream_t st) {
+                             void *ws, const int *gate, int *mark, hipStream_t st) {
     const Plan p = make_plan(s, sizeof(T));
-    rows_pre<T>(s, p, S, h, ws, gate, st);
+    pre<T>(s, p, S, h, ws, gate, mark, st);
     const T *w1 = at<T>(ws, p.off_w1), *w2 = at<T>(ws, p.off_w2);
     const T *lp1 = at<T>(ws, p.off_lp1), *lp2 = at<T>(ws, p.off_lp2);
-    if (Psi1) {
-        TimedScope ts(st, "generic_psi1");
-        const int64_t mt = cdiv(s.M, kPsi1Tile), nt = cdiv(s.N, kPsi1Tile);
-        const dim3 g((unsigned)mt, (unsigned)std::min(nt, std::max<int64_t>(1, kGridCap / mt)));
-        psi1_kernel<T><<<g, 256, 0, st>>>(gate, s.N, (int)s.M, (int)s.Q, mu, Z, w1, lp1, Psi1);
-    }
     if constexpr (sizeof(T) == 8) {
         const size_t budget = p.total - p.off_p2;
         if (f64_stats_fit(s, budget))
-            return f64_psi2(s, mu, Z, w2, lp2, h, psi0, Psi2, accumulate, at<char>(ws, p.off_p2),
-                            budget, st);
+            return f64_psi2(s, mu, Z, w1, w2, lp1, lp2, h, psi0, Psi1, Psi2, accumulate,
+                            at<char>(ws, p.off_p2), budget, st);
     }
     T *partial = at<T>(ws, p.off_p2);
     switch (fwd_qm(s.Q)) {
@@ -1429,11 +1443,11 @@ hipError_t generic_psi_stats(const Shape &s, const T *mu, const T *S, const T *Z
         default: launch_psi2_partial<T, 64>(s, p, mu, Z, w2, lp2, h, partial, gate, st); break;
 #undef GPPS_FWD
     }
-    dim3 g((unsigned)p.tiles_edge, (unsigned)p.tiles_edge);
-    TimedScope ts(st, "generic_psi2_reduce");
-    psi2_reduce_kernel<T><<<g, kPairTile * kPairTile, 0, st>>>(gate, s.N, (int)s.M, s.P, p.nc2,
-                                                               partial, h, psi0, Psi2,
-                                                               accumulate);
+    const int64_t tiles = p.tiles_edge * p.tiles_edge;
+    TimedScope ts(st, "generic_psi2_reduce_psi1");
+    psi2_reduce_kernel<T><<<(unsigned)(tiles + psi1_grid(s.N, s.M, Psi1, kGridCap)), 256, 0, st>>>(
+        gate, s.N, (int)s.M, (int)s.Q, s.P, (int)p.tiles_edge, p.nc2, partial, h, psi0, Psi2, accumulate,
+        mu, Z, w1, lp1, Psi1);
     return hipGetLastError();
 }
 
@@ -1441,45 +1455,34 @@ template <typename T>
 hipError_t generic_psi_grads(const Shape &s, const T *mu, const T *S, const T *Z,
                              const Hyp<T> &h, T dL_dpsi0, const T *G1, const T *G2, T *dmu,
                              T *dS, T *dZ, T *dsf2, T *dl, int accumulate, void *ws,
-                             const int *gate, hipStream_t st) {
+                             const int *gate, int *mark, hipStream_t st) {
     const Plan p = make_plan(s, sizeof(T));
-    rows_pre<T>(s, p, S, h, ws, gate, st);
     const T *w1 = at<T>(ws, p.off_w1), *w2 = at<T>(ws, p.off_w2);
     const T *lp1 = at<T>(ws, p.off_lp1), *lp2 = at<T>(ws, p.off_lp2);
-    const int64_t total = s.M * s.Q + s.Q + 1;
     if constexpr (sizeof(T) == 8) {
         const F64GradPlan f = f64_grad_plan(s, p.total - p.off_p2);
         if (f.ok) {
             char *region = at<char>(ws, p.off_p2);
-            const hipError_t e = f64_psi2_grads(s, f, mu, S, Z, w1, w2, lp1, lp2, h, G1, G2, dmu, dS,
+            T *Gc = G2 ? at<T>(region, f.off_gc) : nullptr;
+            pre<T>(s, p, S, h, ws, gate, mark, st, G2 ? kSymPadded : kSymNone, G2, Z, Gc);
+            const hipError_t e = f64_psi2_grads(s, f, mu, S, Z, w1, w2, lp1, lp2, h, G1, Gc, dmu, dS,
                                                 region, st);
             if (e != hipSuccess) return e;
-            TimedScope ts(st, "generic_grad_reduce");
-            if (f.groups > 1)
-                grad_rows_reduce_kernel<T><<<(unsigned)std::min<int64_t>(cdiv(s.N * s.Q, 256), kGridCap),
-                                             256, 0, st>>>(gate, s.N * s.Q, f.groups,
-                                                           at<T>(region, f.off_rowg), dmu, dS);
-            grad_reduce_kernel<T><<<(unsigned)std::min<int64_t>(total, kGridCap), 256, 0, st>>>(
-                gate, s.N, (int)s.M, (int)s.Q, f.chunks, f.chunks * f.groups, at<T>(region, f.off_colp),
-                at<T>(region, f.off_rowp), dL_dpsi0, dZ, dsf2, dl, accumulate);
+            finish<T>(s, f.groups, at<T>(region, f.off_rowg), dmu, dS, f.chunks, f.chunks * f.groups,
+                      at<T>(region, f.off_colp), at<T>(region, f.off_rowp), dL_dpsi0, dZ, dsf2, dl,
+                      accumulate, gate, st);
             return hipGetLastError();
         }
     }
-    T *G2s = nullptr;
-    if (G2) {
-        G2s = at<T>(ws, p.off_g2s);
-        TimedScope ts(st, "generic_sym");
-        sym_kernel<T><<<(unsigned)cdiv(s.M * s.M, 256), 256, 0, st>>>(gate, (int)s.M, G2, G2s);
-    }
     T *colpart = at<T>(ws, p.off_colp), *rowpart = at<T>(ws, p.off_rowp);
     T *rowg = at<T>(ws, p.off_rowg);
+    const bool sym = p.pairs && p.psym && G2;
+    T *G2s = G2 ? at<T>(ws, sym ? p.off_gc : p.off_g2s) : nullptr;
+    pre<T>(s, p, S, h, ws, gate, mark, st, !G2 ? kSymNone : sym ? kSymCirc : kSymPlain, G2, Z, G2s);
+    // one block of columns (or range of pair rows) writes dmu and dS themselves
+    const int64_t nblk = p.pairs ? p.pmb : p.wide ? p.wmb : p.rr;
+    T *om = nblk > 1 ? rowg : dmu, *os = nblk > 1 ? rowg + s.N * s.Q : dS;
     if (p.pairs) {
-        const bool sym = p.psym && G2s;
-        T *Gc = at<T>(ws, p.off_gc);
-        if (sym) {
-            TimedScope ts(st, "generic_circ");
-            circ_kernel<T><<<(unsigned)cdiv((s.M / 2 + 1) * s.M, 256), 256, 0, st>>>(gate, (int)s.M, G2s, Gc);
-        }
         const size_t lds = sizeof(T) * s.M * (pairs_qm(s.Q) + (sym ? 2 * kBand : 0));
         const size_t lds_slots =
             sizeof(T) * s.M * (pairs_qm(s.Q) + p.prs * 2 * kSlotBand + p.prs * 2 * pairs_qm(s.Q));
@@ -1489,17 +1492,17 @@ hipError_t generic_psi_grads(const Shape &s, const T *mu, const T *S, const T *Z
 #define GPPS_PAIRS(QMV)                                                                            \
     do {                                                                                           \
         if (sym && p.pslots)                                                                       \
-            grad_pairs_slots_kernel<T, QMV><<<grid, p.psthreads, lds_slots, st>>>(gate,                  \
+            grad_pairs_slots_kernel<T, QMV><<<grid, p.psthreads, lds_slots, st>>>(gate,            \
                 s.N, (int)s.M, (int)s.Q, p.prs, p.prows, mu, S, Z, w1, w2, lp1, lp2, h, G1, G2s,   \
-                Gc, rowg, colpart, rowpart);                                                       \
+                G2s, om, os, colpart, rowpart);                                                    \
         else if (sym)                                                                              \
-            grad_pairs_kernel<T, QMV, true><<<grid, p.pthreads, lds, st>>>(gate,                         \
-                s.N, (int)s.M, (int)s.Q, p.prows, mu, S, Z, w1, w2, lp1, lp2, h, G1, G2s, Gc,      \
-                rowg, colpart, rowpart);                                                           \
+            grad_pairs_kernel<T, QMV, true><<<grid, p.pthreads, lds, st>>>(gate,                   \
+                s.N, (int)s.M, (int)s.Q, p.prows, mu, S, Z, w1, w2, lp1, lp2, h, G1, G2s, G2s,     \
+                om, os, colpart, rowpart);                                                         \
         else                                                                                       \
-            grad_pairs_kernel<T, QMV, false><<<grid, p.pthreads, lds, st>>>(gate,                        \
-                s.N, (int)s.M, (int)s.Q, p.prows, mu, S, Z, w1, w2, lp1, lp2, h, G1, G2s, Gc,      \
-                rowg, colpart, rowpart);                                                           \
+            grad_pairs_kernel<T, QMV, false><<<grid, p.pthreads, lds, st>>>(gate,                  \
+                s.N, (int)s.M, (int)s.Q, p.prows, mu, S, Z, w1, w2, lp1, lp2, h, G1, G2s, nullptr, \
+                om, os, colpart, rowpart);                                                         \
     } while (0)
             switch (pairs_qm(s.Q)) {
                 case 1: GPPS_PAIRS(1); break;
@@ -1511,12 +1514,8 @@ hipError_t generic_psi_grads(const Shape &s, const T *mu, const T *S, const T *Z
             }
 #undef GPPS_PAIRS
         }
-        TimedScope ts(st, "generic_grad_reduce");
-        grad_rows_reduce_kernel<T><<<(unsigned)std::min<int64_t>(cdiv(s.N * s.Q, 256), kGridCap), 256, 0, st>>>(gate, 
-            s.N * s.Q, (int)p.pmb, rowg, dmu, dS);
-        grad_reduce_kernel<T><<<(unsigned)std::min<int64_t>(total, kGridCap), 256, 0, st>>>(gate, 
-            s.N, (int)s.M, (int)s.Q, p.pchunks, p.pmb * p.pchunks, colpart, rowpart, dL_dpsi0, dZ,
-            dsf2, dl, accumulate);
+        finish<T>(s, nblk, rowg, dmu, dS, p.pchunks, p.pmb * p.pchunks, colpart, rowpart, dL_dpsi0, dZ,
+                  dsf2, dl, accumulate, gate, st);
         return hipGetLastError();
     }
     if (p.wide) {
@@ -1526,9 +1525,9 @@ hipError_t generic_psi_grads(const Shape &s, const T *mu, const T *S, const T *Z
             TimedScope ts(st, "generic_grad_wide");
 #define GPPS_WIDE(QHV)                                                                             \
     case QHV:                                                                                      \
-        grad_wide_kernel<T, QHV><<<grid, 256, lds, st>>>(gate, s.N, (int)s.M, (int)s.Q, p.wrows,  \
+        grad_wide_kernel<T, QHV><<<grid, 256, lds, st>>>(gate, s.N, (int)s.M, (int)s.Q, p.wrows,   \
                                                           mu, S, Z, w1, w2, lp1, lp2, h, G1, G2s,  \
-                                                          rowg, colpart, rowpart);                 \
+                                                          om, os, colpart, rowpart);               \
         break
             switch (p.wqh) {
                 GPPS_WIDE(4);
@@ -1549,50 +1548,41 @@ hipError_t generic_psi_grads(const Shape &s, const T *mu, const T *S, const T *Z
             }
 #undef GPPS_WIDE
         }
-        TimedScope ts(st, "generic_grad_reduce");
-        grad_rows_reduce_kernel<T><<<(unsigned)std::min<int64_t>(cdiv(s.N * s.Q, 256), kGridCap), 256, 0, st>>>(gate,
-            s.N * s.Q, (int)p.wmb, rowg, dmu, dS);
-        grad_reduce_kernel<T><<<(unsigned)std::min<int64_t>(total, kGridCap), 256, 0, st>>>(gate,
-            s.N, (int)s.M, (int)s.Q, p.wchunks, p.wmb * p.wchunks, colpart, rowpart, dL_dpsi0, dZ,
-            dsf2, dl, accumulate);
+        finish<T>(s, nblk, rowg, dmu, dS, p.wchunks, p.wmb * p.wchunks, colpart, rowpart, dL_dpsi0, dZ,
+                  dsf2, dl, accumulate, gate, st);
         return hipGetLastError();
     }
-    if (s.Q <= 4)
-        launch_grads<T, 4>(s, p, mu, S, Z, w1, w2, lp1, lp2, h, G1, G2s, rowg, colpart, rowpart, gate, st);
-    else if (s.Q <= 8)
-        launch_grads<T, 8>(s, p, mu, S, Z, w1, w2, lp1, lp2, h, G1, G2s, rowg, colpart, rowpart, gate, st);
-    else if (s.Q <= 16)
-        launch_grads<T, 16>(s, p, mu, S, Z, w1, w2, lp1, lp2, h, G1, G2s, rowg, colpart, rowpart, gate, st);
-    else if (s.Q <= 32)
-        launch_grads<T, 32>(s, p, mu, S, Z, w1, w2, lp1, lp2, h, G1, G2s, rowg, colpart, rowpart, gate, st);
-    else
-        launch_grads<T, 64>(s, p, mu, S, Z, w1, w2, lp1, lp2, h, G1, G2s, rowg, colpart, rowpart, gate, st);
-    TimedScope ts(st, "generic_grad_reduce");
-    grad_rows_reduce_kernel<T><<<(unsigned)std::min<int64_t>(cdiv(s.N * s.Q, 256), kGridCap), 256, 0, st>>>(gate, s.N * s.Q, (int)p.rr,
-                                                                              rowg, dmu, dS);
-    grad_reduce_kernel<T><<<(unsigned)std::min<int64_t>(total, kGridCap), 256, 0, st>>>(gate, 
-        s.N, (int)s.M, (int)s.Q, p.ncc * p.cr, p.rr * p.row_blocks, colpart, rowpart, dL_dpsi0,
-        dZ, dsf2, dl, accumulate);
+#define GPPS_ROWS(QMV)                                                                             \
+    launch_grads<T, QMV>(s, p, mu, S, Z, w1, w2, lp1, lp2, h, G1, G2s, om, os, colpart, rowpart,   \
+                         gate, st)
+    if (s.Q <= 4) GPPS_ROWS(4);
+    else if (s.Q <= 8) GPPS_ROWS(8);
+    else if (s.Q <= 16) GPPS_ROWS(16);
+    else if (s.Q <= 32) GPPS_ROWS(32);
+    else GPPS_ROWS(64);
+#undef GPPS_ROWS
+    finish<T>(s, nblk, rowg, dmu, dS, p.ncc * p.cr, p.rr * p.row_blocks, colpart, rowpart, dL_dpsi0, dZ,
+              dsf2, dl, accumulate, gate, st);
     return hipGetLastError();
 }
 
 template hipError_t generic_psi_stats<float>(const Shape &, const float *, const float *,
                                              const float *, const Hyp<float> &, float *,
                                              float *, float *, int, void *, const int *,
-                                             hipStream_t);
+                                             int *, hipStream_t);
 template hipError_t generic_psi_stats<double>(const Shape &, const double *, const double *,
                                               const double *, const Hyp<double> &, double *,
                                               double *, double *, int, void *, const int *,
-                                              hipStream_t);
+                                              int *, hipStream_t);
 template hipError_t generic_psi_grads<float>(const Shape &, const float *, const float *,
                                              const float *, const Hyp<float> &, float,
                                              const float *, const float *, float *, float *,
                                              float *, float *, float *, int, void *,
-                                             const int *, hipStream_t);
+                                             const int *, int *, hipStream_t);
 template hipError_t generic_psi_grads<double>(const Shape &, const double *, const double *,
                                               const double *, const Hyp<double> &, double,
                                               const double *, const double *, double *,
                                               double *, double *, double *, double *, int,
-                                              void *, const int *, hipStream_t);
+                                              void *, const int *, int *, hipStream_t);
 
 }  // namespace gpps

@@ -9,7 +9,7 @@
 
 namespace {
 
-constexpr int kPathAuto = 0, kPathGeneric = 1, kPathMfma = 2;
+constexpr int kPathAuto = 0, kPathGeneric = 1, kPathMfma = 2, kPathSmall = 3;
 
 bool valid_dtype(gpps_dtype dt) { return dt == GPPS_F32 || dt == GPPS_F64; }
 
@@ -53,10 +53,22 @@ int requested_path(int flags, int allowed) {
 // cannot).  Calls without S (known inputs) always take the known-input path.
 constexpr int kPathKnown = 100;
 
+// Calls too small for the matrix-core path's launches (its seven or nine and the three
+// gated generic ones, against three): in us per call, matrix-core / generic, statistics
+// and gradients 42 / 27 and 51 / 31 at N = 200, M = 10, Q = 2, 43 / 26 and 64 / 31 at
+// N = 200, M = 50, Q = 10, 41 / 26 and 53 / 31 at N = 1,000, M = 32, Q = 2.  The
+// generic kernels stay ahead up to about ten times this work, but there the
+// matrix-core path, and the route word that tells whether its range guard passed,
+// is what calls without a path flag have always taken: only the smallest move.
+constexpr double kSmallWork = 1.5e7;
+bool small_call(const gpps::Shape &s) {
+    return (double)s.N * (double)(s.M * s.M + 1000) * (double)(s.Q + 6) <= kSmallWork;
+}
+
 int choose_path(gpps_dtype dt, const gpps::Shape &s, const void *S, int requested) {
     if (!S) return kPathKnown;
     const bool mfma_ok = dt == GPPS_F32 && gpps::mfma_supports(s);
-    if (requested == kPathAuto) return mfma_ok ? kPathMfma : kPathGeneric;
+    if (requested == kPathAuto) return !mfma_ok ? kPathGeneric : small_call(s) ? kPathSmall : kPathMfma;
     if (requested == kPathMfma) return mfma_ok ? kPathMfma : -1;
     return kPathGeneric;
 }
@@ -97,6 +109,7 @@ hipError_t run_stats(gpps_dtype dt, int path, const gpps::Shape &s, const void *
     if (dt == GPPS_F32) {
         const auto h = make_hyp<float>(sigma_f2, l, s.Q);
         const int *gate = nullptr;
+        int *mark = path == kPathSmall ? route_word(dt, s, ws) : nullptr;
         if (path == kPathMfma) {
             // the matrix-core kernels, then the generic ones gated by the route
             // word: only one of the two sets does the work
@@ -109,12 +122,12 @@ hipError_t run_stats(gpps_dtype dt, int path, const gpps::Shape &s, const void *
         }
         return gpps::generic_psi_stats<float>(s, (const float *)mu, (const float *)S,
                                               (const float *)Z, h, (float *)psi0, (float *)Psi1,
-                                              (float *)Psi2, accumulate != 0, ws, gate, st);
+                                              (float *)Psi2, accumulate != 0, ws, gate, mark, st);
     }
     const auto h = make_hyp<double>(sigma_f2, l, s.Q);
     return gpps::generic_psi_stats<double>(s, (const double *)mu, (const double *)S,
                                            (const double *)Z, h, (double *)psi0, (double *)Psi1,
-                                           (double *)Psi2, accumulate != 0, ws, nullptr, st);
+                                           (double *)Psi2, accumulate != 0, ws, nullptr, nullptr, st);
 }
 
 hipError_t run_grads(gpps_dtype dt, int path, const gpps::Shape &s, const void *mu, const void *S,
@@ -135,6 +148,7 @@ hipError_t run_grads(gpps_dtype dt, int path, const gpps::Shape &s, const void *
     if (dt == GPPS_F32) {
         const auto h = make_hyp<float>(sigma_f2, l, s.Q);
         const int *gate = nullptr;
+        int *mark = path == kPathSmall ? route_word(dt, s, ws) : nullptr;
         if (path == kPathMfma) {
             int *route = route_word(dt, s, ws);
             hipError_t e = gpps::mfma_psi_grads(
@@ -149,7 +163,7 @@ hipError_t run_grads(gpps_dtype dt, int path, const gpps::Shape &s, const void *
                                               (const float *)dL_dPsi1, (const float *)dL_dPsi2,
                                               (float *)dmu, (float *)dS, (float *)dZ,
                                               (float *)dsigma_f2, (float *)dl, accumulate != 0,
-                                              ws, gate, st);
+                                              ws, gate, mark, st);
     }
     const auto h = make_hyp<double>(sigma_f2, l, s.Q);
     return gpps::generic_psi_grads<double>(s, (const double *)mu, (const double *)S,
@@ -157,7 +171,7 @@ hipError_t run_grads(gpps_dtype dt, int path, const gpps::Shape &s, const void *
                                            (const double *)dL_dPsi1, (const double *)dL_dPsi2,
                                            (double *)dmu, (double *)dS, (double *)dZ,
                                            (double *)dsigma_f2, (double *)dl, accumulate != 0, ws,
-                                           nullptr, st);
+                                           nullptr, nullptr, st);
 }
 
 }  // namespace

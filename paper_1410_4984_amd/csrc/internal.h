@@ -52,19 +52,21 @@ class TimedScope {
 // Vector-ALU kernels templated on the element type; they serve F64, any F32
 // shape the matrix-core path does not take, and F32 calls whose operands the
 // matrix-core range guard rejects.  gate: NULL, or a device word; the kernels
-// then do their work only where it is nonzero (the matrix-core route word).
+// then do their work only where it is nonzero (the matrix-core route word).  mark:
+// NULL, or the route word of a call that could have taken the matrix cores and was
+// too small for them, which gets 1.
 size_t generic_workspace_bytes(const Shape &s, size_t elem);
 
 template <typename T>
 hipError_t generic_psi_stats(const Shape &s, const T *mu, const T *S, const T *Z,
                              const Hyp<T> &h, T *psi0, T *Psi1, T *Psi2, int accumulate,
-                             void *ws, const int *gate, hipStream_t st);
+                             void *ws, const int *gate, int *mark, hipStream_t st);
 
 template <typename T>
 hipError_t generic_psi_grads(const Shape &s, const T *mu, const T *S, const T *Z,
                              const Hyp<T> &h, T dL_dpsi0, const T *G1, const T *G2, T *dmu,
                              T *dS, T *dZ, T *dsf2, T *dl, int accumulate, void *ws,
-                             const int *gate, hipStream_t st);
+                             const int *gate, int *mark, hipStream_t st);
 
 // ---------------------------------------------------------------- double precision
 // Psi2 and its gradients in F64 on the matrix cores.  They take the generic path's
@@ -81,9 +83,10 @@ bool f64_stats_wanted(const Shape &s);
 bool f64_grads_wanted(const Shape &s);
 size_t f64_region_bytes(const Shape &s);   // the region with which no plan is cut short
 bool f64_stats_fit(const Shape &s, size_t budget);
-hipError_t f64_psi2(const Shape &s, const double *mu, const double *Z, const double *w2,
-                    const double *lp2, const Hyp<double> &h, double *psi0, double *Psi2,
-                    int accumulate, void *ws, size_t budget, hipStream_t st);
+hipError_t f64_psi2(const Shape &s, const double *mu, const double *Z, const double *w1,
+                    const double *w2, const double *lp1, const double *lp2, const Hyp<double> &h,
+                    double *psi0, double *Psi1, double *Psi2, int accumulate, void *ws, size_t budget,
+                    hipStream_t st);
 
 struct F64GradPlan {
     bool ok;                          // the region holds it
@@ -96,7 +99,7 @@ F64GradPlan f64_grad_plan(const Shape &s, size_t budget);
 hipError_t f64_psi2_grads(const Shape &s, const F64GradPlan &p, const double *mu, const double *S,
                           const double *Z, const double *w1, const double *w2, const double *lp1,
                           const double *lp2, const Hyp<double> &h, const double *G1,
-                          const double *G2, double *dmu, double *dS, void *ws, hipStream_t st);
+                          const double *Gc, double *dmu, double *dS, void *ws, hipStream_t st);
 
 // ---------------------------------------------------------------- matrix-core path
 // F32 only: per-datapoint Gram blocks and W * D products on MFMA, exp on VALU.

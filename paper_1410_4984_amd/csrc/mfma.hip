@@ -206,7 +206,7 @@ struct MPlan {
     int64_t fin_blocks;    // finalize: blocks of kFinRows rows
     size_t lds_fwd, lds_grad;
     size_t off_K, off_hq, off_w2, off_hl, off_w1, off_l1, off_zc, off_bt, off_bc, off_t1, off_g2,
-        off_fp, off_rs, off_dz, off_dl, off_gmax, off_gpart, off_bmax, off_smax, total;
+        off_fp, off_rs, off_dz, off_dl, off_gpart, off_bmax, off_smax, total;
 };
 
 // Forward LDS layout (floats):
@@ -362,8 +362,12 @@ __host__ __device__ inline LdsS lds_sym_layout(int nb, int DSF, int Q, int nk, i
     return L;
 }
 
-MPlan make_mplan(const Shape &s) {
+MPlan carve_mplan(const Shape &s, bool few_rows) {
     MPlan p{};
+    // fewest rows per chunk: one staged batch (a row's latency in a lone workgroup is
+    // about 2 us: at N = 5,000, M = 50, Q = 10 the gradient takes 75 us in chunks of 16
+    // rows and 39 in chunks of 5; at N = 200, M = 10 42 and 15)
+    const int64_t fmin = few_rows ? 8 : 32;
     p.Mp = cdiv(s.M, kTile) * kTile;
     p.nb = (int)(p.Mp / kTile);
     p.nqb = s.Q + 1 <= 32 ? 1 : 2;
@@ -399,7 +403,7 @@ MPlan make_mplan(const Shape &s) {
     const int64_t fslots = p.fsym ? (fsym_ranges(p.nb) > 1 ? 2 : 1) * kCUs *
                                         std::min<int64_t>(2, std::max<int64_t>(1, kLdsBytes / p.lds_fwd))
                                   : kCUs * std::min<int64_t>(6, 2 * std::max<int64_t>(1, kLdsBytes / p.lds_fwd));
-    p.fchunks = std::max<int64_t>(1, std::min(fslots / p.fgroups, cdiv(s.N, 32)));
+    p.fchunks = std::max<int64_t>(1, std::min(fslots / p.fgroups, cdiv(s.N, fmin)));
     p.frows = cdiv(s.N, p.fchunks);
     p.fchunks = cdiv(s.N, p.frows);
     // symmetric gradient kernel (one workgroup of nb waves per row chunk) where
@@ -467,13 +471,14 @@ MPlan make_mplan(const Shape &s) {
                                       1, std::min<int64_t>(kLdsBytes / p.lds_grad,
                                                            gwaves / p.wpg));
     const int64_t tgroups = p.gsplit ? 4 : p.ggroups;   // tile-kernel workgroups per chunk
-    p.gchunks = std::max<int64_t>(1, std::min((p.gsym || p.wpg >= 8 ? 1 : 2) * gslots / tgroups, cdiv(s.N, 16)));
+    const int64_t gmin = few_rows ? (p.gsym && p.grb < kSymRBMax ? 4 : 8) : 16;
+    p.gchunks = std::max<int64_t>(1, std::min((p.gsym || p.wpg >= 8 ? 1 : 2) * gslots / tgroups, cdiv(s.N, gmin)));
     p.grows = cdiv(s.N, p.gchunks);
     p.gchunks = cdiv(s.N, p.grows);
     p.dzslabs = p.gchunks * p.njr;
     if (p.gsplit) {
         // each half: one round of one-workgroup-per-CU chunks
-        p.sgchunks = std::max<int64_t>(1, std::min<int64_t>(kCUs, cdiv(s.N, 16)));
+        p.sgchunks = std::max<int64_t>(1, std::min<int64_t>(kCUs, cdiv(s.N, gmin)));
         p.sgrows = cdiv(s.N, p.sgchunks);
         p.sgchunks = cdiv(s.N, p.sgrows);
         p.ggroups = 6;
@@ -497,12 +502,18 @@ MPlan make_mplan(const Shape &s) {
     p.off_rs = take(sizeof(float) * p.ggroups * s.N * (5 * s.Q + 2));
     p.off_dz = take(sizeof(float) * p.dzslabs * s.M * s.Q);
     p.off_dl = take(sizeof(float) * p.fin_blocks * (s.Q + 1));
-    p.off_gmax = take(sizeof(float) * 2);
     p.off_gpart = take(sizeof(float) * cdiv(s.N, 64));
     p.off_bmax = take(sizeof(float) * cdiv(p.Mp, 256) * s.N);
     p.off_smax = take(sizeof(float) * 2 * cdiv(p.Mp * p.Mp, 256));
     p.total = o;
     return p;
+}
+
+MPlan make_mplan(const Shape &s) {
+    // the short chunks, unless their partial results would take the call past the
+    // allocation-free entry point's scratch
+    const MPlan p = carve_mplan(s, true);
+    return p.total <= size_t(GPPS_SCRATCH_BYTES) - 256 ? p : carve_mplan(s, false);
 }
 
 float *fat(void *ws, size_t off) { return reinterpret_cast<float *>(static_cast<char *>(ws) + off); }
@@ -514,11 +525,9 @@ float *fat(void *ws, size_t off) { return reinterpret_cast<float *>(static_cast<
 // R_q = 0), and R_q = max_m |z_mq - zc_q|.  G = 256 / Q groups of Q threads take
 // rows m = g, g + G, ... (coalesced); the G partial sums (then maxima) of each
 // dimension are combined in group order.
-__global__ __launch_bounds__(256) void mfma_centre_kernel(int M, int Q,
-                                                          const float *__restrict__ Z,
-                                                          float *__restrict__ zt) {
-    __shared__ float part[256];
-    __shared__ float s_zc[GPPS_MAX_Q];
+// part: 256 floats of LDS, zt: [4][Q] (LDS or global); every thread of the 256
+// takes part, the results are visible after a barrier.
+__device__ inline void centre_table(int M, int Q, const float *__restrict__ Z, float *part, float *zt) {
     const int t = threadIdx.x, G = 256 / Q;
     const bool act = t < G * Q;
     const int g = t / Q, q = t - g * Q;
@@ -529,15 +538,16 @@ __global__ __launch_bounds__(256) void mfma_centre_kernel(int M, int Q,
         part[t] = s;
     }
     __syncthreads();
-    if (t < Q) {
+    float c = 0.f;
+    if (act) {
         float s = 0.f;
-        for (int k = 0; k < G; ++k) s += part[k * Q + t];
-        s_zc[t] = s / (float)M;
+        for (int k = 0; k < G; ++k) s += part[k * Q + q];
+        c = s / (float)M;
     }
     __syncthreads();
     if (act) {
-        const float c = s_zc[q];
         float r = 0.f;
+#pragma unroll 8
         for (int m = g; m < M; m += G) r = fmaxf(r, fabsf(Z[(int64_t)m * Q + q] - c));
         part[t] = r;
     }
@@ -547,12 +557,25 @@ __global__ __launch_bounds__(256) void mfma_centre_kernel(int M, int Q,
         for (int k = 0; k < G; ++k) r = fmaxf(r, part[k * Q + t]);
         int e = 0;
         if (r > 0.f && r <= 3.0e38f) frexpf(r, &e);
-        zt[t] = s_zc[t];
+        zt[t] = c;
         zt[Q + t] = ldexpf(1.f, e);
         zt[2 * Q + t] = ldexpf(1.f, -e);
         zt[3 * Q + t] = r;
     }
 }
+
+__global__ __launch_bounds__(256) void mfma_centre_kernel(int M, int Q,
+                                                          const float *__restrict__ Z,
+                                                          float *__restrict__ zt) {
+    __shared__ float part[256];
+    centre_table(M, Q, Z, part, zt);
+}
+
+// Up to this many entries of Z every workgroup of the per-row tables kernel forms the
+// centring table itself (8 loads a thread and pass, about 2 us) and the call saves a
+// launch (5 us); at M = 256, Q = 20 the passes' latency over three rounds of
+// workgroups costs what the launch does.
+constexpr int64_t kOwnCentre = 2048;
 
 // Per-row tables, 64 datapoints per workgroup.  For every (n, q), with
 // w2 = 1/(l^2 + 2S):
@@ -569,14 +592,25 @@ __global__ __launch_bounds__(256) void mfma_centre_kernel(int M, int Q,
 constexpr int kRowsPerBlock = 64;
 __global__ __launch_bounds__(256) void mfma_rows_kernel(
     int64_t N, int Q, const float *__restrict__ mu, const float *__restrict__ S,
-    const float *__restrict__ zt, Hyp<float> h, float *__restrict__ Kt, float *__restrict__ hq,
-    float *__restrict__ w2t, float *__restrict__ hl, float *__restrict__ w1t,
-    float *__restrict__ l1, float *__restrict__ gpart) {
+    float *__restrict__ ztg, int M, const float *__restrict__ Z, int own, Hyp<float> h,
+    float *__restrict__ Kt, float *__restrict__ hq, float *__restrict__ w2t, float *__restrict__ hl,
+    float *__restrict__ w1t, float *__restrict__ l1, float *__restrict__ gpart) {
+    // own: the centring table is formed here, by every workgroup, and written by the first
+    __shared__ float zt[4 * GPPS_MAX_Q];
     __shared__ float la2[kRowsPerBlock][GPPS_MAX_Q + 1], la1[kRowsPerBlock][GPPS_MAX_Q + 1];
     __shared__ float lb[kRowsPerBlock][GPPS_MAX_Q + 1], lx[kRowsPerBlock][GPPS_MAX_Q + 1];
     __shared__ float red[kRowsPerBlock];
     const int64_t n0 = (int64_t)blockIdx.x * kRowsPerBlock;
     const int rows = (int)min<int64_t>(kRowsPerBlock, N - n0);
+    if (own) {
+        centre_table(M, Q, Z, &la2[0][0], zt);
+        __syncthreads();
+        if (blockIdx.x == 0)
+            for (int i = threadIdx.x; i < 4 * Q; i += 256) ztg[i] = zt[i];
+    } else {
+        for (int i = threadIdx.x; i < 4 * Q; i += 256) zt[i] = ztg[i];
+        __syncthreads();
+    }
     for (int i = threadIdx.x; i < rows * Q; i += 256) {
         const int r = i / Q, q = i - r * Q;
         const int64_t k = n0 * Q + i;  // = (n0 + r) * Q + q
@@ -626,7 +660,10 @@ __global__ __launch_bounds__(256) void mfma_rows_kernel(
     }
 }
 
-// Range guard of the matrix-core path: route[0] = 0 when every row bound and
+// Range guard of the matrix-core path, formed from the per-row tables' bounds by every
+// workgroup of the row-term kernel up to kOwnGuard of them (two loads a thread, a
+// launch of 5-8 us less) and by a kernel of its own above (at N = 100,000 the loads
+// cost the row-term kernel the 9 us that the launch does): 0 when every row bound and
 // every R_q is inside the fp16 limits and every R_q / l_q is at most
 // kSpreadLimit (the matrix-core kernels compute the call), 1 otherwise (they
 // return at once and the generic kernels compute it).  The last condition is
@@ -635,23 +672,25 @@ __global__ __launch_bounds__(256) void mfma_rows_kernel(
 // pair spacings that matter, about l, so fp32-class rounding of V' is amplified
 // by about R / l, and by more when pairs on both sides of z_m cancel (a CPU model
 // of these kernels' arithmetic: dZ error 2e-6 at R / l = 70 and 1e-3 at 440).
-// One workgroup; the maximum is order-independent.
-__global__ __launch_bounds__(256) void mfma_guard_kernel(int64_t nparts, int Q,
-                                                         const float *__restrict__ gpart,
-                                                         const float *__restrict__ zt,
-                                                         Hyp<float> h, int *__restrict__ route) {
-    __shared__ int bad[256];
+// Order-independent, so every workgroup finds the same.
+constexpr int64_t kOwnGuard = 512;
+struct Guard {
+    int64_t nparts;      // 0: the route word is already written
+    const float *gpart;
+    int *route;          // the route word
+};
+__device__ inline int guard_of(const Guard &gd, int Q, const float *__restrict__ zt, const Hyp<float> &h) {
     int b = 0;
-    for (int64_t i = threadIdx.x; i < nparts; i += 256) b |= !(gpart[i] < kOperandLimit);
+    for (int64_t i = threadIdx.x; i < gd.nparts; i += 256) b |= !(gd.gpart[i] < kOperandLimit);
     for (int q = threadIdx.x; q < Q; q += 256)
         b |= !(zt[3 * Q + q] < kZLimit) | !(zt[3 * Q + q] <= kSpreadLimit * h.l[q]);
-    bad[threadIdx.x] = b;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int v = 0;
-        for (int k = 0; k < 256; ++k) v |= bad[k];
-        route[0] = v;
-    }
+    return __syncthreads_or(b);
+}
+
+__global__ __launch_bounds__(256) void mfma_guard_kernel(Guard gd, int Q, const float *__restrict__ zt,
+                                                         Hyp<float> h) {
+    const int bad = guard_of(gd, Q, zt, h);
+    if (threadIdx.x == 0) gd.route[0] = bad ? 1 : 0;
 }
 
 // Pair constant of the exponent, C_mm' = -log2e sum_q (z_mq - z_m'q)^2 / (4 l_q^2)
@@ -669,15 +708,18 @@ __device__ __forceinline__ float pair_const(int m, int mp, int Q, const float *_
 // G2c = G2s o 2^C: the symmetric part of dL/dPsi2 times the pair factor,
 // zero-padded to Mp x Mp (all zero when G2 is NULL); per workgroup, the largest
 // |G2c| and |G2s| of its entries go to smax[2 block], smax[2 block + 1].
-__global__ __launch_bounds__(256) void mfma_sym_kernel(int M, int Mp, int Q,
-                                                       const float *__restrict__ G2,
-                                                       const float *__restrict__ Z, Hyp<float> h,
-                                                       const int *__restrict__ route,
-                                                       float *__restrict__ G2p,
-                                                       float *__restrict__ smax) {
+// Workgroups of the row-term kernel past the row terms' (its launch is the only one
+// between the caller's arrays and the gradient).
+struct SymArgs {
+    int blocks;         // workgroups (0: none)
+    const float *G2;
+    float *G2p, *smax;
+};
+__device__ inline void sym_block(int block, int M, int Mp, int Q, const float *__restrict__ G2,
+                                 const float *__restrict__ Z, const Hyp<float> &h,
+                                 float *__restrict__ G2p, float *__restrict__ smax) {
     __shared__ float red[2][4];
-    if (route[0]) return;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = (int64_t)block * 256 + threadIdx.x;
     float gc = 0.f, gs = 0.f;
     if (i < (int64_t)Mp * Mp) {
         const int m = (int)(i / Mp), mp = (int)(i - (int64_t)m * Mp);
@@ -701,7 +743,7 @@ __global__ __launch_bounds__(256) void mfma_sym_kernel(int M, int Mp, int Q,
     if (threadIdx.x < 2) {
         float v = 0.f;
         for (int w = 0; w < 4; ++w) v = fmaxf(v, red[threadIdx.x][w]);
-        smax[2 * blockIdx.x + threadIdx.x] = v;
+        smax[2 * block + threadIdx.x] = v;
     }
 }
 
@@ -747,7 +789,7 @@ __global__ __launch_bounds__(256) void mfma_rowterm_kernel(
     int64_t N, int M, int Q, int Mp, const float *__restrict__ mu, const float *__restrict__ Z,
     const float *__restrict__ zc, const float *__restrict__ hq, const float *__restrict__ hl,
     const float *__restrict__ w1t, const float *__restrict__ l1, const float *__restrict__ G1,
-    const int *__restrict__ route, float *__restrict__ bt, float *__restrict__ bc,
+    Guard gd, SymArgs sy, Hyp<float> h, float *__restrict__ bt, float *__restrict__ bc,
     float *__restrict__ psi1, float *__restrict__ t1, float *__restrict__ bmax) {
     typedef float v4f __attribute__((ext_vector_type(4)));
     // z of the range's 256 inducing inputs, dimension-major, centred and zero
@@ -756,7 +798,20 @@ __global__ __launch_bounds__(256) void mfma_rowterm_kernel(
     __shared__ v4f s_row[kRTRows][QM];
     __shared__ v4f s_zt[QM][64];
     __shared__ float s_hl[kRTRows], s_l1[kRTRows];
-    if (route[0]) return;
+    if constexpr (GRAD) {
+        const int rt = (int)gridDim.x - sy.blocks;
+        if ((int)blockIdx.x >= rt) {
+            if (blockIdx.y == 0) sym_block(blockIdx.x - rt, M, Mp, Q, sy.G2, Z, h, sy.G2p, sy.smax);
+            return;
+        }
+    }
+    if (gd.nparts) {
+        const int bad = guard_of(gd, Q, zc, h);
+        if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) gd.route[0] = bad ? 1 : 0;
+        if (bad) return;
+    } else if (gd.route[0]) {
+        return;
+    }
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int m0 = blockIdx.y * 256 + 4 * lane;
@@ -906,17 +961,14 @@ __global__ __launch_bounds__(256) void mfma_rowterm_kernel(
     }
 }
 
-// gmax[0] = max |G2c|, gmax[1] = max |G2s| from the sym kernel's per-workgroup
-// maxima (one workgroup; max is order-independent, so the result is
-// deterministic).
-__global__ __launch_bounds__(1024) void mfma_absmax_kernel(int64_t nblocks,
-                                                           const float *__restrict__ smax,
-                                                           const int *__restrict__ route,
-                                                           float *__restrict__ gmax) {
-    __shared__ float part[2][16];
-    if (route[0]) return;
+// max |G2c| and max |G2s| from the per-workgroup maxima, by every workgroup of the
+// gradient kernels (Mp^2 / 256 pairs, at most 1,024: two loads a thread; a launch
+// less).  red: 32 floats of LDS, free again after the call; the maximum is
+// order-independent.
+__device__ inline float2 absmax_of(int Mp, const float *__restrict__ smax, float *red) {
+    const int n = (Mp * Mp + 255) / 256;
     float a = 0.f, b = 0.f;
-    for (int64_t i = threadIdx.x; i < nblocks; i += 1024) {
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
         a = fmaxf(a, smax[2 * i]);
         b = fmaxf(b, smax[2 * i + 1]);
     }
@@ -926,15 +978,17 @@ __global__ __launch_bounds__(1024) void mfma_absmax_kernel(int64_t nblocks,
         b = fmaxf(b, __shfl_xor(b, off));
     }
     if ((threadIdx.x & 63) == 0) {
-        part[0][threadIdx.x >> 6] = a;
-        part[1][threadIdx.x >> 6] = b;
+        red[2 * (threadIdx.x >> 6)] = a;
+        red[2 * (threadIdx.x >> 6) + 1] = b;
     }
     __syncthreads();
-    if (threadIdx.x < 2) {
-        float r = 0.f;
-        for (int w = 0; w < 16; ++w) r = fmaxf(r, part[threadIdx.x][w]);
-        gmax[threadIdx.x] = r;
+    float2 m = make_float2(0.f, 0.f);
+    for (unsigned w = 0; w < blockDim.x >> 6; ++w) {
+        m.x = fmaxf(m.x, red[2 * w]);
+        m.y = fmaxf(m.y, red[2 * w + 1]);
     }
+    __syncthreads();
+    return m;
 }
 
 // ---------------------------------------------------------------- shared helpers
@@ -1572,10 +1626,11 @@ __global__ __launch_bounds__(grad_waves(NQB) * 64) void psi2_grad_kernel(
     const float *__restrict__ zc, const float *__restrict__ Kt, const float *__restrict__ bt,
     const float *__restrict__ bc, const float *__restrict__ w1t, const float *__restrict__ w2t,
     const float *__restrict__ t1g, const float *__restrict__ G2p, const float *__restrict__ hl,
-    const float *__restrict__ gmax, const float *__restrict__ bmax, Hyp<float> h,
+    const float *__restrict__ smax, const float *__restrict__ bmax, Hyp<float> h,
     const int *__restrict__ route, float *__restrict__ rowsum, float *__restrict__ part_dz) {
     extern __shared__ float lds[];
     if (route[0]) return;
+    const float2 gm = absmax_of(Mp, smax, lds);
     const LdsG L = lds_grad_layout(Mp, DSF, Q, NQB, NK, wpg);
     constexpr int GT = gram_t(NK);
     _Float16 *zh = reinterpret_cast<_Float16 *>(lds + L.zb);
@@ -1636,8 +1691,8 @@ __global__ __launch_bounds__(grad_waves(NQB) * 64) void psi2_grad_kernel(
     // of the half prefactor), and, Psi2_n being positive semidefinite (|Psi2_n[m, m']|
     // <= max_m Psi2_n[m, m]), by max|G2s| 2^(4 bmax_n - 2 hl_n); the per-row scale 2^sc
     // brings the smaller bound to 2^14, inside fp16 and well above its subnormals
-    const float lgc = gmax[0] > 0.f ? __builtin_amdgcn_logf(gmax[0]) : 0.f;
-    const float lgs = gmax[1] > 0.f ? __builtin_amdgcn_logf(gmax[1]) : 0.f;
+    const float lgc = gm.x > 0.f ? __builtin_amdgcn_logf(gm.x) : 0.f;
+    const float lgs = gm.y > 0.f ? __builtin_amdgcn_logf(gm.y) : 0.f;
     const int nbm = (Mp + 255) / 256;          // bmax parts (ranges of 256 inducing inputs)
     stage_za<NK>(za, jr * JPW, JPW, nb, M, Q, Z, zc, threadIdx.x, blockDim.x);
 
@@ -1908,13 +1963,14 @@ __global__ __launch_bounds__(512) void psi2_grad_sym_kernel(
     const float *__restrict__ mu, const float *__restrict__ Z, const float *__restrict__ zc,
     const float *__restrict__ Kt, const float *__restrict__ bt, const float *__restrict__ bc,
     const float *__restrict__ w1t, const float *__restrict__ w2t, const float *__restrict__ t1g,
-    const float *__restrict__ G2p, const float *__restrict__ hl, const float *__restrict__ gmax,
+    const float *__restrict__ G2p, const float *__restrict__ hl, const float *__restrict__ smax,
     const float *__restrict__ bmax, Hyp<float> h, const int *__restrict__ route,
     float *__restrict__ rowsum, float *__restrict__ part_dz) {
     typedef short v4s __attribute__((vector_size(8)));
     typedef __attribute__((address_space(3))) v4s lds_v4s;
     extern __shared__ float lds[];
     if (route[0]) return;
+    const float2 gm = absmax_of(Mg, smax, lds);
     const LdsS L = lds_sym_layout(nb, DSF, Q, NK, RB);
     constexpr int GT = gram_t(NK);
     constexpr int KT = 5;                      // tile slots: 0 diagonal, 1 .. 3 rounds, 4 shared
@@ -1956,8 +2012,8 @@ __global__ __launch_bounds__(512) void psi2_grad_sym_kernel(
     stage_zh(zh, blk0, nb, M, Q, 1, Z, zc);
     stage_za<NK>(za, blk0, nb, nbg, M, Q, Z, zc, threadIdx.x, blockDim.x);
     // per-row scale of W: as in psi2_grad_kernel
-    const float lgc = gmax[0] > 0.f ? __builtin_amdgcn_logf(gmax[0]) : 0.f;
-    const float lgs = gmax[1] > 0.f ? __builtin_amdgcn_logf(gmax[1]) : 0.f;
+    const float lgc = gm.x > 0.f ? __builtin_amdgcn_logf(gm.x) : 0.f;
+    const float lgs = gm.y > 0.f ? __builtin_amdgcn_logf(gm.y) : 0.f;
 
     // the exchange: this wave's slot (written) and the transpose read's lane
     // offsets (rows 4 g + (lane / 4) % 4 of each run of 8, columns 16 ((lane / 16)
@@ -2343,7 +2399,7 @@ hipError_t launch_grad(const MPlan &p, const Shape &s, const float *mu, const fl
         s.N, (int)s.M, (int)s.Q, (int)p.Mp, p.nb, p.DSF, p.njr, p.wpg, p.igroups, p.gsplit ? 1 : 0,
         p.gsplit ? 2 : 0, p.grows, mu, Z, fat(ws, p.off_zc), fat(ws, p.off_K), fat(ws, p.off_bt),
         fat(ws, p.off_bc), fat(ws, p.off_w1), fat(ws, p.off_w2), fat(ws, p.off_t1),
-        fat(ws, p.off_g2), fat(ws, p.off_hl), fat(ws, p.off_gmax), fat(ws, p.off_bmax), h, route,
+        fat(ws, p.off_g2), fat(ws, p.off_hl), fat(ws, p.off_smax), fat(ws, p.off_bmax), h, route,
         fat(ws, p.off_rs), fat(ws, p.off_dz) + (p.gsplit ? p.sgchunks * s.M * s.Q : 0));
     return hipGetLastError();
 }
@@ -2367,7 +2423,7 @@ hipError_t launch_grad_sym(const MPlan &p, const Shape &s, const float *mu, cons
             s.N, (int)s.M, (int)s.Q, nbl * kTile, nbl, blk0, (int)p.Mp, p.nb, hf, p.DSFs,
             p.gsplit ? p.sgrows : p.grows, mu, Z, fat(ws, p.off_zc), fat(ws, p.off_K),
             fat(ws, p.off_bt), fat(ws, p.off_bc), fat(ws, p.off_w1), fat(ws, p.off_w2),
-            fat(ws, p.off_t1), fat(ws, p.off_g2), fat(ws, p.off_hl), fat(ws, p.off_gmax),
+            fat(ws, p.off_t1), fat(ws, p.off_g2), fat(ws, p.off_hl), fat(ws, p.off_smax),
             fat(ws, p.off_bmax), h, route, fat(ws, p.off_rs), fat(ws, p.off_dz));
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
@@ -2431,11 +2487,13 @@ hipError_t dispatch_grad(const MPlan &p, const Shape &s, const float *mu, const 
 }
 
 // The centring table, the per-row tables, the range guard (route word), and
-// the row terms plus Psi1 (forward, psi1 != NULL) or dL/dPsi1 * Psi1 (grad).
+// the row terms plus Psi1 (forward, psi1 != NULL) or dL/dPsi1 * Psi1 and
+// dL/dPsi2's symmetric part (grad; G2 = NULL: zero).
 void prepare(const MPlan &p, const Shape &s, const float *mu, const float *S, const float *Z,
-             const Hyp<float> &h, const float *G1, float *psi1, bool grad, int *route, void *ws,
-             hipStream_t st) {
-    {
+             const Hyp<float> &h, const float *G1, const float *G2, float *psi1, bool grad, int *route,
+             void *ws, hipStream_t st) {
+    const bool own = s.M * s.Q <= kOwnCentre;
+    if (!own) {
         TimedScope ts(st, "mfma_centre");
         mfma_centre_kernel<<<1, 256, 0, st>>>((int)s.M, (int)s.Q, Z, fat(ws, p.off_zc));
     }
@@ -2443,16 +2501,18 @@ void prepare(const MPlan &p, const Shape &s, const float *mu, const float *S, co
     {
         TimedScope ts(st, "mfma_rows");
         mfma_rows_kernel<<<(unsigned)rblocks, 256, 0, st>>>(
-            s.N, (int)s.Q, mu, S, fat(ws, p.off_zc), h, fat(ws, p.off_K), fat(ws, p.off_hq),
-            fat(ws, p.off_w2), fat(ws, p.off_hl), fat(ws, p.off_w1), fat(ws, p.off_l1),
-            fat(ws, p.off_gpart));
+            s.N, (int)s.Q, mu, S, fat(ws, p.off_zc), (int)s.M, Z, own, h, fat(ws, p.off_K),
+            fat(ws, p.off_hq), fat(ws, p.off_w2), fat(ws, p.off_hl), fat(ws, p.off_w1),
+            fat(ws, p.off_l1), fat(ws, p.off_gpart));
     }
-    {
+    Guard gd{rblocks, fat(ws, p.off_gpart), route};
+    if (rblocks > kOwnGuard) {
         TimedScope ts(st, "mfma_guard");
-        mfma_guard_kernel<<<1, 256, 0, st>>>(rblocks, (int)s.Q, fat(ws, p.off_gpart),
-                                             fat(ws, p.off_zc), h, route);
+        mfma_guard_kernel<<<1, 256, 0, st>>>(gd, (int)s.Q, fat(ws, p.off_zc), h);
+        gd.nparts = 0;
     }
-    dim3 grid((unsigned)cdiv(s.N, kRTRows), (unsigned)cdiv(p.Mp, 256));
+    const SymArgs sy{grad ? (int)cdiv(p.Mp * p.Mp, 256) : 0, G2, fat(ws, p.off_g2), fat(ws, p.off_smax)};
+    dim3 grid((unsigned)(cdiv(s.N, kRTRows) + sy.blocks), (unsigned)cdiv(p.Mp, 256));
     float *t1 = grad ? fat(ws, p.off_t1) : nullptr;
     TimedScope ts(st, "mfma_rowterm");
 #define GPPS_RT(QM)                                                                            \
@@ -2460,12 +2520,12 @@ void prepare(const MPlan &p, const Shape &s, const float *mu, const float *S, co
         if (grad)                                                                              \
             mfma_rowterm_kernel<QM, true><<<grid, 256, 0, st>>>(                               \
                 s.N, (int)s.M, (int)s.Q, (int)p.Mp, mu, Z, fat(ws, p.off_zc), fat(ws, p.off_hq), \
-                fat(ws, p.off_hl), fat(ws, p.off_w1), fat(ws, p.off_l1), G1, route,            \
+                fat(ws, p.off_hl), fat(ws, p.off_w1), fat(ws, p.off_l1), G1, gd, sy, h,        \
                 fat(ws, p.off_bt), fat(ws, p.off_bc), nullptr, t1, fat(ws, p.off_bmax));       \
         else                                                                                   \
             mfma_rowterm_kernel<QM, false><<<grid, 256, 0, st>>>(                              \
                 s.N, (int)s.M, (int)s.Q, (int)p.Mp, mu, Z, fat(ws, p.off_zc), fat(ws, p.off_hq), \
-                fat(ws, p.off_hl), fat(ws, p.off_w1), fat(ws, p.off_l1), G1, route,            \
+                fat(ws, p.off_hl), fat(ws, p.off_w1), fat(ws, p.off_l1), G1, gd, sy, h,        \
                 fat(ws, p.off_bt), fat(ws, p.off_bc), psi1, nullptr, nullptr);                 \
     } while (0)
     if (s.Q <= 8) GPPS_RT(8);
@@ -2494,7 +2554,7 @@ hipError_t mfma_psi_stats(const Shape &s, const float *mu, const float *S, const
                           const Hyp<float> &h, float *psi0, float *Psi1, float *Psi2,
                           int accumulate, int *route, void *ws, hipStream_t st) {
     const MPlan p = make_mplan(s);
-    prepare(p, s, mu, S, Z, h, nullptr, Psi1, false, route, ws, st);
+    prepare(p, s, mu, S, Z, h, nullptr, nullptr, Psi1, false, route, ws, st);
     hipError_t e = dispatch_fwd(p, s, mu, Z, route, ws, st);
     if (e != hipSuccess) return e;
     TimedScope ts(st, "mfma_psi2_reduce");
@@ -2509,18 +2569,7 @@ hipError_t mfma_psi_grads(const Shape &s, const float *mu, const float *S, const
                           const float *G2, float *dmu, float *dS, float *dZ, float *dsf2,
                           float *dl, int accumulate, int *route, void *ws, hipStream_t st) {
     const MPlan p = make_mplan(s);
-    prepare(p, s, mu, S, Z, h, G1, nullptr, true, route, ws, st);
-    {
-        // NULL dL/dPsi2 means zero: the kernel then adds only the Psi1 terms
-        TimedScope ts(st, "mfma_sym");
-        mfma_sym_kernel<<<(unsigned)cdiv(p.Mp * p.Mp, 256), 256, 0, st>>>(
-            (int)s.M, (int)p.Mp, (int)s.Q, G2, Z, h, route, fat(ws, p.off_g2), fat(ws, p.off_smax));
-    }
-    {
-        TimedScope ts(st, "mfma_absmax");
-        mfma_absmax_kernel<<<1, 1024, 0, st>>>(cdiv(p.Mp * p.Mp, 256), fat(ws, p.off_smax), route,
-                                               fat(ws, p.off_gmax));
-    }
+    prepare(p, s, mu, S, Z, h, G1, G2, nullptr, true, route, ws, st);
     hipError_t e = dispatch_grad(p, s, mu, Z, h, route, ws, st);
     if (e != hipSuccess) return e;
     {
