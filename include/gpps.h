@@ -80,8 +80,8 @@ typedef enum {
  *
  * With neither path flag the call takes the fastest path that supports it: the
  * matrix-core path for F32 shapes within its limits (M rounded up to 32 at most
- * 512 with Q <= 31, or at most 256 with Q <= GPPS_MAX_Q_MFMA), the generic vector
- * path otherwise and for the smallest calls (N (M^2 + 1000) (Q + 6) <= 1.5e7), whose
+ * 512 with Q <= 31, or at most 256 with Q <= GPPS_MAX_Q_MFMA), the generic
+ * path (whose arithmetic is the element type's own) otherwise and for the smallest calls (N (M^2 + 1000) (Q + 6) <= 1.5e7), whose
  * time is that of their launches.  GPPS_PATH_GENERIC forces the generic path; GPPS_PATH_MFMA
  * asks for the matrix-core path and fails with GPPS_ERR_PATH where it cannot
  * take the call.  The matrix-core path carries its operands as two-part fp16

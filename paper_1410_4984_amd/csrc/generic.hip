@@ -1,5 +1,5 @@
-// Generic vector-ALU path: RBF-ARD psi-statistics and gradients, templated on
-// the element type (float or double).
+// Generic path: RBF-ARD psi-statistics and gradients in the element type's own
+// arithmetic (float or double).
 //
 // What is computed (section 2, eq. (4): phi, Phi and Psi become expectations
 // under q(x_n) = N(mu_n, diag S_n); Alg. 1 and Alg. 2).  With
@@ -11,17 +11,12 @@
 //   Psi2_n[m, m'] = exp(lp2_n - sum_q [(z_m - z_m')^2 / (4 l^2) + (mu - zbar)^2 w2])
 // with zbar = (z_m + z_m') / 2, and Psi2 = sum_n Psi2_n.
 //
-// Work split: Psi1 one thread per output; Psi2 one thread per unique pair
-// (m <= m'), partial sums per row chunk reduced in a fixed order.  Gradients,
-// by the first form that applies:
-//   * pairs kernels (small Q): one thread per inducing input m, the Z table in
-//     LDS, per row the sums r and V over the partners m' (symmetric form: each
-//     unordered pair evaluated once);
-//   * the wide kernel (Q up to 32 in fp64, 64 in fp32): the same ordered sums
-//     with two lanes per m, each holding half of the dimensions;
-//   * otherwise a row kernel (one thread per datapoint and range of pair rows m:
-//     dmu, dS and dl / dsf2 partials) and a column kernel (one thread per
-//     inducing input, row chunk and range of partners: dZ partials).
+// Work split: Psi1 one thread per output.  Psi2 and its gradients go to the 16 x 16 tile
+// kernels but at small Q (tiles_stats_wanted, tiles_grads_wanted), where these stay:
+//   * Psi2: one thread per unique pair (m <= m'), partial sums per row chunk reduced in a
+//     fixed order;
+//   * gradients: one thread per inducing input m, the Z table in LDS, per row the sums r
+//     and V over the partners m' (symmetric form: each unordered pair evaluated once).
 // Fixed-order reduce kernels combine the partials.  No atomics anywhere.
 #include <hip/hip_runtime.h>
 
@@ -33,11 +28,8 @@
 namespace gpps {
 namespace {
 
-constexpr int kRowTile = 32;     // rows staged in LDS at a time
-constexpr int kFwdTile = 128;    // ... by the forward pair kernel
+constexpr int kFwdTile = 128;    // rows staged in LDS at a time by the forward pair kernel
 constexpr int kPairTile = 16;    // pair tile edge (16 x 16 threads)
-constexpr int kRowBlock = 64;    // threads (rows) per block in the gradient row kernel
-constexpr int kColBlock = 64;    // threads (inducing inputs) per block in the column kernel
 constexpr int kBand = 8;         // symmetric pairs kernel: pair offsets k per LDS exchange
 constexpr int kSlotBand = 4;     // ... the same with several rows at a time
 constexpr int64_t kGridCap = 2048;  // workgroups of the grid-stride kernels
@@ -49,126 +41,92 @@ __device__ inline double dlog1p(double x) { return log1p(x); }
 
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// Register width (latent dimensions, padded) of the pairs kernel for Q.
-inline int64_t pairs_qm(int64_t Q) { return Q <= 1 ? 1 : Q <= 2 ? 2 : Q <= 4 ? 4 : Q <= 8 ? 8 : 16; }
-// Register width (dimensions, padded) of the forward pair kernel for Q, and its
-// pairs per thread (two where a dimension's LDS read would otherwise serve one
-// pair's three operations; one at small widths and for wide fp64 rows).
-inline int fwd_qm(int64_t Q) {
-    for (int qm : {1, 2, 4, 8, 12, 16, 20, 24, 32, 48})
-        if (Q <= qm) return qm;
-    return 64;
-}
-inline int fwd_ppt(int64_t Q, size_t elem) {
-    const int qm = fwd_qm(Q);
-    return qm >= 8 && !(elem == 8 && qm >= 48) ? 2 : 1;
-}
-// Dimensions per lane of the wide gradient kernel for Q (0: none fits; fp64
-// keeps seven arrays of QH doubles live, fp32 the same in floats).
-inline int wide_qh(int64_t Q, size_t elem) {
-    for (int qh : {4, 6, 8, 10, 12, 16, 24, 32})
-        if (2 * qh >= Q) return (elem == 8 && qh > 16) ? 0 : qh;
-    return 0;
-}
+// Register width (latent dimensions, padded) of the pair kernels for Q <= 4.
+inline int64_t pairs_qm(int64_t Q) { return Q <= 1 ? 1 : Q <= 2 ? 2 : 4; }
 
 // The largest workspace before the route word that gpps_psi_stats_noalloc takes.
 constexpr size_t kScratchRoom = size_t(GPPS_SCRATCH_BYTES) - 256;
 
 struct Plan {
+    bool tstats, tgrads;             // Psi2 / its gradients by the tile kernels
     int64_t tiles_edge;              // pair tiles per edge (Psi2 reduce)
     int64_t pblocks;                 // forward: blocks of 256 unique pairs
     int64_t nc2;                     // row chunks of the Psi2 forward kernel
     int64_t rows2;                   // rows per chunk (forward)
-    int64_t ncc, rowsc;              // column-kernel chunks and rows per chunk
-    int64_t col_blocks;              // column-kernel blocks per chunk
-    int64_t row_blocks;              // row-kernel blocks
-    int64_t rr;                      // row kernel: ranges of pair rows m (m = r mod rr)
-    int64_t cr;                      // column kernel: ranges of partners m'
-    bool pairs;                      // gradients by grad_pairs_kernel (Z table fits in LDS)
-    bool psym;                       // ... in its symmetric form (one workgroup spans all of M)
+    bool psym;                       // gradients: symmetric form (one workgroup spans all of M)
     bool pslots;                     // ... with R rows at a time (grad_pairs_slots_kernel)
     int prs, psthreads;              // its rows at a time and threads per workgroup
     int pthreads;                    // pairs kernel: threads (inducing inputs) per workgroup
     int64_t pmb, pchunks, prows;     // pairs kernel: m-blocks, row chunks, rows per chunk
-    bool wide;                       // gradients by grad_wide_kernel (wider Q, Z table in LDS)
-    int wqh;                         // its dimensions per lane
-    int64_t wmb, wchunks, wrows;     // its blocks of 128 inducing inputs, row chunks, rows
-    // workspace offsets in bytes
+    // workspace offsets in bytes; the tile kernels carve the region from off_p2 on
     size_t off_w1, off_w2, off_lp1, off_lp2, off_p2, off_g2s, off_gc, off_colp, off_rowp, off_rowg,
         total;
 };
 
 Plan carve(const Shape &s, size_t elem, bool few_rows) {
     Plan p{};
-    p.tiles_edge = cdiv(s.M, kPairTile);
-    p.pblocks = cdiv(s.P, 256 * fwd_ppt(s.Q, elem));
-    // 256 rows a chunk, fewer where the chunks are too few for the chip (a chunk's rows
-    // are summed one after another: 55 us for 200 rows of Q = 20 in one chunk)
-    int64_t cap2 = std::max<int64_t>(1, 2048 / p.pblocks);
-    int64_t nc2 = std::max(cdiv(s.N, 256), few_rows ? std::min(cdiv(s.N, 16), cdiv(256, p.pblocks)) : 0);
-    p.nc2 = std::max<int64_t>(1, std::min(nc2, cap2));
-    p.rows2 = cdiv(s.N, p.nc2);
-    p.nc2 = cdiv(s.N, p.rows2);
-    p.col_blocks = cdiv(s.M, kColBlock);
-    int64_t ncc = cdiv(s.N, 64);
-    int64_t capc = std::max<int64_t>(1, 2048 / p.col_blocks);
-    p.ncc = std::max<int64_t>(1, std::min(ncc, capc));
-    p.rowsc = cdiv(s.N, p.ncc);
-    p.ncc = cdiv(s.N, p.rowsc);
-    p.row_blocks = cdiv(s.N, kRowBlock);
-    p.rr = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(s.M, 64), cdiv(2048, p.row_blocks)));
-    p.cr = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(s.M, 64),
-                                                  cdiv(2048, p.col_blocks * p.ncc)));
-    // the pairs kernel keeps the whole Z table (padded to QM) in LDS and a dozen
-    // per-dimension values per thread in registers: small Q only (beyond that
-    // it spills and the row and column kernels below take over)
-    p.pairs = pairs_qm(s.Q) <= (elem == 4 ? 8 : 4) && s.M * pairs_qm(s.Q) * elem <= 65536;
-    p.pthreads = (int)std::min<int64_t>(256, cdiv(s.M, 64) * 64);
-    p.pmb = cdiv(s.M, p.pthreads);
-    p.pchunks = std::max<int64_t>(1, std::min<int64_t>(s.N, 2048 / p.pmb));
-    p.prows = cdiv(s.N, p.pchunks);
-    p.pchunks = cdiv(s.N, p.prows);
-    // symmetric form: every pair exchange stays inside one workgroup, and the Z
-    // table plus two bands of kBand x M pair values fit in LDS
-    p.psym = p.pairs && p.pmb == 1 && (pairs_qm(s.Q) + 2 * kBand) * s.M * elem <= 65536;
-    p.prs = (int)std::min<int64_t>(8, 512 / s.M);
-    p.psthreads = (int)(cdiv(p.prs * s.M, 64) * 64);
-    p.pslots = p.psym && p.prs >= 2 &&
-               (s.M * pairs_qm(s.Q) + p.prs * 2 * kSlotBand * s.M + p.prs * s.M * 2 * pairs_qm(s.Q)) * elem <=
-                   65536;
-    if (p.pslots) {
-        // chunks a whole number of passes of R rows, about five rounds of two
-        // 512-thread workgroups per CU
-        p.pchunks = std::max<int64_t>(1, std::min<int64_t>(s.N, 2560));
-        p.prows = cdiv(cdiv(s.N, p.pchunks), p.prs) * p.prs;
-        p.pchunks = cdiv(s.N, p.prows);
-    }
-    // wide form: where the pairs kernel does not apply and the padded Z table
-    // fits in LDS
-    p.wqh = wide_qh(s.Q, elem);
-    p.wide = !p.pairs && p.wqh > 0 && (s.M + 128) * 2 * p.wqh * elem <= 65536;
-    p.wmb = cdiv(s.M, 128);
-    p.wchunks = std::max<int64_t>(1, std::min<int64_t>(s.N, 2048 / p.wmb));
-    p.wrows = cdiv(s.N, p.wchunks);
-    p.wchunks = cdiv(s.N, p.wrows);
+    p.tstats = tiles_stats_wanted(s, elem);
+    p.tgrads = tiles_grads_wanted(s, elem);
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t r = o; o = align_up(o + bytes, 256); return r; };
     p.off_w1 = take(elem * s.N * s.Q);
     p.off_w2 = take(elem * s.N * s.Q);
     p.off_lp1 = take(elem * s.N);
     p.off_lp2 = take(elem * s.N);
-    p.off_p2 = take(elem * p.nc2 * s.P);
-    p.off_g2s = take(elem * s.M * s.M);
-    p.off_gc = take(elem * (s.M / 2 + 1) * s.M);
-    p.off_colp = take(elem * std::max({p.ncc * p.cr, p.pchunks, p.wchunks}) * s.M * s.Q);
-    p.off_rowp =
-        take(elem * std::max({p.rr * p.row_blocks, p.pmb * p.pchunks, p.wmb * p.wchunks}) * (s.Q + 1));
-    p.off_rowg = take(elem * std::max({p.rr, p.pmb, p.wmb}) * s.N * s.Q * 2);
-    // the double-precision matrix kernels re-carve the region behind the per-row
-    // tables; it grows to what they want as long as the call's workspace stays
-    // within GPPS_SCRATCH_BYTES (the allocation-free entry point takes no more)
-    if (elem == 8) o = std::max(o, std::min(p.off_p2 + f64_region_bytes(s), kScratchRoom));
-    p.total = o;
+    p.off_p2 = o;
+    if (!p.tstats) {
+        p.tiles_edge = cdiv(s.M, kPairTile);
+        p.pblocks = cdiv(s.P, 256);
+        // 256 rows a chunk, fewer where the chunks are too few for the chip (a chunk's rows
+        // are summed one after another: 55 us for 200 rows of Q = 20 in one chunk)
+        const int64_t cap2 = std::max<int64_t>(1, 2048 / p.pblocks);
+        const int64_t nc2 =
+            std::max(cdiv(s.N, 256), few_rows ? std::min(cdiv(s.N, 16), cdiv(256, p.pblocks)) : 0);
+        p.nc2 = std::max<int64_t>(1, std::min(nc2, cap2));
+        p.rows2 = cdiv(s.N, p.nc2);
+        p.nc2 = cdiv(s.N, p.rows2);
+        take(elem * p.nc2 * s.P);
+    }
+    if (!p.tgrads) {
+        // one thread per inducing input, the whole Z table (at most 64 KB) in LDS
+        const int64_t qm = pairs_qm(s.Q);
+        p.pthreads = (int)std::min<int64_t>(256, cdiv(s.M, 64) * 64);
+        p.pmb = cdiv(s.M, p.pthreads);
+        p.pchunks = std::max<int64_t>(1, std::min<int64_t>(s.N, 2048 / p.pmb));
+        p.prows = cdiv(s.N, p.pchunks);
+        p.pchunks = cdiv(s.N, p.prows);
+        // symmetric form: every pair exchange stays inside one workgroup, and the Z
+        // table plus two bands of kBand x M pair values fit in LDS
+        p.psym = p.pmb == 1 && (qm + 2 * kBand) * s.M * elem <= 65536;
+        p.prs = (int)std::min<int64_t>(8, 512 / s.M);
+        p.psthreads = (int)(cdiv(p.prs * s.M, 64) * 64);
+        p.pslots = p.psym && p.prs >= 2 &&
+                   (s.M * qm + p.prs * 2 * kSlotBand * s.M + p.prs * s.M * 2 * qm) * elem <= 65536;
+        if (p.pslots) {
+            // chunks a whole number of passes of R rows, about five rounds of two
+            // 512-thread workgroups per CU
+            p.pchunks = std::max<int64_t>(1, std::min<int64_t>(s.N, 2560));
+            p.prows = cdiv(cdiv(s.N, p.pchunks), p.prs) * p.prs;
+            p.pchunks = cdiv(s.N, p.prows);
+        }
+        size_t end = o;
+        o = p.off_p2;   // gradients and statistics share the region
+        p.off_g2s = take(elem * s.M * s.M);
+        p.off_gc = take(elem * (s.M / 2 + 1) * s.M);
+        p.off_colp = take(elem * p.pchunks * s.M * s.Q);
+        p.off_rowp = take(elem * p.pmb * p.pchunks * (s.Q + 1));
+        p.off_rowg = take(elem * (p.pmb > 1 ? p.pmb : 0) * s.N * s.Q * 2);
+        o = std::max(o, end);
+    }
+    // The tile kernels' chunks take what the shape's workspace has in any case (the
+    // known-input path's), or what keeps it within GPPS_SCRATCH_BYTES: the
+    // allocation-free entry point takes no more.
+    const TilesRegion t = tiles_region(s, elem);
+    o = std::max(o, p.off_p2 + t.least);
+    p.total = o > kScratchRoom
+                  ? std::max(o, p.off_p2 + t.want)
+                  : std::max(o, std::min(p.off_p2 + t.want,
+                                         std::max(kScratchRoom, known_workspace_bytes(s, elem))));
     return p;
 }
 
@@ -273,10 +231,9 @@ __device__ inline void pair_coords(int64_t t, int64_t M, int &m, int &mp) {
 }
 
 // ---------------------------------------------------------------- Psi2 partials (Alg. 1, Phi)
-// One thread per PPT unique pairs (pairs t = block base + k 256 + thread,
-// k < PPT: consecutive pairs of the row-major upper triangle, so no lane idles
-// below the diagonal) and row chunk.  The rows' (mu, w2) are staged in LDS as
-// pairs, one read per (row, dimension) serving the thread's PPT pairs.
+// Q <= 4: one thread per unique pair (in the row-major order of the upper triangle, so
+// that no lane idles below the diagonal) and row chunk.  The rows' (mu, w2) are
+// staged in LDS as pairs.
 template <typename T>
 struct Two;
 template <>
@@ -288,7 +245,7 @@ struct Two<double> {
     typedef double2 t;
 };
 
-template <typename T, int QM, int PPT>
+template <typename T, int QM>
 __global__ __launch_bounds__(256) void psi2_partial_kernel(const int *__restrict__ gate,
     int64_t N, int M, int Q, int64_t P, int64_t rows_per_chunk,
     const T *__restrict__ mu, const T *__restrict__ Z, const T *__restrict__ w2,
@@ -297,32 +254,23 @@ __global__ __launch_bounds__(256) void psi2_partial_kernel(const int *__restrict
     using T2 = typename Two<T>::t;
     __shared__ T2 s_mw[kFwdTile][QM];
     __shared__ T s_lp[kFwdTile];
-    const int64_t t0 = (int64_t)blockIdx.x * 256 * PPT + threadIdx.x;
+    const int64_t t0 = (int64_t)blockIdx.x * 256 + threadIdx.x;
     // loads from clamped (valid) addresses, masked by a multiplication: a select
     // around each load would let the compiler wait for the loads one at a time
-    T zbar[PPT][QM], C[PPT];
-    bool valid[PPT];
+    T zbar[QM], C = 0;
+    int m = 0, mp = 0;
+    if (t0 < P) pair_coords(t0, M, m, mp);
 #pragma unroll
-    for (int k = 0; k < PPT; ++k) {
-        const int64_t t = t0 + k * 256;
-        valid[k] = t < P;
-        int m = 0, mp = 0;
-        if (valid[k]) pair_coords(t, M, m, mp);
-        C[k] = 0;
-#pragma unroll
-        for (int q = 0; q < QM; ++q) {
-            const int qc = min(q, Q - 1);
-            const T a = Z[(int64_t)m * Q + qc], b = Z[(int64_t)mp * Q + qc];
-            const T on = q < Q ? T(1) : T(0);
-            zbar[k][q] = on * (T(0.5) * (a + b));
-            C[k] -= on * ((a - b) * (a - b) / (T(4) * h.l2[qc]));
-        }
+    for (int q = 0; q < QM; ++q) {
+        const int qc = min(q, Q - 1);
+        const T a = Z[(int64_t)m * Q + qc], b = Z[(int64_t)mp * Q + qc];
+        const T on = q < Q ? T(1) : T(0);
+        zbar[q] = on * (T(0.5) * (a + b));
+        C -= on * ((a - b) * (a - b) / (T(4) * h.l2[qc]));
     }
     const int64_t r0 = (int64_t)blockIdx.y * rows_per_chunk;
     const int64_t r1 = min(N, r0 + rows_per_chunk);
-    T acc[PPT];
-#pragma unroll
-    for (int k = 0; k < PPT; ++k) acc[k] = 0;
+    T acc = 0;
     for (int64_t base = r0; base < r1; base += kFwdTile) {
         const int cnt = (int)min<int64_t>(kFwdTile, r1 - base);
         __syncthreads();
@@ -353,32 +301,21 @@ __global__ __launch_bounds__(256) void psi2_partial_kernel(const int *__restrict
         __syncthreads();
         // two-level sum: the tile's rows first, then into the chunk total, so
         // that rounding grows with tile + tiles per chunk, not rows per chunk
-        T tacc[PPT];
-#pragma unroll
-        for (int k = 0; k < PPT; ++k) tacc[k] = 0;
+        T tacc = 0;
 #pragma unroll 4
         for (int r = 0; r < cnt; ++r) {
-            T e[PPT];
-#pragma unroll
-            for (int k = 0; k < PPT; ++k) e[k] = s_lp[r] + C[k];
+            T e = s_lp[r] + C;
 #pragma unroll
             for (int q = 0; q < QM; ++q) {
                 const T2 v = s_mw[r][q];
-#pragma unroll
-                for (int k = 0; k < PPT; ++k) {
-                    const T d = v.x - zbar[k][q];
-                    e[k] -= d * d * v.y;
-                }
+                const T d = v.x - zbar[q];
+                e -= d * d * v.y;
             }
-#pragma unroll
-            for (int k = 0; k < PPT; ++k) tacc[k] += dexp(e[k]);
+            tacc += dexp(e);
         }
-#pragma unroll
-        for (int k = 0; k < PPT; ++k) acc[k] += tacc[k];
+        acc += tacc;
     }
-#pragma unroll
-    for (int k = 0; k < PPT; ++k)
-        if (valid[k]) partial[(int64_t)blockIdx.y * P + t0 + k * 256] = acc[k];
+    if (t0 < P) partial[(int64_t)blockIdx.y * P + t0] = acc;
 }
 
 // Workgroups below edge^2: fixed-order sum of the chunk partials (16 x 16 pairs
@@ -420,130 +357,6 @@ __global__ __launch_bounds__(256) void psi2_reduce_kernel(
 }
 
 // ---------------------------------------------------------------- gradients (Alg. 2)
-// One thread per datapoint and range r of pair rows (m = r, r + rr, ...; the
-// Psi1 terms in the column tiles t = r, r + rr, ...): partial dmu_n, dS_n of the
-// range (om, os: [r][2][N][Q]) and per-block partials of dl and dsf2.
-template <typename T, int QM>
-__global__ __launch_bounds__(kRowBlock) void grad_rows_kernel(const int *__restrict__ gate, 
-    int64_t N, int M, int Q, int rr, const T *__restrict__ mu, const T *__restrict__ S,
-    const T *__restrict__ Z, const T *__restrict__ w1, const T *__restrict__ w2,
-    const T *__restrict__ lp1, const T *__restrict__ lp2, Hyp<T> h, const T *__restrict__ G1,
-    const T *__restrict__ G2s, T *__restrict__ om, T *__restrict__ os, T *__restrict__ rowpart) {
-    if (gate && gate[0] == 0) return;
-    const int range = blockIdx.y;
-    __shared__ T s_g1[kRowBlock][kRowBlock + 1];
-    __shared__ T s_red[QM + 1][kRowBlock];
-    const int tid = threadIdx.x;
-    const int64_t n0 = (int64_t)blockIdx.x * kRowBlock;
-    const int64_t n = n0 + tid;
-    const bool valid = n < N;
-    T m_[QM], s_[QM], a1[QM], a2[QM];
-    T gmu[QM], gS[QM], gl[QM];
-    T l1 = 0, l2v = 0, gsf = 0;
-#pragma unroll
-    for (int q = 0; q < QM; ++q) {
-        m_[q] = s_[q] = a1[q] = a2[q] = gmu[q] = gS[q] = gl[q] = 0;
-        if (q < Q && valid) {
-            m_[q] = mu[n * Q + q];
-            s_[q] = S[n * Q + q];
-            a1[q] = w1[n * Q + q];
-            a2[q] = w2[n * Q + q];
-        }
-    }
-    if (valid) { l1 = lp1[n]; l2v = lp2[n]; }
-
-    if (G1) {
-        const int rows = (int)min<int64_t>(kRowBlock, N - n0);
-        for (int mt = range * kRowBlock; mt < M; mt += rr * kRowBlock) {
-            const int cols = min(kRowBlock, M - mt);
-            __syncthreads();
-            for (int i = tid; i < rows * cols; i += kRowBlock) {
-                int r = i / cols, c = i - r * cols;
-                s_g1[r][c] = G1[(n0 + r) * M + mt + c];
-            }
-            __syncthreads();
-            if (valid) {
-                for (int c = 0; c < cols; ++c) {
-                    const int m = mt + c;
-                    T e = 0;
-#pragma unroll
-                    for (int q = 0; q < QM; ++q)
-                        if (q < Q) {
-                            T d = m_[q] - Z[(int64_t)m * Q + q];
-                            e += d * d * a1[q];
-                        }
-                    const T t = s_g1[tid][c] * dexp(l1 - T(0.5) * e);
-                    gsf += t;
-#pragma unroll
-                    for (int q = 0; q < QM; ++q)
-                        if (q < Q) {
-                            T d = m_[q] - Z[(int64_t)m * Q + q];
-                            T dd = d * a1[q];
-                            gmu[q] -= t * dd;
-                            gS[q] += t * T(0.5) * (dd * dd - a1[q]);
-                            gl[q] += t * (s_[q] * a1[q] / h.l[q] + h.l[q] * dd * dd);
-                        }
-                }
-            }
-        }
-    }
-
-    if (G2s && valid) {
-        for (int m = range; m < M; m += rr) {
-            T gsf_row = 0;  // sum over m' first, so long rows do not swamp the total
-            for (int mp = m; mp < M; ++mp) {
-                const T g = (m == mp ? T(1) : T(2)) * G2s[(int64_t)m * M + mp];
-                T e = l2v;
-#pragma unroll
-                for (int q = 0; q < QM; ++q)
-                    if (q < Q) {
-                        T a = Z[(int64_t)m * Q + q], b = Z[(int64_t)mp * Q + q];
-                        T d = m_[q] - T(0.5) * (a + b);
-                        e -= (a - b) * (a - b) / (T(4) * h.l2[q]) + d * d * a2[q];
-                    }
-                const T t = g * dexp(e);
-                gsf_row += T(2) * t;
-#pragma unroll
-                for (int q = 0; q < QM; ++q)
-                    if (q < Q) {
-                        T a = Z[(int64_t)m * Q + q], b = Z[(int64_t)mp * Q + q];
-                        T d = m_[q] - T(0.5) * (a + b);
-                        T dd = d * a2[q];
-                        T del = a - b;
-                        gmu[q] -= T(2) * t * dd;
-                        gS[q] += t * (T(2) * dd * dd - a2[q]);
-                        gl[q] += t * (T(2) * s_[q] * a2[q] / h.l[q] +
-                                      del * del / (T(2) * h.l2[q] * h.l[q]) +
-                                      T(2) * h.l[q] * dd * dd);
-                    }
-            }
-            gsf += gsf_row;
-        }
-    }
-
-    if (valid) {
-        T *pm = om + ((int64_t)range * 2) * N * Q, *ps = os + ((int64_t)range * 2) * N * Q;
-#pragma unroll
-        for (int q = 0; q < QM; ++q)
-            if (q < Q) {
-                pm[n * Q + q] = gmu[q];
-                ps[n * Q + q] = gS[q];
-            }
-    }
-    // fixed-order block reduction of dl and dsf2 partials
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < QM; ++q) s_red[q][tid] = gl[q];
-    s_red[QM][tid] = gsf / h.sf2;
-    __syncthreads();
-    for (int k = tid; k <= Q; k += kRowBlock) {
-        const int row = k < Q ? k : QM;
-        T s = 0;
-        for (int i = 0; i < kRowBlock; ++i) s += s_red[row][i];
-        rowpart[((int64_t)range * gridDim.x + blockIdx.x) * (Q + 1) + k] = s;
-    }
-}
-
 // Psi2 and Psi1 gradients through per-(n, m) sums.  With W_n[m, m'] =
 // G2s[m, m'] Psi2_n[m, m'], d = mu_n - z_m, w1 = 1/(l^2 + S_n), w2 = 1/(l^2 + 2 S_n),
 //   r_nm = sum_m' W_n[m, m'],  V_nmq = sum_m' W_n[m, m'] d_nm'q,
@@ -972,102 +785,6 @@ __global__ __launch_bounds__(512) void grad_pairs_slots_kernel(const int *__rest
     }
 }
 
-// One thread per inducing input m, row chunk and range of partners (m' = r,
-// r + cr, ...; the Psi1 term in range 0): partial dZ[m, :] per (chunk, range).
-template <typename T, int QM>
-__global__ __launch_bounds__(kColBlock) void grad_cols_kernel(const int *__restrict__ gate, 
-    int64_t N, int M, int Q, int cr, int64_t rows_per_chunk, const T *__restrict__ mu,
-    const T *__restrict__ Z, const T *__restrict__ w1, const T *__restrict__ w2,
-    const T *__restrict__ lp1, const T *__restrict__ lp2, Hyp<T> h, const T *__restrict__ G1,
-    const T *__restrict__ G2s, T *__restrict__ colpart) {
-    if (gate && gate[0] == 0) return;
-    __shared__ T s_mu[kRowTile][QM];
-    __shared__ T s_w1[kRowTile][QM];
-    __shared__ T s_w2[kRowTile][QM];
-    __shared__ T s_lp1[kRowTile], s_lp2[kRowTile];
-    const int m = blockIdx.x * kColBlock + threadIdx.x;
-    const bool valid = m < M;
-    T zm[QM], gz[QM];
-#pragma unroll
-    for (int q = 0; q < QM; ++q) {
-        gz[q] = 0;
-        zm[q] = (q < Q && valid) ? Z[(int64_t)m * Q + q] : T(0);
-    }
-    const int64_t r0 = (int64_t)blockIdx.y * rows_per_chunk;
-    const int64_t r1 = min(N, r0 + rows_per_chunk);
-    for (int64_t base = r0; base < r1; base += kRowTile) {
-        const int cnt = (int)min<int64_t>(kRowTile, r1 - base);
-        __syncthreads();
-        for (int i = threadIdx.x; i < cnt * Q; i += blockDim.x) {
-            int r = i / Q, q = i - r * Q;
-            s_mu[r][q] = mu[(base + r) * Q + q];
-            s_w1[r][q] = w1[(base + r) * Q + q];
-            s_w2[r][q] = w2[(base + r) * Q + q];
-        }
-        for (int r = threadIdx.x; r < cnt; r += blockDim.x) {
-            s_lp1[r] = lp1[base + r];
-            s_lp2[r] = lp2[base + r];
-        }
-        __syncthreads();
-        if (!valid) continue;
-        for (int r = 0; r < cnt; ++r) {
-            if (G1 && blockIdx.z == 0) {
-                T e = 0;
-#pragma unroll
-                for (int q = 0; q < QM; ++q)
-                    if (q < Q) {
-                        T d = s_mu[r][q] - zm[q];
-                        e += d * d * s_w1[r][q];
-                    }
-                const T t = G1[(base + r) * M + m] * dexp(s_lp1[r] - T(0.5) * e);
-#pragma unroll
-                for (int q = 0; q < QM; ++q)
-                    if (q < Q) gz[q] += t * (s_mu[r][q] - zm[q]) * s_w1[r][q];
-            }
-            if (G2s) {
-                // two-level sum: the row's partners first, then into the chunk total
-                // (the 64-wide variant, already short of registers, adds directly)
-                constexpr bool kTwo = QM <= 32;
-                T gzr_[kTwo ? QM : 1];
-                T *gzr = kTwo ? gzr_ : gz;
-                if constexpr (kTwo) {
-#pragma unroll
-                    for (int q = 0; q < QM; ++q) gzr[q] = 0;
-                }
-                for (int mp = blockIdx.z; mp < M; mp += cr) {
-                    const T g = G2s[(int64_t)mp * M + m];
-                    T e = s_lp2[r];
-#pragma unroll
-                    for (int q = 0; q < QM; ++q)
-                        if (q < Q) {
-                            T b = Z[(int64_t)mp * Q + q];
-                            T d = s_mu[r][q] - T(0.5) * (zm[q] + b);
-                            e -= (zm[q] - b) * (zm[q] - b) / (T(4) * h.l2[q]) +
-                                 d * d * s_w2[r][q];
-                        }
-                    const T t = T(2) * g * dexp(e);
-#pragma unroll
-                    for (int q = 0; q < QM; ++q)
-                        if (q < Q) {
-                            T b = Z[(int64_t)mp * Q + q];
-                            T d = s_mu[r][q] - T(0.5) * (zm[q] + b);
-                            gzr[q] += t * (d * s_w2[r][q] - (zm[q] - b) / (T(2) * h.l2[q]));
-                        }
-                }
-                if constexpr (kTwo) {
-#pragma unroll
-                    for (int q = 0; q < QM; ++q) gz[q] += gzr[q];
-                }
-            }
-        }
-    }
-    if (valid) {
-#pragma unroll
-        for (int q = 0; q < QM; ++q)
-            if (q < Q) colpart[(((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * M + m) * Q + q] = gz[q];
-    }
-}
-
 // Fixed-order reductions of the gradient partials, one launch.  Workgroups below
 // rb: dmu, dS, the nblk partials [nblk][2][N][Q] in block order (none where the
 // kernel before wrote them itself).  Then zb workgroups for dZ: with `wide` 32
@@ -1149,240 +866,6 @@ __global__ __launch_bounds__(256) void grad_finish_kernel(
     }
 }
 
-// Wide form of the ordered pairs gradient, for Q past the pairs kernel's
-// register budget (same outputs as grad_pairs_kernel with SYM = false: om, os,
-// colpart, rowpart).  Two lanes of a wave share an inducing input m (lanes l
-// and l + 32) and each holds QH of its dimensions (lane half hh takes
-// q = hh QH .. hh QH + QH - 1), which halves the per-dimension registers (z,
-// the exponent's coefficients, the V sums, the dZ and dl partials).  Per partner
-// m' each lane forms its half of the exponent (the same quadratic in
-// v = z_m' - z_m as the pairs kernel); the halves are exchanged across the lane
-// pair and added in the same order on both lanes, so both evaluate the same
-// W = G2s[m, m'] Psi2_n[m, m'] and update their own dimensions:
-//   r += W,   Vd_q += W (z_m'q - z_mq)
-// (the local differences, not W z_m'q, so that no sum of the size of |z| r
-// cancels in the dZ and dl terms; V = d r - Vd).
-// Row values are read from clamped addresses and masked, so that their loads
-// issue together.  One workgroup per (block of 128 inducing inputs, row chunk).
-template <typename T, int QH>
-__global__ __launch_bounds__(256) void grad_wide_kernel(const int *__restrict__ gate,
-    int64_t N, int M, int Q, int64_t rows_per_chunk, const T *__restrict__ mu,
-    const T *__restrict__ S, const T *__restrict__ Z, const T *__restrict__ w1t,
-    const T *__restrict__ w2t, const T *__restrict__ lp1, const T *__restrict__ lp2, Hyp<T> h,
-    const T *__restrict__ G1, const T *__restrict__ G2s, T *__restrict__ om, T *__restrict__ os,
-    T *__restrict__ colpart, T *__restrict__ rowpart) {
-    if (gate && gate[0] == 0) return;
-    constexpr int QM = 2 * QH;
-    extern __shared__ double gw_smem[];
-    T *sz = reinterpret_cast<T *>(gw_smem);  // [M][QM], zero beyond Q
-    __shared__ T red[2][4][2 * QM];           // per-wave row sums, double buffered by row
-    __shared__ T redf[4][QM + 1];             // per-wave dl and dsf2 sums
-    __shared__ T sc4[QM], sil2[QM], sl[QM], sinvl[QM];  // 1/(4 l^2), 1/l^2, l, 1/l (zero
-                                                        // beyond Q, except l = 1)
-    __shared__ T srow[2][4][QM];              // staged row values (mu, w1, w2, S)
-    __shared__ T sgl[4][QM];                  // per-wave dl sums over the chunk
-    T *sgz = sz + M * QM;                     // [128][QM] the threads' dZ_m sums (dynamic LDS)
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, hh = lane >> 5;
-    const int m = blockIdx.x * 128 + wv * 32 + (lane & 31);
-    const bool valid = m < M;                 // the same on both lanes of a pair
-    const int q0 = hh * QH;
-    for (int i = tid; i < M * QM; i += 256) {
-        const int mm = i / QM, q = i - mm * QM;
-        sz[i] = q < Q ? Z[(int64_t)mm * Q + q] : T(0);
-    }
-    for (int q = tid; q < QM; q += 256) {
-        sc4[q] = q < Q ? T(0.25) / h.l2[q] : T(0);
-        sil2[q] = q < Q ? T(1) / h.l2[q] : T(0);
-        sl[q] = q < Q ? h.l[q] : T(1);
-        sinvl[q] = q < Q ? T(1) / h.l[q] : T(0);
-    }
-    __syncthreads();
-    // the thread's dZ_m sums and each half-wave's dl sums live in LDS slots
-    // that only they write (read-modify-write once per row and dimension)
-    T z[QH];
-    const int ml = m - blockIdx.x * 128;      // the thread's inducing input in the block
-#pragma unroll
-    for (int j = 0; j < QH; ++j) {
-        z[j] = valid ? sz[m * QM + q0 + j] : T(0);
-        sgz[ml * QM + q0 + j] = 0;
-    }
-    if ((lane & 31) == 0)
-        for (int j = 0; j < QH; ++j) sgl[wv][q0 + j] = 0;
-    T gsf = 0;
-    // Each row's values (mu, w1, w2, S at every dimension, zero beyond Q) are
-    // staged in LDS, double buffered by row parity: the next row's are written
-    // before the barrier that ends the current row.
-    auto stage_row = [&](int64_t n, int buf) {
-        for (int i = tid; i < 4 * QM; i += 256) {
-            const int k = i / QM, q = i - k * QM;
-            const T *src = k == 0 ? mu : k == 1 ? w1t : k == 2 ? w2t : S;
-            srow[buf][k][q] = (q < Q ? T(1) : T(0)) * src[n * Q + min(q, Q - 1)];
-        }
-    };
-    // the two halves of a per-lane-pair sum, added in the same order on both lanes
-    auto pair_sum = [&](T own) {
-        const T other = __shfl_xor(own, 32);
-        return hh == 0 ? own + other : other + own;
-    };
-    const int64_t r0 = (int64_t)blockIdx.y * rows_per_chunk, r1 = min(N, r0 + rows_per_chunk);
-    if (r0 < r1) stage_row(r0, (int)(r0 & 1));
-    __syncthreads();
-    for (int64_t n = r0; n < r1; ++n) {
-        const int b = (int)(n & 1);   // the row's buffer (its first row may be odd)
-        const T *xs = srow[b][0] + q0, *a1s = srow[b][1] + q0, *a2s = srow[b][2] + q0,
-                *svs = srow[b][3] + q0;
-        T bq[QH], cq[QH], Vd[QH];
-        T r = 0, e0 = 0;
-        {
-            T part = 0;
-#pragma unroll
-            for (int j = 0; j < QH; ++j) {
-                const T a2 = a2s[j], d = xs[j] - z[j];
-                bq[j] = a2 * d;
-                cq[j] = sc4[q0 + j] + T(0.25) * a2;
-                part -= bq[j] * d;
-                Vd[j] = 0;
-            }
-            e0 = (G2s ? lp2[n] : T(0)) + pair_sum(part);
-        }
-        if (G2s && valid) {
-            // G2s is symmetric: G2s[m'][m] is a coalesced row over the wave's m;
-            // its entries are loaded kAhead partners ahead
-            constexpr int kAhead = 2;
-            const T *g2 = G2s + m;
-            T gb[kAhead];
-#pragma unroll
-            for (int u = 0; u < kAhead; ++u) gb[u] = u < M ? g2[(int64_t)u * M] : T(0);
-            for (int mp0 = 0; mp0 < M; mp0 += kAhead) {
-#pragma unroll
-                for (int u = 0; u < kAhead; ++u) {
-                    const int mp = mp0 + u;
-                    if (mp >= M) break;  // uniform
-                    const T g = gb[u];
-                    if (mp + kAhead < M) gb[u] = g2[(int64_t)(mp + kAhead) * M];
-                    const T *zr = sz + mp * QM + q0;
-                    T v[QH];
-#pragma unroll
-                    for (int j = 0; j < QH; ++j) v[j] = zr[j] - z[j];
-                    T ep = 0;
-#pragma unroll
-                    for (int j = 0; j < QH; ++j) ep = fma(v[j], fma(-cq[j], v[j], bq[j]), ep);
-                    const T W = g * dexp(e0 + pair_sum(ep));
-                    r += W;
-#pragma unroll
-                    for (int j = 0; j < QH; ++j) Vd[j] = fma(W, v[j], Vd[j]);
-                }
-            }
-        }
-        T t = 0;
-        if (G1 && valid) {
-            T e1 = 0;
-#pragma unroll
-            for (int j = 0; j < QH; ++j) {
-                const T d = xs[j] - z[j];
-                e1 += d * d * a1s[j];
-            }
-            t = G1[n * M + m] * dexp(lp1[n] - T(0.5) * pair_sum(e1));
-        }
-        // per dimension: the dmu / dS terms summed over the block's m (butterflies
-        // within each half-wave, whose lanes hold the same dimensions; then the
-        // waves in order), the thread's dZ_m and dl terms.  The scheduling
-        // barrier keeps each dimension's reads in its own step, so that the
-        // epilogue does not hold every dimension's values at once.
-        gsf += hh == 0 ? T(2) * r + t : T(0);  // dsf2 term, counted once per m
-#pragma unroll
-        for (int j = 0; j < QH; ++j) {
-            const int q = q0 + j;
-            const T x = xs[j], a1 = a1s[j], a2 = a2s[j], sv = svs[j];
-            // with V = d r - Vd: d r + V = 2 d r - Vd, V - d r = -Vd,
-            // d^2 r + d V = d (d r + V), d^2 r - d V = d Vd
-            const T dq = x - z[j], d2 = dq * dq, dr = dq * r;
-            const T s1 = T(2) * dr - Vd[j];
-            const T il2 = sil2[q], l = sl[q], il = sinvl[q];
-            T v0 = -T(2) * a2 * dr - t * dq * a1;
-            T v1 = a2 * a2 * (dq * s1) - a2 * r + T(0.5) * t * (d2 * a1 * a1 - a1);
-            sgz[ml * QM + q] += a2 * s1 + Vd[j] * il2 + t * dq * a1;
-            T v2 = (T(2) * sv * a2 * il) * r + dq * Vd[j] * il2 * il + l * a2 * a2 * (dq * s1) +
-                   t * (sv * a1 * il + l * d2 * a1 * a1);
-#pragma unroll
-            for (int off = 16; off >= 1; off >>= 1) {
-                v0 += __shfl_xor(v0, off);
-                v1 += __shfl_xor(v1, off);
-                v2 += __shfl_xor(v2, off);
-            }
-            if ((lane & 31) == 0) {
-                red[b][wv][q] = v0;
-                red[b][wv][QM + q] = v1;
-                sgl[wv][q] += v2;
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        if (n + 1 < r1) stage_row(n + 1, b ^ 1);
-        __syncthreads();
-        if (tid < 2 * Q) {
-            const int part = tid < Q ? 0 : 1, q = tid < Q ? tid : tid - Q;
-            T v = 0;
-            for (int w = 0; w < 4; ++w) v += red[b][w][part * QM + q];
-            (part == 0 ? om : os)[((int64_t)blockIdx.x * 2 * N + n) * Q + q] = v;
-        }
-    }
-    if (valid) {
-#pragma unroll
-        for (int j = 0; j < QH; ++j)
-            if (q0 + j < Q)
-                colpart[((int64_t)blockIdx.y * M + m) * Q + q0 + j] = sgz[ml * QM + q0 + j];
-    }
-    // block sums of dl and dsf2 (fixed order) -> rowpart[block][Q + 1]
-    if ((lane & 31) == 0)
-        for (int j = 0; j < QH; ++j) redf[wv][q0 + j] = sgl[wv][q0 + j];
-    {
-        T v = gsf;
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-        if (lane == 0) redf[wv][QM] = v;
-    }
-    __syncthreads();
-    const int64_t blk = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-    if (tid <= Q) {
-        const int k = tid < Q ? tid : QM;
-        T v = 0;
-        for (int w = 0; w < 4; ++w) v += redf[w][k];
-        rowpart[blk * (Q + 1) + tid] = tid < Q ? v : v / h.sf2;
-    }
-}
-
-template <typename T, int QM>
-void launch_psi2_partial(const Shape &s, const Plan &p, const T *mu, const T *Z, const T *w2,
-                         const T *lp2, const Hyp<T> &h, T *partial, const int *gate,
-                         hipStream_t st) {
-    dim3 grid((unsigned)p.pblocks, (unsigned)p.nc2);
-    TimedScope ts(st, "generic_psi2_partial");
-    if (fwd_ppt(s.Q, sizeof(T)) == 2)
-        psi2_partial_kernel<T, QM, 2><<<grid, 256, 0, st>>>(gate, s.N, (int)s.M, (int)s.Q, s.P,
-                                                            p.rows2, mu, Z, w2, lp2, h, partial);
-    else
-        psi2_partial_kernel<T, QM, 1><<<grid, 256, 0, st>>>(gate, s.N, (int)s.M, (int)s.Q, s.P,
-                                                            p.rows2, mu, Z, w2, lp2, h, partial);
-}
-
-template <typename T, int QM>
-void launch_grads(const Shape &s, const Plan &p, const T *mu, const T *S, const T *Z,
-                  const T *w1, const T *w2, const T *lp1, const T *lp2, const Hyp<T> &h,
-                  const T *G1, const T *G2s, T *om, T *os, T *colpart, T *rowpart, const int *gate,
-                  hipStream_t st) {
-    {
-        TimedScope ts(st, "generic_grad_rows");
-        grad_rows_kernel<T, QM><<<dim3((unsigned)p.row_blocks, (unsigned)p.rr), kRowBlock, 0, st>>>(gate, 
-            s.N, (int)s.M, (int)s.Q, (int)p.rr, mu, S, Z, w1, w2, lp1, lp2, h, G1, G2s, om, os,
-            rowpart);
-    }
-    dim3 grid((unsigned)p.col_blocks, (unsigned)p.ncc, (unsigned)p.cr);
-    TimedScope ts(st, "generic_grad_cols");
-    grad_cols_kernel<T, QM><<<grid, kColBlock, 0, st>>>(gate, s.N, (int)s.M, (int)s.Q, (int)p.cr,
-                                                         p.rowsc, mu, Z, w1, w2, lp1, lp2, h, G1,
-                                                         G2s, colpart);
-}
-
 // The per-row tables, and the symmetric part of dL/dPsi2 as `mode` asks.
 template <typename T>
 void pre(const Shape &s, const Plan &p, const T *S, const Hyp<T> &h, void *ws, const int *gate,
@@ -1428,19 +911,21 @@ hipError_t generic_psi_stats(const Shape &s, const T *mu, const T *S, const T *Z
     pre<T>(s, p, S, h, ws, gate, mark, st);
     const T *w1 = at<T>(ws, p.off_w1), *w2 = at<T>(ws, p.off_w2);
     const T *lp1 = at<T>(ws, p.off_lp1), *lp2 = at<T>(ws, p.off_lp2);
-    if constexpr (sizeof(T) == 8) {
-        const size_t budget = p.total - p.off_p2;
-        if (f64_stats_fit(s, budget))
-            return f64_psi2(s, mu, Z, w1, w2, lp1, lp2, h, psi0, Psi1, Psi2, accumulate,
-                            at<char>(ws, p.off_p2), budget, st);
-    }
+    if (p.tstats)
+        return tiles_psi2<T>(s, mu, Z, w1, w2, lp1, lp2, h, psi0, Psi1, Psi2, accumulate,
+                             at<char>(ws, p.off_p2), p.total - p.off_p2, gate, st);
     T *partial = at<T>(ws, p.off_p2);
-    switch (fwd_qm(s.Q)) {
-#define GPPS_FWD(QMV) \
-    case QMV: launch_psi2_partial<T, QMV>(s, p, mu, Z, w2, lp2, h, partial, gate, st); break
-        GPPS_FWD(1); GPPS_FWD(2); GPPS_FWD(4); GPPS_FWD(8); GPPS_FWD(12); GPPS_FWD(16);
-        GPPS_FWD(20); GPPS_FWD(24); GPPS_FWD(32); GPPS_FWD(48);
-        default: launch_psi2_partial<T, 64>(s, p, mu, Z, w2, lp2, h, partial, gate, st); break;
+    {
+        const dim3 grid((unsigned)p.pblocks, (unsigned)p.nc2);
+        TimedScope ts(st, "generic_psi2_partial");
+#define GPPS_FWD(QMV)                                                                              \
+    psi2_partial_kernel<T, QMV><<<grid, 256, 0, st>>>(gate, s.N, (int)s.M, (int)s.Q, s.P, p.rows2, \
+                                                      mu, Z, w2, lp2, h, partial)
+        switch (pairs_qm(s.Q)) {
+            case 1: GPPS_FWD(1); break;
+            case 2: GPPS_FWD(2); break;
+            default: GPPS_FWD(4); break;
+        }
 #undef GPPS_FWD
     }
     const int64_t tiles = p.tiles_edge * p.tiles_edge;
@@ -1459,36 +944,33 @@ hipError_t generic_psi_grads(const Shape &s, const T *mu, const T *S, const T *Z
     const Plan p = make_plan(s, sizeof(T));
     const T *w1 = at<T>(ws, p.off_w1), *w2 = at<T>(ws, p.off_w2);
     const T *lp1 = at<T>(ws, p.off_lp1), *lp2 = at<T>(ws, p.off_lp2);
-    if constexpr (sizeof(T) == 8) {
-        const F64GradPlan f = f64_grad_plan(s, p.total - p.off_p2);
-        if (f.ok) {
-            char *region = at<char>(ws, p.off_p2);
-            T *Gc = G2 ? at<T>(region, f.off_gc) : nullptr;
-            pre<T>(s, p, S, h, ws, gate, mark, st, G2 ? kSymPadded : kSymNone, G2, Z, Gc);
-            const hipError_t e = f64_psi2_grads(s, f, mu, S, Z, w1, w2, lp1, lp2, h, G1, Gc, dmu, dS,
-                                                region, st);
-            if (e != hipSuccess) return e;
-            finish<T>(s, f.groups, at<T>(region, f.off_rowg), dmu, dS, f.chunks, f.chunks * f.groups,
-                      at<T>(region, f.off_colp), at<T>(region, f.off_rowp), dL_dpsi0, dZ, dsf2, dl,
-                      accumulate, gate, st);
-            return hipGetLastError();
-        }
+    if (p.tgrads) {
+        const TilesGradPlan f = tiles_grad_plan(s, p.total - p.off_p2, sizeof(T));
+        if (!f.ok) return hipErrorInvalidValue;   // no shape: the region holds at least one chunk
+        char *region = at<char>(ws, p.off_p2);
+        T *Gc = G2 ? at<T>(region, f.off_gc) : nullptr;
+        pre<T>(s, p, S, h, ws, gate, mark, st, G2 ? kSymPadded : kSymNone, G2, Z, Gc);
+        const hipError_t e = tiles_psi2_grads<T>(s, f, mu, S, Z, w1, w2, lp1, lp2, h, G1, Gc, dmu, dS,
+                                                 region, gate, st);
+        if (e != hipSuccess) return e;
+        finish<T>(s, f.groups, at<T>(region, f.off_rowg), dmu, dS, f.chunks, f.chunks * f.groups,
+                  at<T>(region, f.off_colp), at<T>(region, f.off_rowp), dL_dpsi0, dZ, dsf2, dl,
+                  accumulate, gate, st);
+        return hipGetLastError();
     }
     T *colpart = at<T>(ws, p.off_colp), *rowpart = at<T>(ws, p.off_rowp);
     T *rowg = at<T>(ws, p.off_rowg);
-    const bool sym = p.pairs && p.psym && G2;
+    const bool sym = p.psym && G2;
     T *G2s = G2 ? at<T>(ws, sym ? p.off_gc : p.off_g2s) : nullptr;
     pre<T>(s, p, S, h, ws, gate, mark, st, !G2 ? kSymNone : sym ? kSymCirc : kSymPlain, G2, Z, G2s);
-    // one block of columns (or range of pair rows) writes dmu and dS themselves
-    const int64_t nblk = p.pairs ? p.pmb : p.wide ? p.wmb : p.rr;
-    T *om = nblk > 1 ? rowg : dmu, *os = nblk > 1 ? rowg + s.N * s.Q : dS;
-    if (p.pairs) {
-        const size_t lds = sizeof(T) * s.M * (pairs_qm(s.Q) + (sym ? 2 * kBand : 0));
-        const size_t lds_slots =
-            sizeof(T) * s.M * (pairs_qm(s.Q) + p.prs * 2 * kSlotBand + p.prs * 2 * pairs_qm(s.Q));
-        dim3 grid((unsigned)p.pmb, (unsigned)p.pchunks);
-        {
-            TimedScope ts(st, "generic_grad_pairs");
+    // one block of columns writes dmu and dS themselves
+    T *om = p.pmb > 1 ? rowg : dmu, *os = p.pmb > 1 ? rowg + s.N * s.Q : dS;
+    const size_t lds = sizeof(T) * s.M * (pairs_qm(s.Q) + (sym ? 2 * kBand : 0));
+    const size_t lds_slots =
+        sizeof(T) * s.M * (pairs_qm(s.Q) + p.prs * 2 * kSlotBand + p.prs * 2 * pairs_qm(s.Q));
+    dim3 grid((unsigned)p.pmb, (unsigned)p.pchunks);
+    {
+        TimedScope ts(st, "generic_grad_pairs");
 #define GPPS_PAIRS(QMV)                                                                            \
     do {                                                                                           \
         if (sym && p.pslots)                                                                       \
@@ -1504,64 +986,14 @@ hipError_t generic_psi_grads(const Shape &s, const T *mu, const T *S, const T *Z
                 s.N, (int)s.M, (int)s.Q, p.prows, mu, S, Z, w1, w2, lp1, lp2, h, G1, G2s, nullptr, \
                 om, os, colpart, rowpart);                                                         \
     } while (0)
-            switch (pairs_qm(s.Q)) {
-                case 1: GPPS_PAIRS(1); break;
-                case 2: GPPS_PAIRS(2); break;
-                case 4: GPPS_PAIRS(4); break;
-                default:
-                    if (sizeof(T) == 4) GPPS_PAIRS(8);
-                    break;
-            }
+        switch (pairs_qm(s.Q)) {
+            case 1: GPPS_PAIRS(1); break;
+            case 2: GPPS_PAIRS(2); break;
+            default: GPPS_PAIRS(4); break;
+        }
 #undef GPPS_PAIRS
-        }
-        finish<T>(s, nblk, rowg, dmu, dS, p.pchunks, p.pmb * p.pchunks, colpart, rowpart, dL_dpsi0, dZ,
-                  dsf2, dl, accumulate, gate, st);
-        return hipGetLastError();
     }
-    if (p.wide) {
-        const size_t lds = sizeof(T) * (s.M + 128) * 2 * p.wqh;
-        dim3 grid((unsigned)p.wmb, (unsigned)p.wchunks);
-        {
-            TimedScope ts(st, "generic_grad_wide");
-#define GPPS_WIDE(QHV)                                                                             \
-    case QHV:                                                                                      \
-        grad_wide_kernel<T, QHV><<<grid, 256, lds, st>>>(gate, s.N, (int)s.M, (int)s.Q, p.wrows,   \
-                                                          mu, S, Z, w1, w2, lp1, lp2, h, G1, G2s,  \
-                                                          om, os, colpart, rowpart);               \
-        break
-            switch (p.wqh) {
-                GPPS_WIDE(4);
-                GPPS_WIDE(6);
-                GPPS_WIDE(8);
-                GPPS_WIDE(10);
-                GPPS_WIDE(12);
-                GPPS_WIDE(16);
-                default:
-                    if constexpr (sizeof(T) == 4) {
-                        switch (p.wqh) {
-                            GPPS_WIDE(24);
-                            GPPS_WIDE(32);
-                            default: break;
-                        }
-                    }
-                    break;
-            }
-#undef GPPS_WIDE
-        }
-        finish<T>(s, nblk, rowg, dmu, dS, p.wchunks, p.wmb * p.wchunks, colpart, rowpart, dL_dpsi0, dZ,
-                  dsf2, dl, accumulate, gate, st);
-        return hipGetLastError();
-    }
-#define GPPS_ROWS(QMV)                                                                             \
-    launch_grads<T, QMV>(s, p, mu, S, Z, w1, w2, lp1, lp2, h, G1, G2s, om, os, colpart, rowpart,   \
-                         gate, st)
-    if (s.Q <= 4) GPPS_ROWS(4);
-    else if (s.Q <= 8) GPPS_ROWS(8);
-    else if (s.Q <= 16) GPPS_ROWS(16);
-    else if (s.Q <= 32) GPPS_ROWS(32);
-    else GPPS_ROWS(64);
-#undef GPPS_ROWS
-    finish<T>(s, nblk, rowg, dmu, dS, p.ncc * p.cr, p.rr * p.row_blocks, colpart, rowpart, dL_dpsi0, dZ,
+    finish<T>(s, p.pmb, rowg, dmu, dS, p.pchunks, p.pmb * p.pchunks, colpart, rowpart, dL_dpsi0, dZ,
               dsf2, dl, accumulate, gate, st);
     return hipGetLastError();
 }

@@ -68,38 +68,44 @@ hipError_t generic_psi_grads(const Shape &s, const T *mu, const T *S, const T *Z
                              T *dS, T *dZ, T *dsf2, T *dl, int accumulate, void *ws,
                              const int *gate, int *mark, hipStream_t st);
 
-// ---------------------------------------------------------------- double precision
-// Psi2 and its gradients in F64 on the matrix cores.  They take the generic path's
+// ---------------------------------------------------------------- 16 x 16 tiles
+// Psi2 and its gradients on the fp64 and fp32 matrix instructions, in the precision
+// of the element type throughout.  They take the generic path's
 // per-row tables and reduces, and the part of its workspace behind the tables
 // (`budget` bytes at `ws`): the plans fit their chunks to it, so that the path
 // needs no more workspace than the vector kernels it replaces.
 // They are taken where they measured faster than the vector kernels (us per call at
-// N = 64,000, vector / matrix): statistics 297 / 483 at M = 100, Q = 1, 458 / 489 at
-// Q = 4 and 569 / 555 at Q = 5, but 1684 / 1425 at M = 200, Q = 4; gradients
+// N = 64,000 in fp64, vector / tiles): statistics 297 / 483 at M = 100, Q = 1, 458 / 489
+// at Q = 4 and 569 / 555 at Q = 5, but 1684 / 1425 at M = 200, Q = 4; gradients
 // 607 / 1098 at M = 100, Q = 1, 1041 / 1102 at Q = 2 and 1848 / 1108 at Q = 4, but
-// 5755 / 4365 at M = 256, Q = 2.  Small Q pads the products' four dimensions, and the
-// vector kernels' symmetric form takes one exponential per unordered pair.
-bool f64_stats_wanted(const Shape &s);
-bool f64_grads_wanted(const Shape &s);
-size_t f64_region_bytes(const Shape &s);   // the region with which no plan is cut short
-bool f64_stats_fit(const Shape &s, size_t budget);
-hipError_t f64_psi2(const Shape &s, const double *mu, const double *Z, const double *w1,
-                    const double *w2, const double *lp1, const double *lp2, const Hyp<double> &h,
-                    double *psi0, double *Psi1, double *Psi2, int accumulate, void *ws, size_t budget,
-                    hipStream_t st);
+// 5755 / 4365 at M = 256, Q = 2; at N = 30,000 in fp32 90 / 117, 141 / 138 (Q = 4, 5,
+// M = 100), 412 / 394 and 616 / 470 (M = 256); gradients 304 / 332 and 1453 / 1216 at
+// Q = 4, 855 / 366 and 4510 / 1348 at Q = 5.  Small Q pads the products' four dimensions,
+// and the vector kernels take one exponential per unordered pair.
+bool tiles_stats_wanted(const Shape &s, size_t elem);
+bool tiles_grads_wanted(const Shape &s, size_t elem);
+struct TilesRegion {
+    size_t least, want;   // bytes behind the tables: the fewest that run, and all they can use
+};
+TilesRegion tiles_region(const Shape &s, size_t elem);
+template <typename T>
+hipError_t tiles_psi2(const Shape &s, const T *mu, const T *Z, const T *w1, const T *w2, const T *lp1,
+                      const T *lp2, const Hyp<T> &h, T *psi0, T *Psi1, T *Psi2, int accumulate, void *ws,
+                      size_t budget, const int *gate, hipStream_t st);
 
-struct F64GradPlan {
+struct TilesGradPlan {
     bool ok;                          // the region holds it
     int64_t chunks, rows;             // row chunks, rows per chunk
     int groups, nw, wrows, nwin;      // workgroups per chunk, waves, z rows staged, windows
     size_t lds;
     size_t off_gc, off_rowg, off_colp, off_rowp, end;
 };
-F64GradPlan f64_grad_plan(const Shape &s, size_t budget);
-hipError_t f64_psi2_grads(const Shape &s, const F64GradPlan &p, const double *mu, const double *S,
-                          const double *Z, const double *w1, const double *w2, const double *lp1,
-                          const double *lp2, const Hyp<double> &h, const double *G1,
-                          const double *Gc, double *dmu, double *dS, void *ws, hipStream_t st);
+TilesGradPlan tiles_grad_plan(const Shape &s, size_t budget, size_t elem);
+template <typename T>
+hipError_t tiles_psi2_grads(const Shape &s, const TilesGradPlan &p, const T *mu, const T *S, const T *Z,
+                            const T *w1, const T *w2, const T *lp1, const T *lp2, const Hyp<T> &h,
+                            const T *G1, const T *Gc, T *dmu, T *dS, void *ws, const int *gate,
+                            hipStream_t st);
 
 // ---------------------------------------------------------------- matrix-core path
 // F32 only: per-datapoint Gram blocks and W * D products on MFMA, exp on VALU.

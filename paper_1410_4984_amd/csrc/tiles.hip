@@ -1,5 +1,6 @@
-// Double-precision Psi2 and its gradients on the matrix cores
-// (v_mfma_f64_16x16x4f64 and v_mfma_f64_4x4x4f64).
+// Psi2 and its gradients on the matrix instructions of the element type itself
+// (v_mfma_f64_16x16x4f64, v_mfma_f64_4x4x4f64, v_mfma_f32_16x16x4f32): every operand,
+// product and sum is double in fp64 and single in fp32.
 //
 // With d_m = mu_n - z_m, w2 = 1 / (l^2 + 2 S_n) and lambda = log2 e, the part of
 // log2 Psi2_n[m, m'] that depends on n is
@@ -12,18 +13,21 @@
 // d_m ~ -d_m' makes b_m cancel against the product, C is more negative than
 // either.
 //
-// What bounds these kernels is the vector unit's double-precision issue rate.
-// A 16 x 16 x 4 product occupies a SIMD for 64 cycles and no vector
+// What bounds these kernels is the SIMDs' issue rate.  In fp64 a 16 x 16 x 4 product occupies a SIMD for 64 cycles and no vector
 // instruction issues meanwhile (measured: 8 FMAs behind each product add 8 FMAs'
 // time), so matrix and vector work add up: a matrix FMA costs the same as a
 // vector one, but needs one operand load per 16 of them, no cross-lane sums and
 // no index arithmetic.  The exponential is 2^E' in 15 instructions (the table's
-// ln 2 is folded into x and b), against about 21 of exp().
+// ln 2 is folded into x and b), against about 21 of exp().  In fp32 a product takes 32
+// cycles and the exponential is one instruction.
 //
 // Measured against the vector kernels (fp64, psi2 gradient + forward): 45.3 + 10.6 ms
 // -> 14.8 + 5.0 ms at N = 100,000, M = 256, Q = 20; 3.34 + 0.53 -> 1.43 + 0.48 ms at
 // N = 50,000, M = 100, Q = 10; 261 + 3.7 -> 3.3 + 1.2 ms at N = 4096, M = 512, Q = 30.
 // At the first shape the SIMDs' issue is 40% matrix and 30-40% vector instructions.
+// fp32, statistics + gradients: 4.06 -> 1.9 ms at N = 3001, M = 700, Q = 12; 54 -> 0.75 ms
+// at N = 1500, M = 300, Q = 40; 2.2 s -> 40 ms at N = 40,000, M = 700, Q = 31 (the vector
+// kernels' z table did not fit LDS there).
 //
 // Rows whose exponents leave the range in which that is exact (|b| < 2^26: means
 // thousands of lengthscales from an inducing input, infinities, NaN) take a
@@ -39,22 +43,48 @@
 namespace gpps {
 namespace {
 
-typedef double d4 __attribute__((ext_vector_type(4)));
-
 constexpr size_t kLdsMax = 160 * 1024;
 constexpr int kSimds = 1024;   // 256 CUs x 4
 constexpr double kLog2e = 1.4426950408889634074;
-constexpr double kSlow = 67108864.0;  // 2^26: the largest |b| of the fast exponential
+// The largest |b| of the fast exponential (fp64: its integer part has to fit 32 bits;
+// fp32: beyond it b's rounding passes 0.1, and 2^E' of such a row is zero).
+template <typename T>
+__host__ __device__ constexpr T slow_limit() { return sizeof(T) == 8 ? T(67108864.0) : T(1048576.0); }
 
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-__device__ inline d4 mfma16(double a, double b, d4 c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
+// The matrix instructions: 16 x 16 x 4 products (operand lane l holds row or column
+// l % 16 and k = l / 16), whose result register v of lane group g holds row
+// row(v, g), and, in fp64 only, four independent 4 x 4 x 4 ones.
+template <typename T>
+struct Mm;
+template <>
+struct Mm<double> {
+    typedef double v4 __attribute__((ext_vector_type(4)));
+    static constexpr bool kFours = true;
+    static __device__ v4 mul(double a, double b, v4 c) {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
+    static __device__ double fours(double a, double b, double c) {
+        return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
+    }
+    static __host__ __device__ constexpr int row(int v, int g) { return 4 * v + g; }
+};
+template <>
+struct Mm<float> {
+    typedef float v4 __attribute__((ext_vector_type(4)));
+    static constexpr bool kFours = false;
+    static __device__ v4 mul(float a, float b, v4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+    static __device__ float fours(float, float, float) { return 0.f; }
+    static __host__ __device__ constexpr int row(int v, int g) { return 4 * g + v; }
+};
+template <typename T>
+__device__ inline typename Mm<T>::v4 zero4() { return typename Mm<T>::v4{0, 0, 0, 0}; }
 // Sum over the four lane groups (lanes l, l + 16, l + 32, l + 48), in every lane.
-__device__ inline double sum_groups(double v) {
-    return __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, v, 0.0, 0, 0, 0);
-}
+__device__ inline double sum_groups(double v) { return Mm<double>::fours(1.0, v, 0.0); }
+__device__ inline float sum_groups(float v) { return Mm<float>::mul(1.f, v, zero4<float>())[0]; }
 
 // 2^x for |x| < 2^31: x = n + f with n the nearest integer, 2^f by a polynomial of
 // degree 11 with constant term 1 (minimax in the relative error over |f| <= 1/2,
@@ -80,16 +110,20 @@ __device__ inline double exp2_fast(double x) {
     return __builtin_amdgcn_ldexp(p, n);
 }
 
+__device__ inline float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
+__device__ inline double dexp(double x) { return exp(x); }
+__device__ inline float dexp(float x) { return __expf(x); }
+
 // Psi2_n[m, m'] without the pair factor, by the closed form itself (slow rows).
-__device__ inline double direct_pair(const double *__restrict__ x, const double *__restrict__ w2,
-                                     double lp2, const double *__restrict__ za,
-                                     const double *__restrict__ zb, int Q) {
-    double e = lp2;
+template <typename T>
+__device__ inline T direct_pair(const T *__restrict__ x, const T *__restrict__ w2, T lp2,
+                                const T *__restrict__ za, const T *__restrict__ zb, int Q) {
+    T e = lp2;
     for (int q = 0; q < Q; ++q) {
-        const double d = x[q] - 0.5 * (za[q] + zb[q]);
+        const T d = x[q] - T(0.5) * (za[q] + zb[q]);
         e -= d * d * w2[q];
     }
-    return exp(e);
+    return dexp(e);
 }
 
 // LDS written by lanes of this wave is read by others of it: a wave's LDS operations
@@ -129,37 +163,54 @@ struct FwdTask {
 };
 __host__ __device__ inline int fwd_tiles(int nb, int A, int C, int cb, int rb) {
     const int na = nb - rb < A ? nb - rb : A, nc = nb - cb < C ? nb - cb : C;
-    int tiles = 0;
-    for (int a = 0; a < na; ++a) {
-        const int up = rb + a - cb + 1;  // column blocks at or above the diagonal
-        tiles += up < nc ? up : nc;
+    return na * nc - (rb == cb && nc == 2 ? 1 : 0);   // C <= 2: one tile lies below the diagonal
+}
+// From the host: the row chunks of a task by its tiles (at most A C <= 8), and for each
+// column group its first wave and its first task.
+constexpr int kFwdGroups = GPPS_MAX_M / 16;
+struct FwdTable {
+    unsigned n[9];
+    unsigned short wave0[kFwdGroups], task0[kFwdGroups];
+};
+// The last of `groups` (ascending) entries that is no more than x: every lane compares
+// some of them (a search step by step took 20 us of a workgroup's life at M = 2000).
+__device__ inline int last_group(const unsigned short *__restrict__ first, int groups, int x) {
+    int n = 0;
+    for (int i = 0; i < groups; i += 64) {
+        const int k = i + (threadIdx.x & 63);
+        n += __popcll(__ballot(k < groups && first[min(k, groups - 1)] <= x));
     }
-    return tiles;
+    return __builtin_amdgcn_readfirstlane(n - 1);
 }
-__host__ __device__ inline int fwd_chunks(int64_t N, int nb, int A, int C, int cb, int rb, int cmax) {
-    const int n = cmax * (fwd_tiles(nb, A, C, cb, rb) + 1) / (A * C + 1);
-    return n < 1 ? 1 : n > N ? (int)N : n;
+// Of a column group's K tasks all but the first and the last have the same tiles:
+// task k with its chunks and first wave.
+__device__ inline FwdTask group_task(int nb, int A, int C, const FwdTable &n, int group, int k, int K) {
+    const int cb = group * C, w0 = n.wave0[group];
+    const int c0 = n.n[fwd_tiles(nb, A, C, cb, cb)];
+    const int cm = K > 2 ? n.n[fwd_tiles(nb, A, C, cb, cb + A)] : 0;
+    const int rb = cb + k * A;
+    return FwdTask{cb, rb, w0 + (k == 0 ? 0 : c0 + (k - 1) * cm), (int)n.n[fwd_tiles(nb, A, C, cb, rb)]};
 }
-// The task that holds wave w, or the one numbered `task` (the other is negative).
-__device__ inline FwdTask fwd_task(int64_t N, int nb, int A, int C, int cmax, int w, int task) {
-    FwdTask t{0, 0, 0, 0};
-    for (t.cb = 0; t.cb < nb; t.cb += C)
-        for (t.rb = t.cb; t.rb < nb; t.rb += A) {
-            t.chunks = fwd_chunks(N, nb, A, C, t.cb, t.rb, cmax);
-            if (w >= 0 ? w < t.first + t.chunks : task-- == 0) return t;
-            t.first += t.chunks;
-        }
-    t.chunks = 0;
-    return t;
+// The task that holds wave w of `waves`.
+__device__ inline FwdTask fwd_task(int nb, int A, int C, const FwdTable &n, int w) {
+    const int group = last_group(n.wave0, (nb + C - 1) / C, w), cb = group * C;
+    const int K = (nb - cb + A - 1) / A;
+    const int r = w - n.wave0[group] - (int)n.n[fwd_tiles(nb, A, C, cb, cb)];
+    int k = 0;
+    if (r >= 0) k = K > 2 ? min(1 + r / (int)n.n[fwd_tiles(nb, A, C, cb, cb + A)], K - 1) : 1;
+    return group_task(nb, A, C, n, group, k, K);
 }
 
-template <int KS>
-__global__ __launch_bounds__(kFwdWaves * 64, 2) void psi2_fwd_kernel(
-    int64_t N, int M, int Q, int nb, int cmax, const double *__restrict__ mu,
-    const double *__restrict__ Z, const double *__restrict__ w2, const double *__restrict__ lp2,
-    double *__restrict__ partial) {
+template <typename T, int KS>
+__global__ __launch_bounds__(kFwdWaves * 64, 2) void tiles_fwd_kernel(
+    const int *__restrict__ gate, int64_t N, int M, int Q, int nb, int waves, FwdTable table, const T *__restrict__ mu,
+    const T *__restrict__ Z, const T *__restrict__ w2, const T *__restrict__ lp2,
+    T *__restrict__ partial) {
+    if (gate && gate[0] == 0) return;
+    using v4 = typename Mm<T>::v4;
+    constexpr T kLog2 = T(kLog2e), kLim = T(0.25) * slow_limit<T>();
     constexpr int QP = 4 * KS, kFwdA = fwd_a(KS), kFwdC = fwd_c(KS), kFwdRows = fwd_rows(KS);
-    __shared__ double t_mu[kFwdWaves][2][kFwdRows][QP], t_k[kFwdWaves][2][kFwdRows][QP],
+    __shared__ T t_mu[kFwdWaves][2][kFwdRows][QP], t_k[kFwdWaves][2][kFwdRows][QP],
         t_h[kFwdWaves][2][kFwdRows];
     const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -167,19 +218,19 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2) void psi2_fwd_kernel(
     auto &s_k = t_k[wv];
     auto &s_h = t_h[wv];
     const int w = blockIdx.x * kFwdWaves + wv;
-    const FwdTask task = fwd_task(N, nb, kFwdA, kFwdC, cmax, w, -1);
-    if (task.chunks == 0) return;
+    if (w >= waves) return;
+    const FwdTask task = fwd_task(nb, kFwdA, kFwdC, table, w);
     const int cb = task.cb, rb = task.rb, na = min(kFwdA, nb - rb);
     // blocks past the edge repeat the last inducing input (never stored)
-    double za[kFwdA][KS], zc[kFwdC][KS];
+    T za[kFwdA][KS], zc[kFwdC][KS];
 #pragma unroll
     for (int a = 0; a < kFwdA; ++a) {
         const int m = min((rb + a) * 16 + c16, M - 1);
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             const int q = 4 * s + g;
-            const double v = Z[(int64_t)m * Q + min(q, Q - 1)];
-            za[a][s] = q < Q ? v : 0.0;
+            const T v = Z[(int64_t)m * Q + min(q, Q - 1)];
+            za[a][s] = q < Q ? v : T(0);
         }
     }
 #pragma unroll
@@ -188,28 +239,28 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2) void psi2_fwd_kernel(
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             const int q = 4 * s + g;
-            const double v = Z[(int64_t)m * Q + min(q, Q - 1)];
-            zc[c][s] = q < Q ? v : 0.0;
+            const T v = Z[(int64_t)m * Q + min(q, Q - 1)];
+            zc[c][s] = q < Q ? v : T(0);
         }
     }
-    d4 acc[kFwdA][kFwdC];
+    v4 acc[kFwdA][kFwdC];
 #pragma unroll
     for (int a = 0; a < kFwdA; ++a)
 #pragma unroll
-        for (int c = 0; c < kFwdC; ++c) acc[a][c] = d4{0, 0, 0, 0};
+        for (int c = 0; c < kFwdC; ++c) acc[a][c] = zero4<T>();
     const int64_t r0 = N * (w - task.first) / task.chunks, r1 = N * (w - task.first + 1) / task.chunks;
     // partial[wave][tile][v][lane]
-    double *out = partial + (int64_t)w * (kFwdA * kFwdC * 256) + lane;
+    T *out = partial + (int64_t)w * (kFwdA * kFwdC * 256) + lane;
     auto stage = [&](int64_t base, int buf) {
         const int cnt = (int)min<int64_t>(kFwdRows, r1 - base);
         for (int i = lane; i < kFwdRows * QP; i += 64) {
             const int r = i / QP, q = i - r * QP;
             const int64_t n = base + min(r, cnt - 1);
-            const double m = mu[n * Q + min(q, Q - 1)], w = w2[n * Q + min(q, Q - 1)];
-            s_mu[buf][r][q] = q < Q ? m : 0.0;
-            s_k[buf][r][q] = q < Q ? -0.5 * kLog2e * w : 0.0;
+            const T m = mu[n * Q + min(q, Q - 1)], w = w2[n * Q + min(q, Q - 1)];
+            s_mu[buf][r][q] = q < Q ? m : T(0);
+            s_k[buf][r][q] = q < Q ? T(-0.5) * kLog2 * w : T(0);
         }
-        if (lane < kFwdRows) s_h[buf][lane] = 0.125 * kLog2e * lp2[base + min(lane, cnt - 1)];
+        if (lane < kFwdRows) s_h[buf][lane] = T(0.125) * kLog2 * lp2[base + min(lane, cnt - 1)];
     };
     int flushed = 0;
     if (r0 < r1) stage(r0, 0);
@@ -219,49 +270,49 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2) void psi2_fwd_kernel(
         wave_lds_fence();
         if (base + kFwdRows < r1) stage(base + kFwdRows, buf ^ 1);
         for (int r = 0; r < cnt; ++r) {
-            const double hl = s_h[buf][r];  // a quarter of lambda/2 lp2: one per lane group
-            double muq[KS], kq[KS];
+            const T hl = s_h[buf][r];  // a quarter of lambda/2 lp2: one per lane group
+            T muq[KS], kq[KS];
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
                 muq[s] = s_mu[buf][r][4 * s + g];
                 kq[s] = s_k[buf][r][4 * s + g];
             }
-            double x[kFwdC][KS], bc[kFwdC];
+            T x[kFwdC][KS], bc[kFwdC];
             bool ok = true;
 #pragma unroll
             for (int c = 0; c < kFwdC; ++c) {
-                double part = 0.0;
+                T part = 0;
 #pragma unroll
                 for (int s = 0; s < KS; ++s) {
-                    const double d = muq[s] - zc[c][s];
+                    const T d = muq[s] - zc[c][s];
                     x[c][s] = kq[s] * d;
                     part = fma(x[c][s], d, part);
                 }
-                part = fma(0.5, part, hl);
-                ok = ok && fabs(part) < 0.25 * kSlow;
+                part = fma(T(0.5), part, hl);
+                ok = ok && fabs(part) < kLim;
                 bc[c] = sum_groups(part);
             }
 #pragma unroll
             for (int a = 0; a < kFwdA; ++a) {
                 if (a >= na) break;  // uniform
                 __builtin_amdgcn_sched_barrier(0);
-                double da[KS], part = 0.0;
+                T da[KS], part = 0;
 #pragma unroll
                 for (int s = 0; s < KS; ++s) {
                     da[s] = muq[s] - za[a][s];
                     part = fma(kq[s] * da[s], da[s], part);
                 }
-                part = fma(0.5, part, hl);
-                if (__builtin_expect(__all(ok && fabs(part) < 0.25 * kSlow), 1)) {
-                    const d4 br = mfma16(part, 1.0, d4{0, 0, 0, 0});
+                part = fma(T(0.5), part, hl);
+                if (__builtin_expect(__all(ok && fabs(part) < kLim), 1)) {
+                    const v4 br = Mm<T>::mul(part, T(1), zero4<T>());
 #pragma unroll
                     for (int c = 0; c < kFwdC; ++c) {
                         if (cb + c > rb + a || cb + c >= nb) break;  // uniform: below the diagonal
-                        d4 e;
+                        v4 e;
 #pragma unroll
                         for (int v = 0; v < 4; ++v) e[v] = br[v] + bc[c];
 #pragma unroll
-                        for (int s = 0; s < KS; ++s) e = mfma16(da[s], x[c][s], e);
+                        for (int s = 0; s < KS; ++s) e = Mm<T>::mul(da[s], x[c][s], e);
 #pragma unroll
                         for (int v = 0; v < 4; ++v) acc[a][c][v] += exp2_fast(e[v]);
                     }
@@ -274,7 +325,7 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2) void psi2_fwd_kernel(
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
                             const int m = min((cb + c) * 16 + (l & 15), M - 1);
-                            const int mp = min((rb + a) * 16 + 4 * v + (l >> 4), M - 1);
+                            const int mp = min((rb + a) * 16 + Mm<T>::row(v, l >> 4), M - 1);
                             __builtin_amdgcn_sched_barrier(0);
                             acc[a][c][v] += direct_pair(mu + n * Q, w2 + n * Q, lp2[n],
                                                         Z + (int64_t)m * Q, Z + (int64_t)mp * Q, Q);
@@ -292,63 +343,90 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2) void psi2_fwd_kernel(
                 for (int c = 0; c < kFwdC; ++c)
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        double *o = out + ((a * kFwdC + c) * 4 + v) * 64;
+                        T *o = out + ((a * kFwdC + c) * 4 + v) * 64;
                         *o = flushed ? *o + acc[a][c][v] : acc[a][c][v];
-                        acc[a][c][v] = 0.0;
+                        acc[a][c][v] = 0;
                     }
             flushed = 1;
         }
     }
 }
 
-// Workgroups below tasks A C: Psi2[m, m'] = 2^C sum over chunks, in chunk order, one
-// tile of a task each, one thread per entry; both triangles and psi0.  The
-// workgroups past them compute Psi1.
-__global__ __launch_bounds__(256) void psi2_fwd_reduce_kernel(
-    int64_t N, int M, int Q, int nb, int A, int CB, int cmax, int tasks,
-    const double *__restrict__ partial, const double *__restrict__ Z, Hyp<double> h,
-    double *__restrict__ psi0, double *__restrict__ Psi2, int accumulate,
-    const double *__restrict__ mu, const double *__restrict__ w1, const double *__restrict__ lp1,
-    double *__restrict__ Psi1) {
-    __shared__ Psi1Lds<double> s_p1;
-    const unsigned rblocks = tasks * A * CB;
+// Workgroups of the reduce of `tasks` tasks: G to a tile, tiles in whole eights.
+__host__ __device__ inline unsigned reduce_blocks(int tasks, int A, int C, int G) {
+    return (unsigned)((tasks * A * C + 7) / 8 * 8 * G);
+}
+// Workgroups below those: Psi2[m, m'] = 2^C sum over chunks, both triangles and
+// psi0.  256 / G entries of a task's tile each: thread group g of G takes chunks g,
+// g + G, ... in order and the G sums are added in order.  G = 4 where a task has more than
+// 16 chunks and 16 where it has more than 256: one thread per entry took 60 us for the
+// 1,666 chunks of N = 30,000, M = 10, and 16 groups, whose reads are 64-byte pieces,
+// 51 us instead of 20 for the 36 chunks of N = 300, M = 520.  The workgroups past them compute Psi1.
+template <typename T>
+__global__ __launch_bounds__(256) void tiles_reduce_kernel(
+    const int *__restrict__ gate, int64_t N, int M, int Q, int nb, int A, int CB, FwdTable table,
+    int tasks, int G, const T *__restrict__ partial, const T *__restrict__ Z, Hyp<T> h, T *__restrict__ psi0,
+    T *__restrict__ Psi2, int accumulate, const T *__restrict__ mu, const T *__restrict__ w1,
+    const T *__restrict__ lp1, T *__restrict__ Psi1) {
+    if (gate && gate[0] == 0) return;
+    __shared__ Psi1Lds<T> s_p1;
+    __shared__ T s_sum[256];
+    const unsigned rblocks = reduce_blocks(tasks, A, CB, G);
     if (blockIdx.x >= rblocks) {
-        psi1_blocks<double>(s_p1, blockIdx.x - rblocks, gridDim.x - rblocks, N, M, Q, mu, Z, w1, lp1, Psi1,
-                            [](double x) { return exp(x); });
+        psi1_blocks<T>(s_p1, blockIdx.x - rblocks, gridDim.x - rblocks, N, M, Q, mu, Z, w1, lp1, Psi1,
+                       [](T x) { return dexp(x); });
         return;
     }
-    const int tile = blockIdx.x % (A * CB);
     if (blockIdx.x == 0 && threadIdx.x == 0)
-        psi0[0] = (accumulate ? psi0[0] : 0.0) + (double)N * h.sf2;
-    const FwdTask task = fwd_task(N, nb, A, CB, cmax, -1, blockIdx.x / (A * CB));
+        psi0[0] = (accumulate ? psi0[0] : T(0)) + (T)N * h.sf2;
+    // the parts of a tile lie eight workgroups apart: they share cache lines of Psi2 (and
+    // consecutive workgroups go to different XCDs)
+    const int E = 256 / G, part = blockIdx.x / 8 % G, job = blockIdx.x / (8 * G) * 8 + blockIdx.x % 8;
+    const int tile = job % (A * CB), number = job / (A * CB);
+    if (number >= tasks) return;
+    const int group = last_group(table.task0, (nb + CB - 1) / CB, number);
+    const FwdTask task = group_task(nb, A, CB, table, group, number - table.task0[group],
+                                    (nb - group * CB + A - 1) / A);
     const int cb = task.cb + tile % CB, rb = task.rb + tile / CB, chunks = task.chunks;
     if (cb >= nb || rb >= nb || cb > rb) return;
-    const int lane = threadIdx.x & 63, v = threadIdx.x >> 6;
-    const int m = cb * 16 + (lane & 15), mp = rb * 16 + 4 * v + (lane >> 4);
-    if (m >= M || mp >= M || m > mp) return;
+    const int g = threadIdx.x / E, entry = part * E + threadIdx.x % E;
     const int64_t stride = A * CB * 256;
-    const double *src = partial + task.first * stride + tile * 256 + threadIdx.x;
-    double s = 0.0;
-    int k = 0;
-    for (; k + 8 <= chunks; k += 8) {
-        double t[8];
+    const T *src = partial + task.first * stride + tile * 256 + entry;
+    // eight loads in flight together, from clamped addresses past the last chunk
+    T s = 0;
+    for (int k = g; k < chunks; k += 8 * G) {
+        T t[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) t[j] = src[(k + j) * stride];
+        for (int j = 0; j < 8; ++j) t[j] = src[min(k + j * G, chunks - 1) * stride];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) s += t[j];
+        for (int j = 0; j < 8; ++j) s += k + j * G < chunks ? t[j] : T(0);
     }
-    for (; k < chunks; ++k) s += src[k * stride];
-    double C = 0.0;
+    if (G > 1) {
+        s_sum[threadIdx.x] = s;
+        __syncthreads();
+        if (g != 0) return;
+        s = 0;
+        for (int j = 0; j < G; ++j) s += s_sum[j * E + threadIdx.x];
+    }
+    const int lane = entry & 63, v = entry >> 6;
+    const int m = cb * 16 + (lane & 15), mp = rb * 16 + Mm<T>::row(v, lane >> 4);
+    if (m >= M || mp >= M || m > mp) return;
+    T C = 0;
+#pragma unroll 8
     for (int q = 0; q < Q; ++q) {
-        const double dz = Z[(int64_t)m * Q + q] - Z[(int64_t)mp * Q + q];
-        C -= dz * dz / (4.0 * h.l2[q]);
+        const T dz = Z[(int64_t)m * Q + q] - Z[(int64_t)mp * Q + q];
+        C -= dz * dz / (T(4) * h.l2[q]);
     }
-    const double val = (accumulate ? Psi2[(int64_t)m * M + mp] : 0.0) + exp(C) * s;
+    const T val = (accumulate ? Psi2[(int64_t)m * M + mp] : T(0)) + dexp(C) * s;
     Psi2[(int64_t)m * M + mp] = val;
     Psi2[(int64_t)mp * M + m] = val;
 }
 
 // ---------------------------------------------------------------- gradient
+template <int CTRL>
+__device__ inline float rotate16(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
 template <int CTRL>
 __device__ inline double rotate16(double x) {
     const long long b = __double_as_longlong(x);
@@ -358,12 +436,14 @@ __device__ inline double rotate16(double x) {
 }
 // Sums within the 16 lanes of a lane group: over the lanes of equal lane & 3, and
 // over all of them; in every lane.
-__device__ inline double sum_fours(double v) {
+template <typename T>
+__device__ inline T sum_fours(T v) {
     v += rotate16<0x128>(v);  // row_ror:8
     v += rotate16<0x124>(v);
     return v;
 }
-__device__ inline double sum16(double v) {
+template <typename T>
+__device__ inline T sum16(T v) {
     v = sum_fours(v);
     v += rotate16<0x122>(v);
     v += rotate16<0x121>(v);
@@ -372,8 +452,8 @@ __device__ inline double sum16(double v) {
 
 // Rows n a wave works on at once: as many as keep x, V and the row values of
 // 2 R (row, column block) pairs within 256 registers.
-template <int KS>
-constexpr int grad_rows() { return KS <= 5 ? 2 : 1; }
+// (fp32 would hold four up to Q = 16: 5% faster at M >= 700, 5-70% slower below).
+constexpr int grad_rows(int ks, size_t elem) { return ks <= (elem == 8 ? 5 : 12) ? 2 : 1; }
 
 struct GradGeo {
     int nw;          // waves per workgroup (each two column blocks)
@@ -396,49 +476,54 @@ constexpr int kGradC = 2;      // column blocks per wave
 // column of ones would cost 64 cycles.  Sums over m (dmu, dS, dl) go through the
 // lanes and then the waves in a fixed order; dZ stays in LDS slots that one lane
 // owns.
-template <int KS>
-__global__ __launch_bounds__(512) void psi2_grad_kernel(
-    int64_t N, int M, int Q, int nb, int wrows, int nwin, int64_t rows_per_chunk,
-    const double *__restrict__ mu, const double *__restrict__ S, const double *__restrict__ Z,
-    const double *__restrict__ w1t, const double *__restrict__ w2t, const double *__restrict__ lp1,
-    const double *__restrict__ lp2, Hyp<double> h, const double *__restrict__ G1,
-    const double *__restrict__ Gc, double *__restrict__ dmu, double *__restrict__ dS,
-    double *__restrict__ colpart, double *__restrict__ rowpart) {
-    constexpr int QP = 4 * KS, ZS = QP + 1, R = grad_rows<KS>(), T16 = KS / 4, T4 = KS % 4;
-    constexpr int NT = T16 + T4;
-    extern __shared__ double sm[];
+template <typename T, int KS>
+__global__ __launch_bounds__(512) void tiles_grad_kernel(
+    const int *__restrict__ gate, int64_t N, int M, int Q, int nb, int wrows, int nwin, int64_t rows_per_chunk,
+    const T *__restrict__ mu, const T *__restrict__ S, const T *__restrict__ Z,
+    const T *__restrict__ w1t, const T *__restrict__ w2t, const T *__restrict__ lp1,
+    const T *__restrict__ lp2, Hyp<T> h, const T *__restrict__ G1,
+    const T *__restrict__ Gc, T *__restrict__ dmu, T *__restrict__ dS,
+    T *__restrict__ colpart, T *__restrict__ rowpart) {
+    if (gate && gate[0] == 0) return;
+    using v4 = typename Mm<T>::v4;
+    constexpr T kLog2 = T(kLog2e), kLim = slow_limit<T>();
+    // T16 tiles of 16 dimensions and T4 of 4 hold V; QP: that width (zero past Q)
+    constexpr int T16 = Mm<T>::kFours ? KS / 4 : (KS + 3) / 4, T4 = Mm<T>::kFours ? KS % 4 : 0;
+    constexpr int NT = T16 + T4, QP = 16 * T16 + 4 * T4, QK = 4 * KS, ZS = QP + 1, R = grad_rows(KS, sizeof(T));
+    extern __shared__ double sm_[];
+    T *sm = reinterpret_cast<T *>(sm_);
     const int tid = threadIdx.x, nthr = blockDim.x, nw = nthr >> 6;
     const int lane = tid & 63, g = lane >> 4, c16 = lane & 15;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wcols = nw * kGradC * 16;
-    double *sz = sm;                          // [wrows][ZS]
-    double *sb = sz + wrows * ZS;             // [R][wrows]: b of the rows, permuted in each block
-    double *sbc = sb + R * wrows;             // [R][wcols]: b of the workgroup's columns
-    double *srow = sbc + R * wcols;           // [R][4][QP]: mu, w1, w2, S
-    double *slp = srow + R * 4 * QP;          // [R][2]: lp1, lp2
-    double *sred = slp + R * 2;               // [nw][R][3 QP + 2]
-    double *sdl = sred + nw * R * (3 * QP + 2);  // [R][QP + 1]
-    double *shyp = sdl + R * (QP + 1);        // [3][QP]: 1/l^2, l, 1/l^3
-    double *sgz = shyp + 3 * QP;              // [wcols][QP]
+    T *sz = sm;                          // [wrows][ZS]
+    T *sb = sz + wrows * ZS;             // [R][wrows]: b of the rows, permuted in each block
+    T *sbc = sb + R * wrows;             // [R][wcols]: b of the workgroup's columns
+    T *srow = sbc + R * wcols;           // [R][4][QP]: mu, w1, w2, S
+    T *slp = srow + R * 4 * QP;          // [R][2]: lp1, lp2
+    T *sred = slp + R * 2;               // [nw][R][3 QP + 2]
+    T *sdl = sred + nw * R * (3 * QP + 2);  // [R][QP + 1]
+    T *shyp = sdl + R * (QP + 1);        // [3][QP]: 1/l^2, l, 1/l^3
+    T *sgz = shyp + 3 * QP;              // [wcols][QP]
     int *sslow = reinterpret_cast<int *>(sgz + wcols * QP);  // [2][R]
     const int Mp = nb * 16;
     const int cb0 = (blockIdx.x * nw + wv) * kGradC;       // the wave's first column block
     const int ncol = min(kGradC, nb - cb0);                // its column blocks (<= 0: none)
     const int m0 = blockIdx.x * wcols;                     // the workgroup's first column
     for (int q = tid; q < QP; q += nthr) {
-        const double l = q < Q ? h.l[q] : 1.0, l2 = q < Q ? h.l2[q] : 1.0;
-        shyp[q] = 1.0 / l2;
+        const T l = q < Q ? h.l[q] : T(1.0), l2 = q < Q ? h.l2[q] : T(1.0);
+        shyp[q] = T(1.0) / l2;
         shyp[QP + q] = l;
-        shyp[2 * QP + q] = 1.0 / (l2 * l);
+        shyp[2 * QP + q] = T(1.0) / (l2 * l);
     }
-    for (int i = tid; i < R * (QP + 1); i += nthr) sdl[i] = 0.0;
-    for (int i = tid; i < wcols * QP; i += nthr) sgz[i] = 0.0;
+    for (int i = tid; i < R * (QP + 1); i += nthr) sdl[i] = T(0.0);
+    for (int i = tid; i < wcols * QP; i += nthr) sgz[i] = T(0.0);
     // rows of Z past M repeat the last one: finite wherever the real ones are
     auto stage_z = [&](int w0) {
         for (int i = tid; i < wrows * QP; i += nthr) {
             const int r = i / QP, q = i - r * QP;
-            const double v = Z[(int64_t)min(w0 + r, M - 1) * Q + min(q, Q - 1)];
-            sz[r * ZS + q] = q < Q ? v : 0.0;
+            const T v = Z[(int64_t)min(w0 + r, M - 1) * Q + min(q, Q - 1)];
+            sz[r * ZS + q] = q < Q ? v : T(0.0);
         }
     };
     if (nwin == 1) stage_z(0);
@@ -446,16 +531,15 @@ __global__ __launch_bounds__(512) void psi2_grad_kernel(
     auto zcol = [&](int m, int q) {
         return nwin == 1 ? sz[m * ZS + q] : Z[(int64_t)m * Q + min(q, Q - 1)];
     };
-    // this lane's Psi1 term: row lane >> 5 (R = 2) of its columns lane & 31
     const int64_t r0 = (int64_t)blockIdx.y * rows_per_chunk, r1 = min(N, r0 + rows_per_chunk);
     for (int64_t base = r0; base < r1; base += R) {
         const int cnt = (int)min<int64_t>(R, r1 - base);
         __syncthreads();
         for (int i = tid; i < R * 4 * QP; i += nthr) {
             const int r = i / (4 * QP), k = (i / QP) & 3, q = i % QP;
-            const double *src = k == 0 ? mu : k == 1 ? w1t : k == 2 ? w2t : S;
-            const double v = src[(base + min(r, cnt - 1)) * Q + min(q, Q - 1)];
-            srow[i] = q < Q ? v : 0.0;
+            const T *src = k == 0 ? mu : k == 1 ? w1t : k == 2 ? w2t : S;
+            const T v = src[(base + min(r, cnt - 1)) * Q + min(q, Q - 1)];
+            srow[i] = q < Q ? v : T(0.0);
         }
         if (tid < R) {
             slp[2 * tid] = lp1[base + min(tid, cnt - 1)];
@@ -464,64 +548,67 @@ __global__ __launch_bounds__(512) void psi2_grad_kernel(
         if (tid < 2 * R) sslow[tid] = 0;
         __syncthreads();
         // b of row r and inducing input m
-        auto b_of = [&](int r, const double *z) {
-            const double *xr = srow + r * 4 * QP, *w = xr + 2 * QP;
-            double s = 0.0;
+        auto b_of = [&](int r, const T *z) {
+            const T *xr = srow + r * 4 * QP, *w = xr + 2 * QP;
+            T s = T(0.0);
 #pragma unroll 4
-            for (int q = 0; q < QP; ++q) {
-                const double d = xr[q] - z[min(q, Q - 1)];
+            for (int q = 0; q < QK; ++q) {
+                const T d = xr[q] - z[min(q, Q - 1)];
                 s = fma(w[q] * d, d, s);
             }
-            return kLog2e * (0.5 * slp[2 * r + 1] - 0.25 * s);
+            return kLog2 * (T(0.5) * slp[2 * r + 1] - T(0.25) * s);
         };
-        // place of row j in sb: row 4 v + g of a block at 4 g + v, so that a lane's four
+        // place of row j in sb: row(v, g) of a block at 4 g + v, so that a lane's four
         // are contiguous
-        auto b_at = [](int j) { return (j & ~15) + 4 * (j & 3) + ((j >> 2) & 3); };
+        auto b_at = [](int j) {
+            return Mm<T>::row(1, 0) == 4 ? (j & ~15) + 4 * (j & 3) + ((j >> 2) & 3) : j;
+        };
         if (nwin > 1)  // else the columns are among the rows of the one window
             for (int i = tid; i < R * wcols; i += nthr) {
                 const int r = i / wcols;
-                const double s = b_of(r, Z + (int64_t)min(m0 + i - r * wcols, M - 1) * Q);
+                const T s = b_of(r, Z + (int64_t)min(m0 + i - r * wcols, M - 1) * Q);
                 sbc[i] = s;
-                if (!(fabs(s) < kSlow)) sslow[r] = 1;
+                if (!(fabs(s) < kLim)) sslow[r] = 1;
             }
-        double x[R][kGradC][KS], rs[R][kGradC];
-        d4 V16[R][kGradC][T16 > 0 ? T16 : 1];
-        double V4[R][kGradC][T4 > 0 ? T4 : 1];
-        double tval = 0.0;
-        // the Psi1 terms t = dL/dPsi1 o Psi1 of (row, column) = this lane's
-        if (G1) {
-            const int r = R == 2 ? lane >> 5 : 0, cc = lane & 31;
-            const int m = cb0 * 16 + cc;
-            if (r < cnt && m < M && (R == 2 || lane < 32)) {
-                const double *xr = srow + r * 4 * QP, *w = xr + QP;
-                double s = 0.0;
+        T x[R][kGradC][KS], rs[R][kGradC];
+        v4 V16[R][kGradC][T16 > 0 ? T16 : 1];
+        T V4[R][kGradC][T4 > 0 ? T4 : 1];
+        // the Psi1 terms t = dL/dPsi1 o Psi1: lane l has rows 2 u + l / 32, column l % 32
+        T tval[(R + 1) / 2];
+#pragma unroll
+        for (int u = 0; u < (R + 1) / 2; ++u) {
+            tval[u] = 0;
+            const int r = 2 * u + (lane >> 5), m = cb0 * 16 + (lane & 31);
+            if (G1 && r < cnt && m < M) {
+                const T *xr = srow + r * 4 * QP, *w = xr + QP;
+                T s = 0;
 #pragma unroll 4
-                for (int q = 0; q < QP; ++q) {
-                    const double d = xr[q] - zcol(m, q);
+                for (int q = 0; q < QK; ++q) {
+                    const T d = xr[q] - zcol(m, q);
                     s = fma(w[q] * d, d, s);
                 }
-                tval = G1[(base + r) * M + m] * exp(slp[2 * r] - 0.5 * s);
+                tval[u] = G1[(base + r) * M + m] * dexp(slp[2 * r] - T(0.5) * s);
             }
         }
 #pragma unroll
         for (int r = 0; r < R; ++r)
 #pragma unroll
             for (int c = 0; c < kGradC; ++c) {
-                rs[r][c] = 0.0;
+                rs[r][c] = T(0.0);
                 const int m = min((cb0 + c) * 16 + c16, M - 1);
 #pragma unroll
                 for (int s = 0; s < KS; ++s) {
                     const int q = 4 * s + g;
-                    const double d = srow[r * 4 * QP + q] - zcol(m, q);
-                    x[r][c][s] = -0.5 * kLog2e * srow[r * 4 * QP + 2 * QP + q] * d;
+                    const T d = srow[r * 4 * QP + q] - zcol(m, q);
+                    x[r][c][s] = -T(0.5) * kLog2 * srow[r * 4 * QP + 2 * QP + q] * d;
                 }
 #pragma unroll
-                for (int t = 0; t < T16; ++t) V16[r][c][t] = d4{0, 0, 0, 0};
+                for (int t = 0; t < T16; ++t) V16[r][c][t] = zero4<T>();
 #pragma unroll
-                for (int t = 0; t < T4; ++t) V4[r][c][t] = 0.0;
+                for (int t = 0; t < T4; ++t) V4[r][c][t] = T(0.0);
             }
         if (Gc) {
-            double bi[R][kGradC];
+            T bi[R][kGradC];
             for (int win = 0; win < nwin; ++win) {
                 const int w0 = win * wrows;
                 if (nwin > 1) {
@@ -532,16 +619,16 @@ __global__ __launch_bounds__(512) void psi2_grad_kernel(
                 }
                 for (int i = tid; i < R * wrows; i += nthr) {
                     const int r = i / wrows, j = i - r * wrows;
-                    const double *xr = srow + r * 4 * QP, *w = xr + 2 * QP, *z = sz + j * ZS;
-                    double s = 0.0;
+                    const T *xr = srow + r * 4 * QP, *w = xr + 2 * QP, *z = sz + j * ZS;
+                    T s = T(0.0);
 #pragma unroll 4
-                    for (int q = 0; q < QP; ++q) {
-                        const double d = xr[q] - z[q];
+                    for (int q = 0; q < QK; ++q) {
+                        const T d = xr[q] - z[q];
                         s = fma(w[q] * d, d, s);
                     }
-                    s = kLog2e * (0.5 * slp[2 * r + 1] - 0.25 * s);
+                    s = kLog2 * (T(0.5) * slp[2 * r + 1] - T(0.25) * s);
                     sb[r * wrows + b_at(j)] = s;
-                    if (!(fabs(s) < kSlow)) sslow[R + r] = 1;
+                    if (!(fabs(s) < kLim)) sslow[R + r] = 1;
                 }
                 __syncthreads();
                 if (win == 0) {
@@ -557,7 +644,7 @@ __global__ __launch_bounds__(512) void psi2_grad_kernel(
 #pragma unroll
                 for (int r = 0; r < R; ++r)
                     slow[r] = __builtin_amdgcn_readfirstlane(sslow[r] | sslow[R + r]) != 0;
-                double muA[R][KS], muB[R][NT];
+                T muA[R][KS], muB[R][NT];
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
 #pragma unroll
@@ -572,25 +659,25 @@ __global__ __launch_bounds__(512) void psi2_grad_kernel(
                 auto tiles = [&](auto ncc) {
                     constexpr int NC = decltype(ncc)::value;
                     for (int J = 0; J < jn; ++J) {
-                        double G[NC][4];
+                        T G[NC][4];
 #pragma unroll
                         for (int c = 0; c < NC; ++c)
 #pragma unroll
                             for (int v = 0; v < 4; ++v)
-                                G[c][v] = Gc[(int64_t)(w0 + 16 * J + 4 * v + g) * Mp + (cb0 + c) * 16 + c16];
-                        double zA[KS];
+                                G[c][v] = Gc[(int64_t)(w0 + 16 * J + Mm<T>::row(v, g)) * Mp + (cb0 + c) * 16 + c16];
+                        T zA[KS];
 #pragma unroll
                         for (int s = 0; s < KS; ++s) zA[s] = sz[(16 * J + c16) * ZS + 4 * s + g];
 #pragma unroll
                         for (int r = 0; r < R; ++r) {
                             __builtin_amdgcn_sched_barrier(0);
-                            double W[NC][4];
+                            T W[NC][4];
                             if (__builtin_expect(!slow[r], 1)) {
-                                double dA[KS];
-                                d4 e[NC];
+                                T dA[KS];
+                                v4 e[NC];
 #pragma unroll
                                 for (int v = 0; v < 4; ++v) {
-                                    const double b = sb[r * wrows + 16 * J + 4 * g + v];
+                                    const T b = sb[r * wrows + 16 * J + 4 * g + v];
 #pragma unroll
                                     for (int c = 0; c < NC; ++c) e[c][v] = b + bi[r][c];
                                 }
@@ -599,7 +686,7 @@ __global__ __launch_bounds__(512) void psi2_grad_kernel(
 #pragma unroll
                                 for (int s = 0; s < KS; ++s)
 #pragma unroll
-                                    for (int c = 0; c < NC; ++c) e[c] = mfma16(dA[s], x[r][c][s], e[c]);
+                                    for (int c = 0; c < NC; ++c) e[c] = Mm<T>::mul(dA[s], x[r][c][s], e[c]);
 #pragma unroll
                                 for (int c = 0; c < NC; ++c)
 #pragma unroll
@@ -612,9 +699,9 @@ __global__ __launch_bounds__(512) void psi2_grad_kernel(
 #pragma unroll
                                     for (int v = 0; v < 4; ++v) {
                                         const int m = (cb0 + c) * 16 + (l & 15);
-                                        const int mp = w0 + 16 * J + 4 * v + (l >> 4);
+                                        const int mp = w0 + 16 * J + Mm<T>::row(v, l >> 4);
                                         __builtin_amdgcn_sched_barrier(0);
-                                        W[c][v] = 0.0;
+                                        W[c][v] = T(0.0);
                                         if (m < M && mp < M)
                                             W[c][v] = G[c][v] *
                                                       direct_pair(srow + r * 4 * QP,
@@ -629,21 +716,20 @@ __global__ __launch_bounds__(512) void psi2_grad_kernel(
                                 rs[r][c] += (W[c][0] + W[c][1]) + (W[c][2] + W[c][3]);
 #pragma unroll
                             for (int v = 0; v < 4; ++v) {
-                                double dB[NT];
+                                T dB[NT];
 #pragma unroll
                                 for (int t = 0; t < NT; ++t)
                                     dB[t] = muB[r][t] -
-                                            sz[(16 * J + 4 * v + g) * ZS +
+                                            sz[(16 * J + Mm<T>::row(v, g)) * ZS +
                                                (t < T16 ? 16 * t + c16 : 16 * T16 + 4 * (t - T16) + (lane & 3))];
 #pragma unroll
                                 for (int c = 0; c < NC; ++c) {
 #pragma unroll
                                     for (int t = 0; t < T16; ++t)
-                                        V16[r][c][t] = mfma16(W[c][v], dB[t], V16[r][c][t]);
+                                        V16[r][c][t] = Mm<T>::mul(W[c][v], dB[t], V16[r][c][t]);
 #pragma unroll
                                     for (int t = 0; t < T4; ++t)
-                                        V4[r][c][t] = __builtin_amdgcn_mfma_f64_4x4x4f64(
-                                            W[c][v], dB[T16 + t], V4[r][c][t], 0, 0, 0);
+                                        V4[r][c][t] = Mm<T>::fours(W[c][v], dB[T16 + t], V4[r][c][t]);
                                 }
                             }
                         }
@@ -664,18 +750,18 @@ __global__ __launch_bounds__(512) void psi2_grad_kernel(
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 if (r >= cnt) break;  // uniform
-                double *red = sred + (wv * R + r) * (3 * QP + 2);
-                double tc[kGradC];
-                d4 r16[kGradC];
-                double r4[kGradC], rt = 0.0, tt = 0.0;
+                T *red = sred + (wv * R + r) * (3 * QP + 2);
+                T tc[kGradC];
+                v4 r16[kGradC];
+                T r4[kGradC], rt = T(0.0), tt = T(0.0);
 #pragma unroll
                 for (int c = 0; c < kGradC; ++c) {
-                    if (c >= ncol) rs[r][c] = 0.0;
-                    tc[c] = __shfl(tval, 32 * r + 16 * c + ce);
+                    if (c >= ncol) rs[r][c] = T(0.0);
+                    tc[c] = __shfl(tval[r / 2], 32 * (r & 1) + 16 * c + ce);
                     rt += rs[r][c];
                     tt += tc[c];
-                    if (T16 > 0) r16[c] = mfma16(rs[r][c], 1.0, d4{0, 0, 0, 0});
-                    if (T4 > 0) r4[c] = __builtin_amdgcn_mfma_f64_4x4x4f64(rs[r][c], 1.0, 0.0, 0, 0, 0);
+                    if (T16 > 0) r16[c] = Mm<T>::mul(rs[r][c], T(1.0), zero4<T>());
+                    if (T4 > 0) r4[c] = Mm<T>::fours(rs[r][c], T(1), T(0));
                 }
                 rt = sum16(sum_groups(rt));
                 tt = sum16(tt);
@@ -687,35 +773,35 @@ __global__ __launch_bounds__(512) void psi2_grad_kernel(
                 for (int t = 0; t < NT; ++t) {
                     const bool wide = t < T16;
                     const int q = wide ? 16 * t + ce : 16 * T16 + 4 * (t - T16) + (le & 3);
-                    const double *row = srow + r * 4 * QP + q;
-                    const double xm = row[0], a1 = row[QP], a2 = row[2 * QP];
-                    const double il2 = shyp[q], l = shyp[QP + q], il3 = shyp[2 * QP + q];
-                    double sp0 = 0.0, st0 = 0.0, su = 0.0, sn = 0.0, sx = 0.0;
+                    const T *row = srow + r * 4 * QP + q;
+                    const T xm = row[0], a1 = row[QP], a2 = row[2 * QP];
+                    const T il2 = shyp[q], l = shyp[QP + q], il3 = shyp[2 * QP + q];
+                    T sp0 = T(0.0), st0 = T(0.0), su = T(0.0), sn = T(0.0), sx = T(0.0);
 #pragma unroll
                     for (int c = 0; c < kGradC; ++c) {
                         if (c >= ncol) break;  // uniform
 #pragma unroll
                         for (int v = 0; v < (wide ? 4 : 1); ++v) {
-                            const int ml = wide ? 4 * v + ge : (le & 12) + ge;
+                            const int ml = wide ? Mm<T>::row(v, ge) : (le & 12) + ge;
                             const int m = min((cb0 + c) * 16 + ml, M - 1);
-                            const double rm = wide ? r16[c][v] : r4[c];
-                            const double tm = __shfl(tval, 32 * r + 16 * c + ml);
-                            const double Vq = wide ? V16[r][c][wide ? t : 0][v] : V4[r][c][wide ? 0 : t - T16];
-                            const double d = xm - zcol(m, q), dr = d * rm, td = tm * d;
-                            const double p = dr + Vq, n = dr - Vq;
+                            const T rm = wide ? r16[c][v] : r4[c];
+                            const T tm = __shfl(tval[r / 2], 32 * (r & 1) + 16 * c + ml);
+                            const T Vq = wide ? V16[r][c][wide ? t : 0][v] : V4[r][c][wide ? 0 : t - T16];
+                            const T d = xm - zcol(m, q), dr = d * rm, td = tm * d;
+                            const T p = dr + Vq, n = dr - Vq;
                             sp0 += dr;
                             st0 += td;
                             su = fma(d, p, su);
                             sn = fma(d, n, sn);
                             sx = fma(d, td, sx);
-                            double *gz = sgz + ((wv * kGradC + c) * 16 + ml) * QP + q;
+                            T *gz = sgz + ((wv * kGradC + c) * 16 + ml) * QP + q;
                             *gz += fma(a2, p, fma(il2, n, a1 * td));
                         }
                     }
-                    const double u = a2 * a2 * su, y = a1 * a1 * sx;
-                    double v0 = sum_groups(-2.0 * a2 * sp0 - a1 * st0);
-                    double v1 = sum_groups(u + 0.5 * y);
-                    double v2 = sum_groups(fma(sn, il3, l * (u + y)));
+                    const T u = a2 * a2 * su, y = a1 * a1 * sx;
+                    T v0 = sum_groups(-T(2.0) * a2 * sp0 - a1 * st0);
+                    T v1 = sum_groups(u + T(0.5) * y);
+                    T v2 = sum_groups(fma(sn, il3, l * (u + y)));
                     if (!wide) {
                         v0 = sum_fours(v0);
                         v1 = sum_fours(v1);
@@ -734,22 +820,22 @@ __global__ __launch_bounds__(512) void psi2_grad_kernel(
         const int live = min(nw, (nb - (int)blockIdx.x * nw * kGradC + kGradC - 1) / kGradC);
         for (int i = tid; i < cnt * Q; i += nthr) {
             const int r = i / Q, q = i - r * Q;
-            double v0 = 0.0, v1 = 0.0, v2 = 0.0, Rt = 0.0, Tt = 0.0;
+            T v0 = T(0.0), v1 = T(0.0), v2 = T(0.0), Rt = T(0.0), Tt = T(0.0);
             for (int w = 0; w < live; ++w) {
-                const double *red = sred + (w * R + r) * (3 * QP + 2);
+                const T *red = sred + (w * R + r) * (3 * QP + 2);
                 v0 += red[q];
                 v1 += red[QP + q];
                 v2 += red[2 * QP + q];
                 Rt += red[3 * QP];
                 Tt += red[3 * QP + 1];
             }
-            const double *row = srow + r * 4 * QP + q;
-            const double a1 = row[QP], a2 = row[2 * QP], sv = row[3 * QP], il = 1.0 / shyp[QP + q];
+            const T *row = srow + r * 4 * QP + q;
+            const T a1 = row[QP], a2 = row[2 * QP], sv = row[3 * QP], il = T(1.0) / shyp[QP + q];
             const int64_t o = ((int64_t)blockIdx.x * 2 * N + base + r) * Q + q;
             dmu[o] = v0;
-            dS[o] = v1 - a2 * Rt - 0.5 * a1 * Tt;
-            sdl[r * (QP + 1) + q] += v2 + (2.0 * sv * a2 * il) * Rt + (sv * a1 * il) * Tt;
-            if (q == 0) sdl[r * (QP + 1) + QP] += 2.0 * Rt + Tt;
+            dS[o] = v1 - a2 * Rt - T(0.5) * a1 * Tt;
+            sdl[r * (QP + 1) + q] += v2 + (T(2.0) * sv * a2 * il) * Rt + (sv * a1 * il) * Tt;
+            if (q == 0) sdl[r * (QP + 1) + QP] += T(2.0) * Rt + Tt;
         }
     }
     __syncthreads();
@@ -758,7 +844,7 @@ __global__ __launch_bounds__(512) void psi2_grad_kernel(
         if (m0 + cc < M) colpart[((int64_t)blockIdx.y * M + m0 + cc) * Q + q] = sgz[cc * QP + q];
     }
     for (int q = tid; q <= Q; q += nthr) {
-        double s = 0.0;
+        T s = T(0.0);
         for (int r = 0; r < R; ++r) s += sdl[r * (QP + 1) + (q < Q ? q : QP)];
         rowpart[((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * (Q + 1) + q] =
             q < Q ? s : s / h.sf2;
@@ -772,23 +858,25 @@ int ks_of(int64_t Q) {
     return 16;
 }
 
-int rows_of(int ks) { return ks <= 5 ? 2 : 1; }
-
-size_t grad_lds(int ks, int nw, int wrows) {
-    const int QP = 4 * ks, R = rows_of(ks), wcols = nw * kGradC * 16;
+size_t grad_lds(int ks, int nw, int wrows, size_t elem) {
+    // as in the kernel: fp32 V comes in tiles of 16 dimensions only
+    const int QP = elem == 8 ? 4 * ks : (ks + 3) / 4 * 16, R = grad_rows(ks, elem), wcols = nw * kGradC * 16;
     const size_t d = (size_t)wrows * (QP + 1) + R * wrows + R * wcols + R * 4 * QP + R * 2 +
                      (size_t)nw * R * (3 * QP + 2) + R * (QP + 1) + 3 * QP + (size_t)wcols * QP;
-    return d * 8 + 2 * R * 4 + 8;
+    return align_up(d * elem, 8) + 2 * R * 4 + 8;
 }
 
 
-GradGeo grad_geo(const Shape &s) {
+GradGeo grad_geo(const Shape &s, size_t elem) {
     GradGeo g{};
-    const int ks = ks_of(s.Q), R = rows_of(ks);
+    const int ks = ks_of(s.Q), R = grad_rows(ks, elem);
     const int nb = (int)cdiv(s.M, 16), need = (int)cdiv(nb, kGradC);  // waves per row chunk
     // the waves per workgroup that keep the most of a CU's eight wave slots (two per
     // SIMD: the register limit) on column blocks that exist, in at most one group of
-    // columns per 128 (each writes dmu and dS of its own); the widest of equal ones
+    // columns per 128 (each writes dmu and dS of its own); the widest of equal ones.
+    // fp32 up to Q = 16 has three waves per SIMD: 11% faster at M <= 256, but 30% slower
+    // at M = 520 and 700, whose workgroups then hold fewer columns
+    const int slots = elem == 4 && ks <= 4 && s.M <= 256 ? 12 : 8;
     double best = 0.0;
     for (int nw = std::min(8, need); nw >= 1; --nw) {
         const int groups = (int)cdiv(need, nw);
@@ -798,11 +886,11 @@ GradGeo grad_geo(const Shape &s) {
         size_t lds;
         for (;; ++nwin) {
             wrows = (int)cdiv(nb, nwin) * 16;
-            lds = grad_lds(ks, nw, wrows);
+            lds = grad_lds(ks, nw, wrows, elem);
             if (lds <= kLdsMax || wrows == 16) break;
         }
         if (lds > kLdsMax) continue;
-        const int per_cu = (int)std::min<int64_t>((int64_t)(kLdsMax / lds), 8 / nw);
+        const int per_cu = (int)std::min<int64_t>((int64_t)(kLdsMax / lds), slots / nw);
         const double score = (double)nb / (kGradC * nw * groups) * (per_cu * nw) / (nwin > 1 ? 1.05 : 1.0);
         if (score > 1.02 * best) {
             best = score;
@@ -826,105 +914,136 @@ GradGeo grad_geo(const Shape &s) {
 
 struct FwdGeo {
     int nb, a, c, tasks, cmax, waves;
+    FwdTable table;
 };
 
-FwdGeo fwd_geo(const Shape &s, size_t budget) {
+FwdGeo fwd_geo(const Shape &s, size_t budget, size_t elem) {
     FwdGeo f{};
     const int ks = ks_of(s.Q);
     f.nb = (int)cdiv(s.M, 16);
     f.a = fwd_a(ks);
     f.c = fwd_c(ks);
     const int full = f.a * f.c + 1;
-    auto waves = [&](int cmax) {
-        int n = 0;
-        f.tasks = 0;
-        for (int cb = 0; cb < f.nb; cb += f.c)
-            for (int rb = cb; rb < f.nb; rb += f.a, ++f.tasks)
-                n += fwd_chunks(s.N, f.nb, f.a, f.c, cb, rb, cmax);
-        return n;
+    // over the tasks: of a column group all but the first and last have the same tiles
+    auto each = [&](auto fn) {
+        for (int cb = 0; cb < f.nb; cb += f.c) {
+            const int k = (f.nb - cb + f.a - 1) / f.a;
+            fn(cb, cb, 1);
+            if (k > 2) fn(cb, cb + f.a, k - 2);
+            if (k > 1) fn(cb, cb + (k - 1) * f.a, 1);
+        }
     };
-    // the chunks with which the grid fills one round of two waves per SIMD, with the
+    // the chunks with which the grid fills one round of two or three waves per SIMD, with the
     // partial sums within the region and at least kFwdMinRows rows in each
-    const int64_t room = (int64_t)(budget / ((size_t)f.a * f.c * 256 * 8));
-    const int64_t most = std::min<int64_t>(2 * kSimds, room);
+    const int64_t room = (int64_t)(budget / ((size_t)f.a * f.c * 256 * elem));
+    // waves per SIMD: by the register count, and the LDS of the staged rows
+    const int per_simd = elem == 4 && ks <= 6 ? 3 : 2;
+    const int64_t most = std::min<int64_t>(per_simd * kSimds, room);
+    // ceil(cmax (t + 1) / full) chunks for a task of t tiles, so that none takes longer than
+    // a full one (rounded down, the diagonal's seven-tile tasks took a third longer at M = 2000)
     int64_t work = 0;   // full times the waves of cmax = 1, without the roundings
-    for (int cb = 0; cb < f.nb; cb += f.c)
-        for (int rb = cb; rb < f.nb; rb += f.a)
-            work += fwd_tiles(f.nb, f.a, f.c, cb, rb) + 1;
-    const int64_t cmax = std::min(most * full / work, cdiv(s.N, kFwdMinRows));
-    f.cmax = (int)std::max<int64_t>(1, cmax);
-    f.waves = waves(f.cmax);
+    each([&](int cb, int rb, int n) {
+        work += (int64_t)n * (fwd_tiles(f.nb, f.a, f.c, cb, rb) + 1);
+        f.tasks += n;
+    });
+    int64_t cmax = std::max<int64_t>(1, std::min(most * full / work, cdiv(s.N, kFwdMinRows)));
+    for (;; --cmax) {
+        f.cmax = (int)cmax;
+        for (int t = 0; t <= 8; ++t) f.table.n[t] = (unsigned)std::min(s.N, cdiv(cmax * (t + 1), full));
+        f.waves = 0;
+        each([&](int cb, int rb, int n) {
+            f.waves += n * f.table.n[fwd_tiles(f.nb, f.a, f.c, cb, rb)];
+        });
+        if (f.waves <= most || cmax == 1) break;
+    }
     if (f.waves > room) f.cmax = 0;
+    int wave = 0, task = 0;
+    each([&](int cb, int rb, int n) {
+        if (rb == cb) {
+            f.table.wave0[cb / f.c] = (unsigned short)wave;
+            f.table.task0[cb / f.c] = (unsigned short)task;
+        }
+        wave += n * f.table.n[fwd_tiles(f.nb, f.a, f.c, cb, rb)];
+        task += n;
+    });
     return f;
 }
 
-double *dbl(void *p, size_t off) { return reinterpret_cast<double *>(static_cast<char *>(p) + off); }
+template <typename T>
+T *at(void *p, size_t off) { return reinterpret_cast<T *>(static_cast<char *>(p) + off); }
 
 }  // namespace
 
-bool f64_stats_wanted(const Shape &s) { return s.Q > 4 || (s.Q > 2 && s.M > 128); }
-bool f64_grads_wanted(const Shape &s) { return s.Q > 2 || (s.Q > 1 && s.M > 128); }
+bool tiles_stats_wanted(const Shape &s, size_t elem) {
+    return s.Q > 4 || (elem == 8 && s.Q > 2 && s.M > 128);
+}
+bool tiles_grads_wanted(const Shape &s, size_t) { return s.Q > 2 && (s.Q > 4 || s.M > 128); }
 
-size_t f64_region_bytes(const Shape &s) {
-    size_t b = 0;
-    if (f64_stats_wanted(s)) {
-        const FwdGeo f = fwd_geo(s, SIZE_MAX);
-        b = (size_t)f.waves * f.a * f.c * 256 * 8;
+TilesRegion tiles_region(const Shape &s, size_t elem) {
+    TilesRegion r{0, 0};
+    if (tiles_stats_wanted(s, elem)) {
+        const FwdGeo f = fwd_geo(s, SIZE_MAX, elem);
+        const size_t per = (size_t)f.a * f.c * 256 * elem;
+        r.least = f.tasks * per;
+        r.want = f.waves * per;
     }
-    if (f64_grads_wanted(s)) b = std::max(b, f64_grad_plan(s, SIZE_MAX).end);
-    return b;
+    if (tiles_grads_wanted(s, elem)) {
+        const TilesGradPlan g = tiles_grad_plan(s, SIZE_MAX, elem);
+        // of the chunks' slabs one is needed
+        r.want = std::max(r.want, g.end);
+        r.least = std::max(r.least, g.off_colp + align_up(elem * s.M * s.Q, 256) +
+                                        align_up(elem * g.groups * (s.Q + 1), 256) + 1024);
+    }
+    return r;
 }
 
-bool f64_stats_fit(const Shape &s, size_t budget) {
-    return f64_stats_wanted(s) && fwd_geo(s, budget).cmax >= 1;
-}
-
-hipError_t f64_psi2(const Shape &s, const double *mu, const double *Z, const double *w1,
-                    const double *w2, const double *lp1, const double *lp2, const Hyp<double> &h,
-                    double *psi0, double *Psi1, double *Psi2, int accumulate, void *ws, size_t budget,
-                    hipStream_t st) {
-    const FwdGeo f = fwd_geo(s, budget);
-    double *partial = static_cast<double *>(ws);
+template <typename T>
+hipError_t tiles_psi2(const Shape &s, const T *mu, const T *Z, const T *w1, const T *w2, const T *lp1,
+                      const T *lp2, const Hyp<T> &h, T *psi0, T *Psi1, T *Psi2, int accumulate, void *ws,
+                      size_t budget, const int *gate, hipStream_t st) {
+    const FwdGeo f = fwd_geo(s, budget, sizeof(T));
+    T *partial = static_cast<T *>(ws);
     const unsigned grid = (unsigned)cdiv(f.waves, kFwdWaves);
     {
-        TimedScope ts(st, "f64_psi2_fwd");
-#define GPPS_F64_FWD(KS)                                                                          \
+        TimedScope ts(st, "tiles_psi2_fwd");
+#define GPPS_TILES_FWD(KS)                                                                        \
     case KS:                                                                                      \
-        psi2_fwd_kernel<KS><<<grid, kFwdWaves * 64, 0, st>>>(s.N, (int)s.M, (int)s.Q, f.nb,        \
-                                                             f.cmax, mu, Z, w2, lp2, partial);     \
+        tiles_fwd_kernel<T, KS><<<grid, kFwdWaves * 64, 0, st>>>(                                 \
+            gate, s.N, (int)s.M, (int)s.Q, f.nb, f.waves, f.table, mu, Z, w2, lp2, partial);                \
         break
         switch (ks_of(s.Q)) {
-            GPPS_F64_FWD(1); GPPS_F64_FWD(2); GPPS_F64_FWD(3); GPPS_F64_FWD(4); GPPS_F64_FWD(5);
-            GPPS_F64_FWD(6); GPPS_F64_FWD(8); GPPS_F64_FWD(10); GPPS_F64_FWD(12); GPPS_F64_FWD(16);
+            GPPS_TILES_FWD(1); GPPS_TILES_FWD(2); GPPS_TILES_FWD(3); GPPS_TILES_FWD(4);
+            GPPS_TILES_FWD(5); GPPS_TILES_FWD(6); GPPS_TILES_FWD(8); GPPS_TILES_FWD(10);
+            GPPS_TILES_FWD(12); GPPS_TILES_FWD(16);
             default: return hipErrorInvalidValue;
         }
-#undef GPPS_F64_FWD
+#undef GPPS_TILES_FWD
     }
-    TimedScope ts(st, "f64_psi2_reduce_psi1");
-    psi2_fwd_reduce_kernel<<<(unsigned)(f.tasks * f.a * f.c + psi1_grid(s.N, s.M, Psi1, 4096)), 256, 0, st>>>(
-        s.N, (int)s.M, (int)s.Q, f.nb, f.a, f.c, f.cmax, f.tasks, partial, Z, h, psi0, Psi2, accumulate, mu,
-        w1, lp1, Psi1);
+    const int G = f.cmax > 256 ? 16 : f.cmax > 16 ? 4 : 1;
+    TimedScope ts(st, "tiles_psi2_reduce_psi1");
+    tiles_reduce_kernel<T><<<reduce_blocks(f.tasks, f.a, f.c, G) + psi1_grid(s.N, s.M, Psi1, gate ? 2048 : 4096),
+                             256, 0, st>>>(gate, s.N, (int)s.M, (int)s.Q, f.nb, f.a, f.c, f.table, f.tasks, G,
+                                           partial, Z, h, psi0, Psi2, accumulate, mu, w1, lp1, Psi1);
     return hipGetLastError();
 }
 
 // Region: Gc = (G2 + G2^T)/2 o 2^C [Mp x Mp], row gradients [groups][2][N][Q] (only when groups > 1),
 // dZ slabs [chunks][M][Q], row sums [chunks][groups][Q + 1].
-F64GradPlan f64_grad_plan(const Shape &s, size_t budget) {
-    F64GradPlan p{};
-    if (!f64_grads_wanted(s)) return p;
-    GradGeo g = grad_geo(s);
+TilesGradPlan tiles_grad_plan(const Shape &s, size_t budget, size_t elem) {
+    TilesGradPlan p{};
+    GradGeo g = grad_geo(s, elem);
     if (g.lds > kLdsMax) return p;
     const int64_t Mp = cdiv(s.M, 16) * 16;
     size_t o = 0;
-    auto take = [&](size_t n) { size_t r = o; o = align_up(o + n * 8, 256); return r; };
+    auto take = [&](size_t n) { size_t r = o; o = align_up(o + n * elem, 256); return r; };
     p.off_gc = take(Mp * Mp);
     p.off_rowg = take(g.groups > 1 ? (size_t)g.groups * 2 * s.N * s.Q : 0);
     // as many chunks as the region has room for
-    const size_t per = (size_t)(s.M * s.Q + g.groups * (s.Q + 1)) * 8;
+    const size_t per = (size_t)(s.M * s.Q + g.groups * (s.Q + 1)) * elem;
     const int64_t room = budget > o + 512 ? (int64_t)((budget - o - 512) / per) : 0;
     if (room < 1) return p;  // ok = false
     if (g.chunks > room) {
-        const int R = rows_of(ks_of(s.Q));
+        const int R = grad_rows(ks_of(s.Q), elem);
         g.rows = cdiv(cdiv(s.N, room), R) * R;
         g.chunks = cdiv(s.N, g.rows);
     }
@@ -942,34 +1061,48 @@ F64GradPlan f64_grad_plan(const Shape &s, size_t budget) {
     return p;
 }
 
-hipError_t f64_psi2_grads(const Shape &s, const F64GradPlan &p, const double *mu, const double *S,
-                          const double *Z, const double *w1, const double *w2, const double *lp1,
-                          const double *lp2, const Hyp<double> &h, const double *G1,
-                          const double *Gc, double *dmu, double *dS, void *ws, hipStream_t st) {
+template <typename T>
+hipError_t tiles_psi2_grads(const Shape &s, const TilesGradPlan &p, const T *mu, const T *S, const T *Z,
+                            const T *w1, const T *w2, const T *lp1, const T *lp2, const Hyp<T> &h,
+                            const T *G1, const T *Gc, T *dmu, T *dS, void *ws, const int *gate,
+                            hipStream_t st) {
     const int nb = (int)cdiv(s.M, 16);
     // one group of columns writes dmu and dS themselves
-    double *om = p.groups > 1 ? dbl(ws, p.off_rowg) : dmu;
-    double *os = p.groups > 1 ? om + s.N * s.Q : dS;
+    T *om = p.groups > 1 ? at<T>(ws, p.off_rowg) : dmu;
+    T *os = p.groups > 1 ? om + s.N * s.Q : dS;
     const dim3 grid((unsigned)p.groups, (unsigned)p.chunks);
-    TimedScope ts(st, "f64_psi2_grad");
-#define GPPS_F64_GRAD(KS)                                                                         \
+    TimedScope ts(st, "tiles_psi2_grad");
+#define GPPS_TILES_GRAD(KS)                                                                       \
     case KS: {                                                                                    \
-        const hipError_t e = hipFuncSetAttribute((const void *)psi2_grad_kernel<KS>,              \
+        const hipError_t e = hipFuncSetAttribute((const void *)tiles_grad_kernel<T, KS>,          \
                                                  hipFuncAttributeMaxDynamicSharedMemorySize,      \
                                                  (int)p.lds);                                     \
         if (e != hipSuccess) return e;                                                            \
-        psi2_grad_kernel<KS><<<grid, p.nw * 64, p.lds, st>>>(                                     \
-            s.N, (int)s.M, (int)s.Q, nb, p.wrows, p.nwin, p.rows, mu, S, Z, w1, w2, lp1, lp2, h,  \
-            G1, Gc, om, os, dbl(ws, p.off_colp), dbl(ws, p.off_rowp));                            \
+        tiles_grad_kernel<T, KS><<<grid, p.nw * 64, p.lds, st>>>(                                 \
+            gate, s.N, (int)s.M, (int)s.Q, nb, p.wrows, p.nwin, p.rows, mu, S, Z, w1, w2, lp1,    \
+            lp2, h, G1, Gc, om, os, at<T>(ws, p.off_colp), at<T>(ws, p.off_rowp));                \
         break;                                                                                    \
     }
     switch (ks_of(s.Q)) {
-        GPPS_F64_GRAD(1) GPPS_F64_GRAD(2) GPPS_F64_GRAD(3) GPPS_F64_GRAD(4) GPPS_F64_GRAD(5)
-        GPPS_F64_GRAD(6) GPPS_F64_GRAD(8) GPPS_F64_GRAD(10) GPPS_F64_GRAD(12) GPPS_F64_GRAD(16)
+        GPPS_TILES_GRAD(1) GPPS_TILES_GRAD(2) GPPS_TILES_GRAD(3) GPPS_TILES_GRAD(4)
+        GPPS_TILES_GRAD(5) GPPS_TILES_GRAD(6) GPPS_TILES_GRAD(8) GPPS_TILES_GRAD(10)
+        GPPS_TILES_GRAD(12) GPPS_TILES_GRAD(16)
         default: return hipErrorInvalidValue;
     }
-#undef GPPS_F64_GRAD
+#undef GPPS_TILES_GRAD
     return hipGetLastError();
 }
+
+#define GPPS_TILES_INST(T)                                                                        \
+    template hipError_t tiles_psi2<T>(const Shape &, const T *, const T *, const T *, const T *,  \
+                                      const T *, const T *, const Hyp<T> &, T *, T *, T *, int,   \
+                                      void *, size_t, const int *, hipStream_t);                  \
+    template hipError_t tiles_psi2_grads<T>(const Shape &, const TilesGradPlan &, const T *,      \
+                                            const T *, const T *, const T *, const T *,           \
+                                            const T *, const T *, const Hyp<T> &, const T *,      \
+                                            const T *, T *, T *, void *, const int *, hipStream_t);
+GPPS_TILES_INST(float)
+GPPS_TILES_INST(double)
+#undef GPPS_TILES_INST
 
 }  // namespace gpps
