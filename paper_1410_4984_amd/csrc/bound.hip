@@ -92,11 +92,12 @@ P *at(void *ws, size_t off) { return reinterpret_cast<P *>(static_cast<char *>(w
 // Kmm = k(Z, Z) + jitter I and A = Kmm + beta Psi2, both fp64 and padded to Mp with
 // the identity; K0 = k(Z, Z) and Psi2 (fp64, zero-padded) kept for later.
 template <typename T>
-__global__ void bound_kmm_kernel(int M, int Q, int Mp, const T *__restrict__ Z, Hyp<T> h,
-                                 double jitter, double beta, const T *__restrict__ Psi2,
-                                 double *__restrict__ K0, double *__restrict__ Kj,
-                                 double *__restrict__ A, double *__restrict__ P2) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__device__ inline void kmm_block(int64_t block, int M, int Q, int Mp, const T *__restrict__ Z,
+                                 const Hyp<T> &h, double jitter, double beta,
+                                 const T *__restrict__ Psi2, double *__restrict__ K0,
+                                 double *__restrict__ Kj, double *__restrict__ A,
+                                 double *__restrict__ P2) {
+    const int64_t i = block * 256 + threadIdx.x;
     if (i >= (int64_t)Mp * Mp) return;
     const int m = (int)(i / Mp), mp = (int)(i - (int64_t)m * Mp);
     if (m < M && mp < M) {
@@ -123,13 +124,11 @@ __global__ void bound_kmm_kernel(int M, int Q, int Mp, const T *__restrict__ Z, 
 // Per block of kRowBlock rows: sum_nd Y^2 and sum_nq (mu^2 + S - log S - 1) / 2
 // (zero when S is null: known inputs).
 template <typename T>
-__global__ __launch_bounds__(256) void bound_rows_kernel(int64_t N, int Q, int64_t D,
-                                                         const T *__restrict__ mu,
-                                                         const T *__restrict__ S,
-                                                         const T *__restrict__ Y,
-                                                         double *__restrict__ part) {
+__device__ inline void rows_block(int64_t block, int64_t N, int Q, int64_t D, const T *__restrict__ mu,
+                                  const T *__restrict__ S, const T *__restrict__ Y,
+                                  double *__restrict__ part) {
     __shared__ double red[2][256];
-    const int64_t n0 = (int64_t)blockIdx.x * kRowBlock;
+    const int64_t n0 = block * kRowBlock;
     const int64_t rows = min<int64_t>(kRowBlock, N - n0);
     double yy = 0.0, kl = 0.0;
     for (int64_t k = threadIdx.x; k < rows * D; k += 256) {
@@ -153,22 +152,20 @@ __global__ __launch_bounds__(256) void bound_rows_kernel(int64_t N, int Q, int64
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        part[blockIdx.x * 2] = red[0][0];
-        part[blockIdx.x * 2 + 1] = red[1][0];
+        part[block * 2] = red[0][0];
+        part[block * 2 + 1] = red[1][0];
     }
 }
 
 // Psi1^T Y over one chunk of kPsiYRows rows: part[chunk][m][d].  Threads walk
 // the (m, d) entries; each sums its chunk's rows in order.
 template <typename T>
-__global__ __launch_bounds__(256) void bound_psiy_kernel(int64_t N, int M, int64_t D,
-                                                         const T *__restrict__ Psi1,
-                                                         const T *__restrict__ Y,
-                                                         double *__restrict__ part) {
-    const int64_t n0 = (int64_t)blockIdx.x * kPsiYRows;
+__device__ inline void psiy_block(int64_t chunk, int64_t part0, int64_t parts, int64_t N, int M, int64_t D,
+                                  const T *__restrict__ Psi1, const T *__restrict__ Y,
+                                  double *__restrict__ part) {
+    const int64_t n0 = chunk * kPsiYRows;
     const int64_t n1 = min<int64_t>(N, n0 + kPsiYRows);
-    for (int64_t k = (int64_t)blockIdx.y * 256 + threadIdx.x; k < (int64_t)M * D;
-         k += (int64_t)gridDim.y * 256) {
+    for (int64_t k = part0 * 256 + threadIdx.x; k < (int64_t)M * D; k += parts * 256) {
         const int m = (int)(k % M);
         const int64_t d = k / M;
         // row order; loads issued 16 rows at a time so that they overlap
@@ -185,19 +182,34 @@ __global__ __launch_bounds__(256) void bound_psiy_kernel(int64_t N, int M, int64
             for (int j = 0; j < 16; ++j) s += a[j] * b[j];
         }
         for (; n < n1; ++n) s += (double)Psi1[n * M + m] * (double)Y[n * D + d];
-        part[((int64_t)blockIdx.x * D + d) * M + m] = s;
+        part[(chunk * D + d) * M + m] = s;
     }
+}
+
+// The three above, which do not depend on each other, in one launch: of a small fit's
+// evaluation the launches are the time (N = 3,000, M = 25: see bound_middle).
+template <typename T>
+__global__ __launch_bounds__(256) void bound_first_kernel(
+    int64_t N, int M, int Q, int64_t D, int Mp, unsigned kb, unsigned rb, unsigned chunks, unsigned parts,
+    const T *__restrict__ mu, const T *__restrict__ S, const T *__restrict__ Z, const T *__restrict__ Y,
+    Hyp<T> h, double jitter, double beta, const T *__restrict__ Psi1, const T *__restrict__ Psi2,
+    double *__restrict__ K0, double *__restrict__ Kj, double *__restrict__ A, double *__restrict__ P2,
+    double *__restrict__ rpart, double *__restrict__ ypart) {
+    unsigned b = blockIdx.x;
+    if (b < kb) return kmm_block<T>(b, M, Q, Mp, Z, h, jitter, beta, Psi2, K0, Kj, A, P2);
+    if ((b -= kb) < rb) return rows_block<T>(b, N, Q, D, mu, S, Y, rpart);
+    b -= rb;
+    psiy_block<T>(b % chunks, b / chunks, parts, N, M, D, Psi1, Y, ypart);
 }
 
 // Psi[m][d] = sum over chunks; padded rows zero.  32 outputs per workgroup,
 // each summed by 8 groups of threads (group g: chunks g, g + 8, ... in order,
 // loads issued 4 at a time), then the 8 group sums in order.
-__global__ __launch_bounds__(256) void bound_psiy_reduce_kernel(int M, int Mp, int64_t D, int64_t chunks,
-                                                                const double *__restrict__ part,
-                                                                double *__restrict__ Psi) {
+__device__ inline void psiy_reduce_block(int64_t block, int M, int Mp, int64_t D, int64_t chunks,
+                                         const double *__restrict__ part, double *__restrict__ Psi) {
     __shared__ double gs[8][32];
     const int o = threadIdx.x & 31, g = threadIdx.x >> 5;
-    const int64_t k = (int64_t)blockIdx.x * 32 + o;
+    const int64_t k = block * 32 + o;
     const bool in = k < (int64_t)Mp * D;
     const int m = in ? (int)(k / D) : M;
     const int64_t d = in ? k - (int64_t)m * D : 0;
@@ -241,7 +253,8 @@ __device__ inline double lane_bcast(double v, int l) {
 // register round trip and its wait states).  Each element is updated in the
 // same order as a column sweep over j.  Workgroup K writes L_KK (zero above the diagonal) to the side
 // buffer Dg, since the others are still reading tile (K, K) (the update launch
-// copies it in), the sum of its log-pivots to logdet[K], and adds the count of
+// copies it in; the last step has no others and writes the tile itself), the sum of its
+// log-pivots, taken by a lane each, to logdet[K], and adds the count of
 // non-positive pivots to logdet[nbk].
 __global__ __launch_bounds__(64) void bound_chol_panel_kernel(int Mp, int K, double *__restrict__ A0,
                                                               double *__restrict__ Dg,
@@ -255,15 +268,11 @@ __global__ __launch_bounds__(64) void bound_chol_panel_kernel(int Mp, int K, dou
     double a[kB];
 #pragma unroll
     for (int c = 0; c < kB; ++c) a[c] = A[(int64_t)(K * kB + r) * Mp + K * kB + c];
-    double ld = 0.0;
-    bool bad = false;
+    double pivot = 1.0;
 #pragma unroll
     for (int j = 0; j < kB; ++j) {
         const double d = lane_bcast(a[j], j);  // A_jj after steps 0 .. j - 1
-        if (I == K) {  // uniform: only the diagonal workgroup records the pivots
-            bad |= !(d > 0.0);
-            ld += log(d);
-        }
+        if (r == j) pivot = d;
         const double ljj = sqrt(d);
         a[j] = r > j ? a[j] / ljj : (r == j ? ljj : 0.0);  // column j of L; zero above
         __syncthreads();  // one wave: orders the previous step's reads before the store
@@ -275,9 +284,15 @@ __global__ __launch_bounds__(64) void bound_chol_panel_kernel(int Mp, int K, dou
         for (int c = j + 1; c < kB; ++c) a[c] -= a[j] * col[c];
     }
     if (I == K) {
+        double *out = K == nbk - 1 ? A + (int64_t)(K * kB + r) * Mp + K * kB : Dg + (mat * kB + r) * kB;
         if (own)
 #pragma unroll
-            for (int c = 0; c < kB; ++c) Dg[(mat * kB + r) * kB + c] = a[c];
+            for (int c = 0; c < kB; ++c) out[c] = a[c];
+        const bool bad = __any(!(pivot > 0.0));
+        const double lp = log(pivot);
+        double ld = 0.0;
+#pragma unroll
+        for (int j = 0; j < kB; ++j) ld += lane_bcast(lp, j);
         if (lane == 0) {
             logdet[mat * (nbk + 1) + K] = ld;
             const double prev = K == 0 ? 0.0 : logdet[mat * (nbk + 1) + nbk];
@@ -335,11 +350,16 @@ __global__ __launch_bounds__(256) void bound_chol_update_kernel(int Mp, int K, d
 // matrix: X_KK = L_KK^-1, X_IK = L_II^-1 (-sum_{J=K}^{I-1} L_IJ X_JK) for I > K, by
 // forward substitution; the finished X_JK of the column stay in LDS (dynamic:
 // one tile of L plus nbk - K tiles of X).  Tiles above the diagonal are written
-// as zero.
-__global__ __launch_bounds__(256) void bound_trinv_kernel(int Mp, const double *__restrict__ L0,
-                                                          double *__restrict__ X0) {
+// as zero.  The workgroups past the 2 nbk first ones finish Psi1^T Y, which has to
+// be there for the next launch only.
+__global__ __launch_bounds__(256) void bound_trinv_kernel(int M, int Mp, int64_t D, int64_t chunks,
+                                                          const double *__restrict__ L0,
+                                                          double *__restrict__ X0,
+                                                          const double *__restrict__ ypart,
+                                                          double *__restrict__ Psi) {
     extern __shared__ double sh[];
-    const int K = blockIdx.x, mat = blockIdx.y, nbk = Mp / kB;
+    const int nbk = Mp / kB, K = blockIdx.x % nbk, mat = blockIdx.x / nbk;
+    if (mat >= 2) return psiy_reduce_block(blockIdx.x - 2 * nbk, M, Mp, D, chunks, ypart, Psi);
     const double *L = L0 + (int64_t)mat * Mp * Mp;
     double *Xg = X0 + (int64_t)mat * Mp * Mp;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
@@ -441,15 +461,39 @@ __global__ __launch_bounds__(256) void bound_gemm2_kernel(GemmJob j0, GemmJob j1
     gemm_tile(j, blockIdx.x, blockIdx.y);
 }
 
+// dL/dPsi1[n][m] = beta^2 sum_d Y[n][d] C[m][d]  (written over Psi1).
+template <typename T>
+__device__ inline void g1_block(int64_t block, int64_t N, int M, int64_t D, double beta2,
+                                const T *__restrict__ Y, const double *__restrict__ C, T *__restrict__ G1) {
+    const int64_t i = block * 256 + threadIdx.x;
+    if (i >= N * M) return;
+    int64_t n;
+    int m;
+    if (i <= 0x7fffffff) {  // 32-bit division where the index fits
+        const unsigned u = (unsigned)i, nn = u / (unsigned)M;
+        n = nn;
+        m = (int)(u - nn * (unsigned)M);
+    } else {
+        n = i / M;
+        m = (int)(i - n * M);
+    }
+    double s = 0.0;
+    for (int64_t d = 0; d < D; ++d) s += (double)Y[n * D + d] * C[(int64_t)m * D + d];
+    G1[i] = (T)(beta2 * s);
+}
+
 // dL/dPsi2 (element type T, M x M), dL/dKmm (fp64, Mp x Mp) and, per row m, the
-// partial traces tr(A^-1 Psi2), tr(P Psi2), tr(Kmm^-1 Psi2) (all symmetric).
+// partial traces tr(A^-1 Psi2), tr(P Psi2), tr(Kmm^-1 Psi2) (all symmetric).  The workgroups
+// past the first Mp form dL/dPsi1.
 template <typename T>
 __global__ __launch_bounds__(256) void bound_assemble_kernel(
     int M, int Mp, int64_t D, double beta, const double *__restrict__ Kinv,
     const double *__restrict__ Ainv, const double *__restrict__ Pm, const double *__restrict__ KPK,
     const double *__restrict__ P2, T *__restrict__ G2, double *__restrict__ GK,
-    double *__restrict__ tpart) {
+    double *__restrict__ tpart, int64_t N, const T *__restrict__ Y, const double *__restrict__ C,
+    T *__restrict__ G1) {
     __shared__ double red[3][256];
+    if ((int)blockIdx.x >= Mp) return g1_block<T>(blockIdx.x - Mp, N, M, D, beta * beta, Y, C, G1);
     const int m = blockIdx.x;
     const double hd = 0.5 * (double)D;
     double ta = 0.0, tp = 0.0, tk = 0.0;
@@ -475,27 +519,6 @@ __global__ __launch_bounds__(256) void bound_assemble_kernel(
     }
     if (threadIdx.x == 0)
         for (int j = 0; j < 3; ++j) tpart[(int64_t)m * 4 + j] = red[j][0];
-}
-
-// dL/dPsi1[n][m] = beta^2 sum_d Y[n][d] C[m][d]  (written over Psi1).
-template <typename T>
-__global__ void bound_g1_kernel(int64_t N, int M, int64_t D, double beta2, const T *__restrict__ Y,
-                                const double *__restrict__ C, T *__restrict__ G1) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N * M) return;
-    int64_t n;
-    int m;
-    if (i <= 0x7fffffff) {  // 32-bit division where the index fits
-        const unsigned u = (unsigned)i, nn = u / (unsigned)M;
-        n = nn;
-        m = (int)(u - nn * (unsigned)M);
-    } else {
-        n = i / M;
-        m = (int)(i - n * M);
-    }
-    double s = 0.0;
-    for (int64_t d = 0; d < D; ++d) s += (double)Y[n * D + d] * C[(int64_t)m * D + d];
-    G1[i] = (T)(beta2 * s);
 }
 
 // The bound and dL/dbeta from the reductions (one workgroup, fixed order).
@@ -591,11 +614,20 @@ __global__ __launch_bounds__(64) void bound_kmm_grad_kernel(int M, int Q, int Mp
     if (q == 0) ksf[m] = sw / (double)h.sf2;
 }
 
-// dl[q] += sum_m kdl[m][q], dsigma_f2 += sum_m ksf[m] (fixed order).
+// Workgroup 0: dl[q] += sum_m kdl[m][q], dsigma_f2 += sum_m ksf[m] (fixed order).  The others:
+// the KL term's gradient, dmu -= mu, dS -= (1 - 1/S) / 2.
 template <typename T>
-__global__ void bound_kmm_reduce_kernel(int M, int Q, const double *__restrict__ kdl,
-                                        const double *__restrict__ ksf, T *__restrict__ dl,
-                                        T *__restrict__ dsf2) {
+__global__ __launch_bounds__(256) void bound_tail_kernel(
+    int M, int Q, const double *__restrict__ kdl, const double *__restrict__ ksf, T *__restrict__ dl,
+    T *__restrict__ dsf2, int64_t NQ, const T *__restrict__ mu, const T *__restrict__ S, T *__restrict__ dmu,
+    T *__restrict__ dS) {
+    if (blockIdx.x > 0) {
+        const int64_t i = (int64_t)(blockIdx.x - 1) * 256 + threadIdx.x;
+        if (i >= NQ) return;
+        dmu[i] = dmu[i] - mu[i];
+        dS[i] = dS[i] - (T)0.5 * ((T)1 - (T)1 / S[i]);
+        return;
+    }
     const int q = threadIdx.x;
     // m in order; loads issued 8 at a time so that they overlap
     if (q <= Q) {
@@ -612,16 +644,6 @@ __global__ void bound_kmm_reduce_kernel(int M, int Q, const double *__restrict__
         if (q < Q) dl[q] = (T)((double)dl[q] + s);
         else dsf2[0] = (T)((double)dsf2[0] + s);
     }
-}
-
-// The KL term's gradient: dmu -= mu, dS -= (1 - 1/S) / 2.
-template <typename T>
-__global__ void bound_kl_grad_kernel(int64_t NQ, const T *__restrict__ mu, const T *__restrict__ S,
-                                     T *__restrict__ dmu, T *__restrict__ dS) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= NQ) return;
-    dmu[i] = dmu[i] - mu[i];
-    dS[i] = dS[i] - (T)0.5 * ((T)1 - (T)1 / S[i]);
 }
 
 }  // namespace
@@ -649,23 +671,18 @@ hipError_t bound_middle(const Shape &s, int64_t D, const T *mu, const T *S, cons
     double *Psi = at<double>(ws, p.off_psi), *C = at<double>(ws, p.off_c);
     double *ld = at<double>(ws, p.off_ld);
 
-    // Kmm, A; the row reductions; Psi = Psi1^T Y
+    // Launches that do not depend on each other are one, each part with workgroups of its own
+    // (at M <= 32 thirteen were nine, and with the known-input path's merged ones an evaluation at
+    // N = 3,000, M = 25, Q = 1, D = 2 went from 173 to 128 us).
+    // Kmm, A; the row reductions; Psi1^T Y by chunks
     {
-        TimedScope ts(st, "bound_kmm");
-        bound_kmm_kernel<T><<<(unsigned)cdiv(mm, 256), 256, 0, st>>>(M, Q, Mp, Z, h, jitter, beta, Psi2,
-                                                                    K0, gj, gj + mm, P2);
-    }
-    {
-        TimedScope ts(st, "bound_rows");
-        bound_rows_kernel<T><<<(unsigned)p.rblocks, 256, 0, st>>>(s.N, Q, D, mu, S, Y,
-                                                                 at<double>(ws, p.off_rpart));
-    }
-    {
-        TimedScope ts(st, "bound_psiy");
-        dim3 g((unsigned)p.ychunks, (unsigned)std::min<int64_t>(cdiv((int64_t)M * D, 256), 16));
-        bound_psiy_kernel<T><<<g, 256, 0, st>>>(s.N, M, D, Psi1, Y, at<double>(ws, p.off_ypart));
-        bound_psiy_reduce_kernel<<<(unsigned)cdiv(p.Mp * D, 32), 256, 0, st>>>(
-            M, Mp, D, p.ychunks, at<double>(ws, p.off_ypart), Psi);
+        const unsigned kb = (unsigned)cdiv(mm, 256);
+        const unsigned parts = (unsigned)std::min<int64_t>(cdiv((int64_t)M * D, 256), 16);
+        TimedScope ts(st, "bound_first");
+        bound_first_kernel<T><<<(unsigned)(kb + p.rblocks + p.ychunks * parts), 256, 0, st>>>(
+            s.N, M, Q, D, Mp, kb, (unsigned)p.rblocks, (unsigned)p.ychunks, parts, mu, S, Z, Y, h, jitter,
+            beta, Psi1, Psi2, K0, gj, gj + mm, P2, at<double>(ws, p.off_rpart),
+            at<double>(ws, p.off_ypart));
     }
     // Kmm = L_k L_k^T and A = L_a L_a^T (blocked Cholesky, in place), log determinants,
     // the triangular inverses and Kmm^-1 = L_k^-T L_k^-1, A^-1 = L_a^-T L_a^-1
@@ -675,13 +692,15 @@ hipError_t bound_middle(const Shape &s, int64_t D, const T *mu, const T *S, cons
         double *Dg = at<double>(ws, p.off_dg);
         for (int K = 0; K < p.nbk; ++K) {
             bound_chol_panel_kernel<<<dim3(p.nbk - K, 2), 64, 0, st>>>(Mp, K, Lf, Dg, ld);
-            bound_chol_update_kernel<<<dim3(p.nbk, p.nbk, 2), 256, 0, st>>>(Mp, K, Lf, Dg);
+            if (K + 1 < p.nbk)
+                bound_chol_update_kernel<<<dim3(p.nbk, p.nbk, 2), 256, 0, st>>>(Mp, K, Lf, Dg);
         }
         const size_t shb = sizeof(double) * kB * (kB + 1) * (p.nbk + 1);
         hipError_t e = hipFuncSetAttribute((const void *)bound_trinv_kernel,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)shb);
         if (e != hipSuccess) return e;
-        bound_trinv_kernel<<<dim3(p.nbk, 2), 256, shb, st>>>(Mp, Lf, Li);
+        bound_trinv_kernel<<<(unsigned)(2 * p.nbk + cdiv(p.Mp * D, 32)), 256, shb, st>>>(
+            M, Mp, D, p.ychunks, Lf, Li, at<double>(ws, p.off_ypart), Psi);
     }
     // C = A^-1 Psi, P = C C^T, Kmm^-1 Psi2 Kmm^-1; dL/dPsi2, dL/dKmm, dL/dPsi1; the scalars
     {
@@ -702,10 +721,8 @@ hipError_t bound_middle(const Shape &s, int64_t D, const T *mu, const T *S, cons
     }
     {
         TimedScope ts(st, "bound_assemble");
-        bound_assemble_kernel<T><<<(unsigned)p.Mp, 256, 0, st>>>(M, Mp, D, beta, Kinv, Ainv, Pm, KPK, P2,
-                                                                G2, GK, at<double>(ws, p.off_tpart));
-        bound_g1_kernel<T><<<(unsigned)cdiv(s.N * M, 256), 256, 0, st>>>(s.N, M, D, beta * beta, Y, C,
-                                                                        Psi1);
+        bound_assemble_kernel<T><<<(unsigned)(p.Mp + cdiv(s.N * M, 256)), 256, 0, st>>>(
+            M, Mp, D, beta, Kinv, Ainv, Pm, KPK, P2, G2, GK, at<double>(ws, p.off_tpart), s.N, Y, C, Psi1);
         bound_scalar_kernel<T><<<1, 256, 0, st>>>(s.N, M, Mp, D, p.nbk, beta, (double)s.N * (double)h.sf2,
                                                  p.rblocks, at<double>(ws, p.off_rpart),
                                                  at<double>(ws, p.off_tpart), ld, Psi, C, L, dbeta);
@@ -722,9 +739,8 @@ hipError_t bound_tail(const Shape &s, int64_t D, const T *mu, const T *S, const 
     bound_kmm_grad_kernel<T><<<(unsigned)M, 64, 0, st>>>(M, Q, (int)p.Mp, Z, h, at<double>(ws, p.off_k0),
                                                         at<double>(ws, p.off_gk), dZ,
                                                         at<double>(ws, p.off_kdl), at<double>(ws, p.off_ksf));
-    bound_kmm_reduce_kernel<T><<<1, 128, 0, st>>>(M, Q, at<double>(ws, p.off_kdl), at<double>(ws, p.off_ksf),
-                                                 dl, dsf2);
-    if (S) bound_kl_grad_kernel<T><<<(unsigned)cdiv(s.N * Q, 256), 256, 0, st>>>(s.N * Q, mu, S, dmu, dS);
+    bound_tail_kernel<T><<<(unsigned)(1 + (S ? cdiv(s.N * Q, 256) : 0)), 256, 0, st>>>(
+        M, Q, at<double>(ws, p.off_kdl), at<double>(ws, p.off_ksf), dl, dsf2, s.N * Q, mu, S, dmu, dS);
     return hipGetLastError();
 }
 

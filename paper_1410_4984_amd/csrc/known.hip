@@ -141,29 +141,23 @@ KPlan make_kplan(const Shape &s, size_t elem) {
 }
 
 // ---------------------------------------------------------------- centring
-// cz[q] = mean_m z_mq, zs = (Z - cz) / l.  One workgroup: G = 1024 / Q groups of
-// Q threads sum rows m = g, g + G, ... (coalesced; loads issued 8 at a time so
-// that they overlap), then the G partial sums of each dimension are added in
-// group order.
-template <typename T>
-__global__ __launch_bounds__(1024) void known_centre_kernel(int M, int Q, const T *__restrict__ Z,
-                                                           Hyp<T> h, T *__restrict__ cz,
-                                                           T *__restrict__ zs) {
-    __shared__ T part[1024];
-    __shared__ T c[GPPS_MAX_Q];
-    const int t = threadIdx.x, G = 1024 / Q;
+// c[q] = mean_m z_mq in LDS, by one workgroup of W threads: up to 64 groups of Q threads
+// sum rows m = g, g + G, ... (coalesced; loads issued 8 at a time so that they overlap),
+// then the G partial sums of each dimension are added in group order (1024 / Q groups
+// took 20 us at Q = 1, whose one thread added 1024 of them).
+template <typename T, int W>
+__device__ inline void centre(int M, int Q, const T *__restrict__ Z, T *part, T *c) {
+    const int t = threadIdx.x, G = min(min(W / Q, 64), M);
     if (t < G * Q) {
         const int g = t / Q, q = t - g * Q;
         T s = 0;
-        int m = g;
-        for (; m + 7 * G < M; m += 8 * G) {
+        for (int m = g; m < M; m += 8 * G) {
             T v[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = Z[(int64_t)(m + j * G) * Q + q];
+            for (int j = 0; j < 8; ++j) v[j] = Z[(int64_t)min(m + j * G, M - 1) * Q + q];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) s += v[j];
+            for (int j = 0; j < 8; ++j) s += m + j * G < M ? v[j] : T(0);
         }
-        for (; m < M; m += G) s += Z[(int64_t)m * Q + q];
         part[t] = s;
     }
     __syncthreads();
@@ -171,11 +165,24 @@ __global__ __launch_bounds__(1024) void known_centre_kernel(int M, int Q, const 
         T s = 0;
         for (int g = 0; g < G; ++g) s += part[g * Q + t];
         c[t] = s / T(M);
-        cz[t] = c[t];
     }
     __syncthreads();
+}
+// M Q and Q up to which every Kfu workgroup finds the centre itself, for one launch less:
+// 8 values a thread of a workgroup, and LDS within 64 KB.
+constexpr int64_t kOwnCentre = 2048, kOwnQ = 32;
+
+// cz[q] = c[q], zs = (Z - cz) / l.
+template <typename T>
+__global__ __launch_bounds__(1024) void known_centre_kernel(int M, int Q, const T *__restrict__ Z,
+                                                           Hyp<T> h, T *__restrict__ cz,
+                                                           T *__restrict__ zs) {
+    __shared__ T part[1024];
+    __shared__ T c[GPPS_MAX_Q];
+    centre<T, 1024>(M, Q, Z, part, c);
+    if ((int)threadIdx.x < Q) cz[threadIdx.x] = c[threadIdx.x];
 #pragma unroll 4
-    for (int i = t; i < M * Q; i += 1024) zs[i] = (Z[i] - c[i % Q]) / h.l[i % Q];
+    for (int i = threadIdx.x; i < M * Q; i += 1024) zs[i] = (Z[i] - c[i % Q]) / h.l[i % Q];
 }
 
 // ---------------------------------------------------------------- Kfu
@@ -183,16 +190,33 @@ __global__ __launch_bounds__(1024) void known_centre_kernel(int M, int Q, const 
 // (N x M, the Psi1 layout), TRANS = true writes out[m][n] (M x N, the layout
 // the gradient GEMM streams).  Grid: (row blocks, column blocks); the
 // workgroups of the first column block also write xs.  Dynamic LDS: 2 * 64 * Q elements.
+// own: cz and zs are not there yet; each workgroup centres Z itself, and those of the first
+// row block write zs.  TRANS: the row blocks past the rows' own form the symmetric part
+// of dL/dPsi2 (G2; NULL: none).
 template <typename T, bool TRANS>
 __global__ __launch_bounds__(256) void known_kfu_kernel(int64_t N, int M, int Q,
                                                         const T *__restrict__ X,
+                                                        const T *__restrict__ Z, bool own,
                                                         const T *__restrict__ cz,
-                                                        const T *__restrict__ zs, Hyp<T> h,
-                                                        T *__restrict__ out, T *__restrict__ xs) {
+                                                        T *__restrict__ zs, Hyp<T> h,
+                                                        T *__restrict__ out, T *__restrict__ xs,
+                                                        const T *__restrict__ G2, T *__restrict__ G2s) {
     extern __shared__ double known_smem[];
     T *sx = reinterpret_cast<T *>(known_smem);  // [q][64] scaled rows
     T *sz = sx + Q * kEdge;                     // [q][64] scaled inducing inputs
+    T *c0 = sz + Q * kEdge;                     // [Q] the centre (own only)
     const int tid = threadIdx.x;
+    if (TRANS) {
+        const int64_t rb = (N + kEdge - 1) / kEdge;
+        if ((int64_t)blockIdx.x >= rb) {
+            const int64_t i = ((blockIdx.x - rb) * gridDim.y + blockIdx.y) * 256 + tid;
+            if (i >= (int64_t)M * M) return;
+            const int m = (int)(i / M), mp = (int)(i - (int64_t)m * M);
+            G2s[i] = T(0.5) * (G2[(int64_t)m * M + mp] + G2[(int64_t)mp * M + m]);
+            return;
+        }
+    }
+    if (own) centre<T, 256>(M, Q, Z, sx, c0);   // at most 64 Q partial sums
     const int64_t n0 = (int64_t)blockIdx.x * kEdge;
     const int m0 = blockIdx.y * kEdge;
     for (int i = tid; i < kEdge * Q; i += 256) {
@@ -200,12 +224,18 @@ __global__ __launch_bounds__(256) void known_kfu_kernel(int64_t N, int M, int Q,
         const int64_t n = n0 + r;
         T v = 0;
         if (n < N) {
-            v = (X[n * Q + q] - cz[q]) / h.l[q];
+            v = (X[n * Q + q] - (own ? c0[q] : cz[q])) / h.l[q];
             if (blockIdx.y == 0) xs[n * Q + q] = v;
         }
         sx[q * kEdge + r] = v;
         const int m = m0 + r;
-        sz[q * kEdge + r] = m < M ? zs[(int64_t)m * Q + q] : T(0);
+        T z = 0;
+        if (m < M) {
+            const int64_t k = (int64_t)m * Q + q;
+            z = own ? (Z[k] - c0[q]) / h.l[q] : zs[k];
+            if (own && blockIdx.x == 0) zs[k] = z;
+        }
+        sz[q * kEdge + r] = z;
     }
     __syncthreads();
     const T pre = kpre(h);
@@ -479,14 +509,6 @@ __global__ __launch_bounds__(256) void known_syrk_reduce_kernel(int64_t N, int M
 }
 
 // ---------------------------------------------------------------- gradients
-template <typename T>
-__global__ void known_sym_kernel(int M, const T *__restrict__ G2, T *__restrict__ G2s) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (int64_t)M * M) return;
-    const int m = (int)(i / M), mp = (int)(i - (int64_t)m * M);
-    G2s[i] = T(0.5) * (G2[(int64_t)m * M + mp] + G2[(int64_t)mp * M + m]);
-}
-
 // E^T[m][n] = (G1[n][m] + 2 sum_k G2s[m][k] Kt[k][n]) Kt[m][n], one workgroup
 // per kBlk x kBlk block (m, n) on the matrix cores.  G2s is symmetric, so its
 // A operand G2s[m][k] is read as G2s[k][m], a contiguous row.  Same XCD
@@ -722,15 +744,48 @@ __global__ __launch_bounds__(256) void known_chain_kernel(int64_t N, int M, int 
     if (tid == 0) epart[g * nbk + blk] = se_all;
 }
 
-// dX = -(sum over the inducing-input blocks of dxpart, in block order) / l.
-// One workgroup per 64 datapoints: the sums are read coalesced over n from
+// Workgroups below tiles: dX = -(sum over the inducing-input blocks of dxpart, in block
+// order) / l, one per 64 datapoints: the sums are read coalesced over n from
 // dxpart [b][q][n] and written through an LDS transpose as the block's 64 Q
 // contiguous elements of dX.
+// Then one workgroup per inducing input m: Vc[m][k] = sum over the chain kernel's
+// tile groups of colpart[group][m][k], k < 2 Q.  S = 256 / (2 Q) sets of 2 Q
+// threads take groups s, s + S, ... (coalesced over k); the S partials are
+// added in order.
 template <typename T>
-__global__ __launch_bounds__(256) void known_dx_kernel(int64_t N, int Q, int nbk,
-                                                       const T *__restrict__ dxpart, Hyp<T> h,
-                                                       T *__restrict__ dX) {
+__global__ __launch_bounds__(256) void known_dx_reduce_kernel(int64_t N, int M, int Q, int nbk, int64_t tiles,
+                                                              int64_t groups, const T *__restrict__ dxpart,
+                                                              Hyp<T> h, T *__restrict__ dX,
+                                                              const T *__restrict__ colpart,
+                                                              T *__restrict__ Vc) {
     __shared__ T tile[kEdge][GPPS_MAX_Q + 1];
+    __shared__ T part[256];
+    if ((int64_t)blockIdx.x >= tiles) {
+        const int t = threadIdx.x, K = 2 * Q, S = 256 / K;
+        const int64_t m = blockIdx.x - tiles;
+        if (t < S * K) {
+            const int j = t / K, k = t - j * K;
+            // groups j, j + S, ... in order; loads issued 8 at a time so that they overlap
+            T s = 0;
+            int64_t c = j;
+            for (; c + 7 * S < groups; c += 8 * S) {
+                T v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = colpart[((c + u * S) * M + m) * K + k];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) s += v[u];
+            }
+            for (; c < groups; c += S) s += colpart[(c * M + m) * K + k];
+            part[t] = s;
+        }
+        __syncthreads();
+        if (t < K) {
+            T s = 0;
+            for (int j = 0; j < S; ++j) s += part[j * K + t];
+            Vc[m * K + t] = s;
+        }
+        return;
+    }
     const int tid = threadIdx.x, nn = tid & 63;
     const int64_t n0 = (int64_t)blockIdx.x * kEdge, n = n0 + nn;
     const int cnt = (int)min<int64_t>(kEdge, N - n0);
@@ -745,40 +800,6 @@ __global__ __launch_bounds__(256) void known_dx_kernel(int64_t N, int Q, int nbk
     for (int i = tid; i < cnt * Q; i += 256) {
         const int r = i / Q, q = i - r * Q;
         dX[n0 * Q + i] = tile[r][q];
-    }
-}
-
-// One workgroup per inducing input m: Vc[m][k] = sum over the chain kernel's
-// tile groups of colpart[group][m][k], k < 2 Q.  S = 256 / (2 Q) sets of 2 Q
-// threads take groups s, s + S, ... (coalesced over k); the S partials are
-// added in order.
-template <typename T>
-__global__ __launch_bounds__(256) void known_col_reduce_kernel(int M, int Q, int64_t groups,
-                                                               const T *__restrict__ colpart,
-                                                               T *__restrict__ Vc) {
-    __shared__ T part[256];
-    const int t = threadIdx.x, K = 2 * Q, S = 256 / K;
-    const int64_t m = blockIdx.x;
-    if (t < S * K) {
-        const int j = t / K, k = t - j * K;
-        // groups j, j + S, ... in order; loads issued 8 at a time so that they overlap
-        T s = 0;
-        int64_t c = j;
-        for (; c + 7 * S < groups; c += 8 * S) {
-            T v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = colpart[((c + u * S) * M + m) * K + k];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) s += v[u];
-        }
-        for (; c < groups; c += S) s += colpart[(c * M + m) * K + k];
-        part[t] = s;
-    }
-    __syncthreads();
-    if (t < K) {
-        T s = 0;
-        for (int j = 0; j < S; ++j) s += part[j * K + t];
-        Vc[m * K + t] = s;
     }
 }
 
@@ -815,19 +836,24 @@ __global__ __launch_bounds__(256) void known_grad_final_kernel(
 
 template <typename T>
 void launch_centre_kfu(const Shape &s, const KPlan &p, const T *X, const T *Z, const Hyp<T> &h,
-                       bool trans, T *out, void *ws, hipStream_t st) {
+                       bool trans, T *out, const T *G2, void *ws, hipStream_t st) {
     T *cz = at<T>(ws, p.off_cz), *zs = at<T>(ws, p.off_zs), *xs = at<T>(ws, p.off_xs);
-    {
+    const bool own = s.M * s.Q <= kOwnCentre && s.Q <= kOwnQ;
+    if (!own) {
         TimedScope ts(st, "known_centre");
         known_centre_kernel<T><<<1, 1024, 0, st>>>((int)s.M, (int)s.Q, Z, h, cz, zs);
     }
-    dim3 grid((unsigned)cdiv(s.N, kEdge), (unsigned)cdiv(s.M, kEdge));
-    const size_t lds = 2 * kEdge * s.Q * sizeof(T);
+    const int64_t rb = cdiv(s.N, kEdge), mb = cdiv(s.M, kEdge);
+    const int64_t sym = G2 ? cdiv(cdiv(s.M * s.M, 256), mb) : 0;   // G2's workgroups, mb at a time
+    dim3 grid((unsigned)(rb + sym), (unsigned)mb);
+    const size_t lds = (2 * kEdge + (own ? 1 : 0)) * s.Q * sizeof(T);
     TimedScope ts(st, "known_kfu");
     if (trans)
-        known_kfu_kernel<T, true><<<grid, 256, lds, st>>>(s.N, (int)s.M, (int)s.Q, X, cz, zs, h, out, xs);
+        known_kfu_kernel<T, true><<<grid, 256, lds, st>>>(s.N, (int)s.M, (int)s.Q, X, Z, own, cz, zs, h, out,
+                                                          xs, G2, at<T>(ws, p.off_g2s));
     else
-        known_kfu_kernel<T, false><<<grid, 256, lds, st>>>(s.N, (int)s.M, (int)s.Q, X, cz, zs, h, out, xs);
+        known_kfu_kernel<T, false><<<grid, 256, lds, st>>>(s.N, (int)s.M, (int)s.Q, X, Z, own, cz, zs, h, out,
+                                                           xs, nullptr, nullptr);
 }
 
 template <typename T, int QM>
@@ -852,8 +878,9 @@ hipError_t launch_chain(const Shape &s, const KPlan &p, const T *Et, const Hyp<T
             at<T>(ws, p.off_colp), at<T>(ws, p.off_ep));
     }
     TimedScope ts(st, "known_dx");
-    known_dx_kernel<T><<<(unsigned)p.tiles, 256, 0, st>>>(s.N, (int)s.Q, (int)p.nb,
-                                                         at<T>(ws, p.off_dxp), h, dX);
+    known_dx_reduce_kernel<T><<<(unsigned)(p.tiles + s.M), 256, 0, st>>>(
+        s.N, (int)s.M, (int)s.Q, (int)p.nb, p.tiles, G, at<T>(ws, p.off_dxp), h, dX, at<T>(ws, p.off_colp),
+        at<T>(ws, p.off_vc));
     return hipGetLastError();
 }
 
@@ -866,7 +893,7 @@ hipError_t known_psi_stats(const Shape &s, const T *X, const T *Z, const Hyp<T> 
                            T *Psi1, T *Psi2, int accumulate, void *ws, hipStream_t st) {
     const KPlan p = make_kplan(s, sizeof(T));
     T *K = Psi1 ? Psi1 : at<T>(ws, p.off_k);
-    launch_centre_kfu<T>(s, p, X, Z, h, false, K, ws, st);
+    launch_centre_kfu<T>(s, p, X, Z, h, false, K, nullptr, ws, st);
     T *part = at<T>(ws, p.off_part);
     {
         TimedScope ts(st, "known_syrk");
@@ -891,16 +918,12 @@ hipError_t known_psi_grads(const Shape &s, const T *X, const T *Z, const Hyp<T> 
                            void *ws, hipStream_t st) {
     const KPlan p = make_kplan(s, sizeof(T));
     T *Kt = at<T>(ws, p.off_k), *Et = at<T>(ws, p.off_e);
-    launch_centre_kfu<T>(s, p, X, Z, h, true, Kt, ws, st);
+    launch_centre_kfu<T>(s, p, X, Z, h, true, Kt, G2, ws, st);
     const int64_t nblk = cdiv(s.N, kBlk), mb = p.nb2;
     const unsigned grid = (unsigned)(round_up(nblk, 8) * mb);
     const bool vec = s.M % Vec<T>::W == 0 && s.N % Vec<T>::W == 0;  // workspace rows start on 16 bytes
     if (G2) {
-        T *G2s = at<T>(ws, p.off_g2s);
-        {
-            TimedScope ts(st, "known_sym");
-            known_sym_kernel<T><<<(unsigned)cdiv(s.M * s.M, 256), 256, 0, st>>>((int)s.M, G2, G2s);
-        }
+        const T *G2s = at<T>(ws, p.off_g2s);
         TimedScope ts(st, "known_dkfu");
         if (vec)
             known_dkfu_kernel<T, true, true><<<grid, 256, 0, st>>>(s.N, (int)s.M, nblk, mb, Kt, G1, G2s, Et);
@@ -926,8 +949,6 @@ hipError_t known_psi_grads(const Shape &s, const T *X, const T *Z, const Hyp<T> 
     if (e != hipSuccess) return e;
     TimedScope ts(st, "known_grad_reduce");
     T *Vc = at<T>(ws, p.off_vc);
-    known_col_reduce_kernel<T><<<(unsigned)s.M, 256, 0, st>>>((int)s.M, (int)s.Q, G,
-                                                             at<T>(ws, p.off_colp), Vc);
     const int64_t zblocks = cdiv(s.M * s.Q, 256);
     known_grad_final_kernel<T><<<(unsigned)(zblocks + s.Q + 1), 256, 0, st>>>(
         s.N, (int)s.M, (int)s.Q, zblocks, p.nb * G, Vc, at<T>(ws, p.off_ep), h, dL_dpsi0, dZ,
