@@ -84,10 +84,9 @@ def algorithmic(kernel: str, N: int, M: int, Q: int):
     fwd, grad = 2.0 * Q * N * P, 6.0 * Q * N * P
     table = {
         "generic_psi2_partial": ("alu", fwd, "flop"),
-        "generic_grad_rows": ("alu", 4.0 * Q * N * P, "flop"),
-        "generic_grad_cols": ("alu", 2.0 * Q * N * P, "flop"),
         "generic_grad_pairs": ("alu", grad, "flop"),
-        "generic_grad_wide": ("alu", grad, "flop"),
+        "tiles_psi2_fwd": ("alu", fwd, "flop"),
+        "tiles_psi2_grad": ("alu", grad, "flop"),
         # the matrix-core Psi2 kernels are bound by instruction issue on the SIMD,
         # mostly vector ALU (exp2, weighting, operand splits); their algorithmic
         # flops are priced against the fp32 vector peak
@@ -597,11 +596,9 @@ def main():
                 "counters": f"profiles/counters_{dom}_{args.workload}.md"}
     # Psi2 forward + gradient kernels with their reductions (F_alg's kernels), and
     # beside them with the per-row kernels that feed them
-    core = ("psi2_partial", "psi2_fwd", "psi2_grad", "grad_rows", "grad_cols", "grad_pairs",
-            "grad_wide",
-            "psi2_reduce", "psi2_finalize", "grad_reduce")
-    feed = ("mfma_rows", "mfma_rowterm", "mfma_centre", "mfma_guard", "mfma_sym",
-            "mfma_absmax", "generic_rows_pre", "generic_sym", "generic_circ", "generic_psi1")
+    core = ("psi2_partial", "psi2_fwd", "psi2_grad", "grad_pairs",
+            "psi2_reduce", "psi2_finalize", "grad_reduce", "grad_finish")
+    feed = ("mfma_rows", "mfma_rowterm", "mfma_centre", "mfma_guard", "generic_pre")
     per_step = {k: v["avg_ms"] * v["launches"] / args.kernel_steps for k, v in kernels.items()}
     t_psi2 = sum(v for k, v in per_step.items() if any(c in k for c in core)) * 1e-3
     t_feed = sum(v for k, v in per_step.items() if any(c in k for c in feed)) * 1e-3
