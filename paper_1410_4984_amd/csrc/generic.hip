@@ -150,7 +150,8 @@ T *at(void *ws, size_t off) { return reinterpret_cast<T *>(static_cast<char *>(w
 //   kSymCirc   Gc[k][m] = G2s[m][(m + k) mod M], k = 0 .. M/2: the symmetric pairs
 //              kernel reads the pair (m, m + k) of every thread m as one coalesced row
 //   kSymPadded G2s o exp(-sum_q (z_m - z_m')^2 / (4 l^2)), zero-padded to Mp x Mp (the
-//              double-precision matrix kernels)
+//              tile kernels; the last Q workgroups then find the centre and the
+//              variance of Z in a dimension each, zref [2][Q])
 constexpr int kPreElems = 1024;   // (row, dimension) pairs per workgroup
 enum SymMode { kSymNone, kSymPlain, kSymCirc, kSymPadded };
 
@@ -161,10 +162,37 @@ __global__ __launch_bounds__(256) void pre_kernel(const int *__restrict__ gate, 
                                                   T *__restrict__ w1, T *__restrict__ w2,
                                                   T *__restrict__ lp1, T *__restrict__ lp2, int mode,
                                                   int M, int Mp, const T *__restrict__ G2,
-                                                  const T *__restrict__ Z, T *__restrict__ G2s) {
+                                                  const T *__restrict__ Z, T *__restrict__ G2s,
+                                                  unsigned sblocks, T *__restrict__ zref) {
     if (gate && gate[0] == 0) return;
     if (mark && blockIdx.x == 0 && threadIdx.x == 0) mark[0] = 1;
     __shared__ T sl1[kPreElems], sl2[kPreElems];
+    if (blockIdx.x >= rblocks + sblocks) {
+        const int q = blockIdx.x - rblocks - sblocks;
+        auto total = [&](T v) {
+            __syncthreads();
+            sl1[threadIdx.x] = v;
+            __syncthreads();
+            for (int w = 128; w >= 1; w >>= 1) {
+                if ((int)threadIdx.x < w) sl1[threadIdx.x] += sl1[threadIdx.x + w];
+                __syncthreads();
+            }
+            return sl1[0];
+        };
+        T a = 0, b = 0;
+        for (int m = threadIdx.x; m < M; m += 256) a += Z[(int64_t)m * Q + q];
+        const T c = total(a) / T(M);
+        for (int m = threadIdx.x; m < M; m += 256) {
+            const T d = Z[(int64_t)m * Q + q] - c;
+            b += d * d;
+        }
+        b = total(b) / T(M);
+        if (threadIdx.x == 0) {
+            zref[q] = c;
+            zref[Q + q] = b;
+        }
+        return;
+    }
     if (blockIdx.x >= rblocks) {
         const int64_t i = (int64_t)(blockIdx.x - rblocks) * 256 + threadIdx.x;
         if (mode == kSymCirc) {
@@ -870,7 +898,7 @@ __global__ __launch_bounds__(256) void grad_finish_kernel(
 template <typename T>
 void pre(const Shape &s, const Plan &p, const T *S, const Hyp<T> &h, void *ws, const int *gate,
          int *mark, hipStream_t st, int mode = kSymNone, const T *G2 = nullptr, const T *Z = nullptr,
-         T *G2s = nullptr) {
+         T *G2s = nullptr, T *zref = nullptr) {
     // few rows a workgroup where there are few: at least a workgroup per CU
     const int64_t rows = std::max<int64_t>(1, std::min(kPreElems / s.Q, cdiv(s.N, 256)));
     const int64_t rb = cdiv(s.N, rows), Mp = cdiv(s.M, 16) * 16;
@@ -878,9 +906,11 @@ void pre(const Shape &s, const Plan &p, const T *S, const Hyp<T> &h, void *ws, c
                       : mode == kSymCirc ? (s.M / 2 + 1) * s.M
                       : mode == kSymPadded ? Mp * Mp : s.M * s.M;
     TimedScope ts(st, "generic_pre");
-    pre_kernel<T><<<(unsigned)(rb + cdiv(n, 256)), 256, 0, st>>>(
+    const int64_t sb = cdiv(n, 256), zb = zref ? s.Q : 0;
+    pre_kernel<T><<<(unsigned)(rb + sb + zb), 256, 0, st>>>(
         gate, mark, s.N, (int)s.Q, (int)rows, (unsigned)rb, S, h, at<T>(ws, p.off_w1), at<T>(ws, p.off_w2),
-        at<T>(ws, p.off_lp1), at<T>(ws, p.off_lp2), mode, (int)s.M, (int)Mp, G2, Z, G2s);
+        at<T>(ws, p.off_lp1), at<T>(ws, p.off_lp2), mode, (int)s.M, (int)Mp, G2, Z, G2s,
+        (unsigned)sb, zref);
 }
 
 // nblk > 1: dmu and dS from rowg's partials; else the caller's kernel wrote them.
@@ -949,7 +979,8 @@ hipError_t generic_psi_grads(const Shape &s, const T *mu, const T *S, const T *Z
         if (!f.ok) return hipErrorInvalidValue;   // no shape: the region holds at least one chunk
         char *region = at<char>(ws, p.off_p2);
         T *Gc = G2 ? at<T>(region, f.off_gc) : nullptr;
-        pre<T>(s, p, S, h, ws, gate, mark, st, G2 ? kSymPadded : kSymNone, G2, Z, Gc);
+        T *zref = G2 ? at<T>(region, f.off_ref) : nullptr;
+        pre<T>(s, p, S, h, ws, gate, mark, st, G2 ? kSymPadded : kSymNone, G2, Z, Gc, zref);
         const hipError_t e = tiles_psi2_grads<T>(s, f, mu, S, Z, w1, w2, lp1, lp2, h, G1, Gc, dmu, dS,
                                                  region, gate, st);
         if (e != hipSuccess) return e;

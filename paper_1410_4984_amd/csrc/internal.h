@@ -98,7 +98,7 @@ struct TilesGradPlan {
     int64_t chunks, rows;             // row chunks, rows per chunk
     int groups, nw, wrows, nwin;      // workgroups per chunk, waves, z rows staged, windows
     size_t lds;
-    size_t off_gc, off_rowg, off_colp, off_rowp, end;
+    size_t off_gc, off_ref, off_rowg, off_colp, off_rowp, end;
 };
 TilesGradPlan tiles_grad_plan(const Shape &s, size_t budget, size_t elem);
 template <typename T>

@@ -65,9 +65,6 @@ struct Mm<double> {
     static __device__ v4 mul(double a, double b, v4 c) {
         return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
     }
-    static __device__ double fours(double a, double b, double c) {
-        return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
-    }
     static __host__ __device__ constexpr int row(int v, int g) { return 4 * v + g; }
 };
 template <>
@@ -77,13 +74,15 @@ struct Mm<float> {
     static __device__ v4 mul(float a, float b, v4 c) {
         return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
     }
-    static __device__ float fours(float, float, float) { return 0.f; }
     static __host__ __device__ constexpr int row(int v, int g) { return 4 * g + v; }
 };
+__device__ inline double fours(double a, double b, double c) {
+    return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
+}
 template <typename T>
 __device__ inline typename Mm<T>::v4 zero4() { return typename Mm<T>::v4{0, 0, 0, 0}; }
 // Sum over the four lane groups (lanes l, l + 16, l + 32, l + 48), in every lane.
-__device__ inline double sum_groups(double v) { return Mm<double>::fours(1.0, v, 0.0); }
+__device__ inline double sum_groups(double v) { return fours(1.0, v, 0.0); }
 __device__ inline float sum_groups(float v) { return Mm<float>::mul(1.f, v, zero4<float>())[0]; }
 
 // 2^x for |x| < 2^31: x = n + f with n the nearest integer, 2^f by a polynomial of
@@ -450,10 +449,20 @@ __device__ inline T sum16(T v) {
     return v;
 }
 
-// Rows n a wave works on at once: as many as keep x, V and the row values of
-// 2 R (row, column block) pairs within 256 registers.
-// (fp32 would hold four up to Q = 16: 5% faster at M >= 700, 5-70% slower below).
-constexpr int grad_rows(int ks, size_t elem) { return ks <= (elem == 8 ? 5 : 12) ? 2 : 1; }
+// Rows n a wave works on at once: each serves the same z and Gc operands again, and keeps x, U
+// and its row values for 2 column blocks in registers.  Two where that measured faster than one
+// (fp64: 15.6 ms with two and 15.0 with one at Q = 20; fp32 would hold four up to Q = 16: 5%
+// faster at M >= 700, 5-70% slower below).
+constexpr int grad_rows(int ks, size_t elem) { return ks <= (elem == 8 ? 4 : 12) ? 2 : 1; }
+
+// The reference c of a row's second product: where a Gaussian with the centre and variance of
+// Z, weighted by the row's (mu, 1 / w2), has its mean.  Near the centre where Z spreads
+// less than the row sees, near mu where it spreads more; mu where that is not finite.
+template <typename T>
+__device__ inline T reference(T mu, T w2, T centre, T var) {
+    const T s = var * w2, c = centre + (mu - centre) * (s / (T(1) + s));
+    return fabs(c) <= T(1e38) ? c : mu;
+}
 
 struct GradGeo {
     int nw;          // waves per workgroup (each two column blocks)
@@ -468,10 +477,23 @@ constexpr int kGradC = 2;      // column blocks per wave
 
 // With W_n = Gc o 2^E'_n, r_m = sum_m' W, V_m = sum_m' W d_m', t = dL/dPsi1 o Psi1,
 // every gradient is a sum over (n, m) of terms in (r, V, t) (the formulas stand at
-// the generic pairs kernel).  A wave owns 32 columns m and walks the blocks of
+// the generic pairs kernel).  dZ and dl take n_m = d_m r_m - V_m = sum_m' W (z_m' - z_m),
+// of the size of the spacing of the Z whose W matters, while d r and V are of that of
+// d: where S >> l^2 their difference loses sqrt(l^2 + 2 S) / l of its precision.  So the
+// second product is U_m = sum_{m' != m} W (z_m' - c) with a reference c per row and
+// dimension that is near those Z (reference()), and n = U - (z_m - c) (r - W[m, m]),
+// d r + V = 2 d r - n.  The pair (m, m), which adds nothing to n, stays out of U and of
+// its r: where Z is spread over many lengthscales it is most of r.  Against the difference
+// of d r and V (long-double reference, S in 0.5 .. 2, N = 300, M = 64, relative error of dl):
+// Q = 10, l = 0.005, Z within l: fp32 2.7e-4 -> 4.4e-6, fp64 6.5e-13 -> 2.4e-14; Q = 12,
+// l = 0.002: 4.6e-4 -> 2.3e-6, 7.9e-13 -> 1.3e-14; Q = 10, l = 0.05, Z spread over 20 l in
+// groups of neighbours: 1.5e-5 -> 1.6e-6, 3.2e-14 -> 2.4e-14.  It costs 1-8% of the
+// gradients' time up to Q = 48 (fp64 14.8 -> 15.0 ms at N = 100,000, M = 256, Q = 20; fp32
+// 1.20 -> 1.23 ms at N = 3,001, M = 700, Q = 12) and 12% past it in fp64.
+// A wave owns 32 columns m and walks the blocks of
 // 16 rows m': a tile of W leaves the exponent's product in exactly the layout
-// that the second product, V^T += d^T W, takes as its right operand, and V comes
-// out in the layout of x, so neither goes through LDS.  Each (m', d, Gc) operand
+// that the second product, U^T += (z - c)^T W, takes as its right operand, and U comes
+// out in the layout of x, so neither goes through LDS.  Each (m', z, Gc) operand
 // serves 2 R products.  r is summed on the vector unit: 4 additions a tile, where a
 // column of ones would cost 64 cycles.  Sums over m (dmu, dS, dl) go through the
 // lanes and then the waves in a fixed order; dZ stays in LDS slots that one lane
@@ -482,14 +504,15 @@ __global__ __launch_bounds__(512) void tiles_grad_kernel(
     const T *__restrict__ mu, const T *__restrict__ S, const T *__restrict__ Z,
     const T *__restrict__ w1t, const T *__restrict__ w2t, const T *__restrict__ lp1,
     const T *__restrict__ lp2, Hyp<T> h, const T *__restrict__ G1,
-    const T *__restrict__ Gc, T *__restrict__ dmu, T *__restrict__ dS,
+    const T *__restrict__ Gc, const T *__restrict__ zref, T *__restrict__ dmu, T *__restrict__ dS,
     T *__restrict__ colpart, T *__restrict__ rowpart) {
     if (gate && gate[0] == 0) return;
     using v4 = typename Mm<T>::v4;
     constexpr T kLog2 = T(kLog2e), kLim = slow_limit<T>();
-    // T16 tiles of 16 dimensions and T4 of 4 hold V; QP: that width (zero past Q)
+    // T16 tiles of 16 dimensions and T4 of 4 hold U; QP: that width (zero past Q)
     constexpr int T16 = Mm<T>::kFours ? KS / 4 : (KS + 3) / 4, T4 = Mm<T>::kFours ? KS % 4 : 0;
     constexpr int NT = T16 + T4, QP = 16 * T16 + 4 * T4, QK = 4 * KS, ZS = QP + 1, R = grad_rows(KS, sizeof(T));
+    constexpr int RV = 5;                // values staged for a row and dimension
     extern __shared__ double sm_[];
     T *sm = reinterpret_cast<T *>(sm_);
     const int tid = threadIdx.x, nthr = blockDim.x, nw = nthr >> 6;
@@ -499,8 +522,8 @@ __global__ __launch_bounds__(512) void tiles_grad_kernel(
     T *sz = sm;                          // [wrows][ZS]
     T *sb = sz + wrows * ZS;             // [R][wrows]: b of the rows, permuted in each block
     T *sbc = sb + R * wrows;             // [R][wcols]: b of the workgroup's columns
-    T *srow = sbc + R * wcols;           // [R][4][QP]: mu, w1, w2, S
-    T *slp = srow + R * 4 * QP;          // [R][2]: lp1, lp2
+    T *srow = sbc + R * wcols;           // [R][RV][QP]: mu, w1, w2, S, c
+    T *slp = srow + R * RV * QP;         // [R][2]: lp1, lp2
     T *sred = slp + R * 2;               // [nw][R][3 QP + 2]
     T *sdl = sred + nw * R * (3 * QP + 2);  // [R][QP + 1]
     T *shyp = sdl + R * (QP + 1);        // [3][QP]: 1/l^2, l, 1/l^3
@@ -535,10 +558,12 @@ __global__ __launch_bounds__(512) void tiles_grad_kernel(
     for (int64_t base = r0; base < r1; base += R) {
         const int cnt = (int)min<int64_t>(R, r1 - base);
         __syncthreads();
-        for (int i = tid; i < R * 4 * QP; i += nthr) {
-            const int r = i / (4 * QP), k = (i / QP) & 3, q = i % QP;
-            const T *src = k == 0 ? mu : k == 1 ? w1t : k == 2 ? w2t : S;
-            const T v = src[(base + min(r, cnt - 1)) * Q + min(q, Q - 1)];
+        for (int i = tid; i < R * RV * QP; i += nthr) {
+            const int r = i / (RV * QP), k = i / QP - r * RV, q = i % QP, qc = min(q, Q - 1);
+            const int64_t j = (base + min(r, cnt - 1)) * Q + qc;
+            const T *src = k == 1 ? w1t : k == 2 ? w2t : k == 3 ? S : mu;
+            T v = src[j];
+            if (k == 4 && Gc) v = reference(v, w2t[j], zref[qc], zref[Q + qc]);
             srow[i] = q < Q ? v : T(0.0);
         }
         if (tid < R) {
@@ -549,7 +574,7 @@ __global__ __launch_bounds__(512) void tiles_grad_kernel(
         __syncthreads();
         // b of row r and inducing input m
         auto b_of = [&](int r, const T *z) {
-            const T *xr = srow + r * 4 * QP, *w = xr + 2 * QP;
+            const T *xr = srow + r * RV * QP, *w = xr + 2 * QP;
             T s = T(0.0);
 #pragma unroll 4
             for (int q = 0; q < QK; ++q) {
@@ -570,9 +595,9 @@ __global__ __launch_bounds__(512) void tiles_grad_kernel(
                 sbc[i] = s;
                 if (!(fabs(s) < kLim)) sslow[r] = 1;
             }
-        T x[R][kGradC][KS], rs[R][kGradC];
-        v4 V16[R][kGradC][T16 > 0 ? T16 : 1];
-        T V4[R][kGradC][T4 > 0 ? T4 : 1];
+        T x[R][kGradC][KS], rs[R][kGradC], rd[R][kGradC];   // rs: sums of W over m' != m, rd: W[m, m]
+        v4 U16[R][kGradC][T16 > 0 ? T16 : 1];
+        T U4[R][kGradC][T4 > 0 ? T4 : 1];
         // the Psi1 terms t = dL/dPsi1 o Psi1: lane l has rows 2 u + l / 32, column l % 32
         T tval[(R + 1) / 2];
 #pragma unroll
@@ -580,7 +605,7 @@ __global__ __launch_bounds__(512) void tiles_grad_kernel(
             tval[u] = 0;
             const int r = 2 * u + (lane >> 5), m = cb0 * 16 + (lane & 31);
             if (G1 && r < cnt && m < M) {
-                const T *xr = srow + r * 4 * QP, *w = xr + QP;
+                const T *xr = srow + r * RV * QP, *w = xr + QP;
                 T s = 0;
 #pragma unroll 4
                 for (int q = 0; q < QK; ++q) {
@@ -594,18 +619,18 @@ __global__ __launch_bounds__(512) void tiles_grad_kernel(
         for (int r = 0; r < R; ++r)
 #pragma unroll
             for (int c = 0; c < kGradC; ++c) {
-                rs[r][c] = T(0.0);
+                rs[r][c] = rd[r][c] = T(0.0);
                 const int m = min((cb0 + c) * 16 + c16, M - 1);
 #pragma unroll
                 for (int s = 0; s < KS; ++s) {
                     const int q = 4 * s + g;
-                    const T d = srow[r * 4 * QP + q] - zcol(m, q);
-                    x[r][c][s] = -T(0.5) * kLog2 * srow[r * 4 * QP + 2 * QP + q] * d;
+                    const T d = srow[r * RV * QP + q] - zcol(m, q);
+                    x[r][c][s] = -T(0.5) * kLog2 * srow[r * RV * QP + 2 * QP + q] * d;
                 }
 #pragma unroll
-                for (int t = 0; t < T16; ++t) V16[r][c][t] = zero4<T>();
+                for (int t = 0; t < T16; ++t) U16[r][c][t] = zero4<T>();
 #pragma unroll
-                for (int t = 0; t < T4; ++t) V4[r][c][t] = T(0.0);
+                for (int t = 0; t < T4; ++t) U4[r][c][t] = T(0.0);
             }
         if (Gc) {
             T bi[R][kGradC];
@@ -619,7 +644,7 @@ __global__ __launch_bounds__(512) void tiles_grad_kernel(
                 }
                 for (int i = tid; i < R * wrows; i += nthr) {
                     const int r = i / wrows, j = i - r * wrows;
-                    const T *xr = srow + r * 4 * QP, *w = xr + 2 * QP, *z = sz + j * ZS;
+                    const T *xr = srow + r * RV * QP, *w = xr + 2 * QP, *z = sz + j * ZS;
                     T s = T(0.0);
 #pragma unroll 4
                     for (int q = 0; q < QK; ++q) {
@@ -644,15 +669,15 @@ __global__ __launch_bounds__(512) void tiles_grad_kernel(
 #pragma unroll
                 for (int r = 0; r < R; ++r)
                     slow[r] = __builtin_amdgcn_readfirstlane(sslow[r] | sslow[R + r]) != 0;
-                T muA[R][KS], muB[R][NT];
+                T muA[R][KS], cB[R][NT];
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
 #pragma unroll
-                    for (int s = 0; s < KS; ++s) muA[r][s] = srow[r * 4 * QP + 4 * s + g];
+                    for (int s = 0; s < KS; ++s) muA[r][s] = srow[r * RV * QP + 4 * s + g];
 #pragma unroll
                     for (int t = 0; t < NT; ++t)
-                        muB[r][t] = srow[r * 4 * QP + (t < T16 ? 16 * t + c16
-                                                               : 16 * T16 + 4 * (t - T16) + (lane & 3))];
+                        cB[r][t] = srow[(r * RV + 4) * QP + (t < T16 ? 16 * t + c16
+                                                                     : 16 * T16 + 4 * (t - T16) + (lane & 3))];
                 }
                 const int jn = min(wrows, Mp - w0) / 16;
                 // NC: the wave's column blocks, so that their tiles interleave
@@ -704,8 +729,8 @@ __global__ __launch_bounds__(512) void tiles_grad_kernel(
                                         W[c][v] = T(0.0);
                                         if (m < M && mp < M)
                                             W[c][v] = G[c][v] *
-                                                      direct_pair(srow + r * 4 * QP,
-                                                                  srow + r * 4 * QP + 2 * QP,
+                                                      direct_pair(srow + r * RV * QP,
+                                                                  srow + r * RV * QP + 2 * QP,
                                                                   slp[2 * r + 1], Z + (int64_t)m * Q,
                                                                   Z + (int64_t)mp * Q, Q);
                                     }
@@ -713,23 +738,33 @@ __global__ __launch_bounds__(512) void tiles_grad_kernel(
                             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                             for (int c = 0; c < NC; ++c)
+                                if (__builtin_expect(w0 + 16 * J == (cb0 + c) * 16, 0)) {  // uniform: on the diagonal
+#pragma unroll
+                                    for (int v = 0; v < 4; ++v)
+                                        if (Mm<T>::row(v, g) == c16) {
+                                            rd[r][c] = W[c][v];
+                                            W[c][v] = T(0.0);
+                                        }
+                                }
+#pragma unroll
+                            for (int c = 0; c < NC; ++c)
                                 rs[r][c] += (W[c][0] + W[c][1]) + (W[c][2] + W[c][3]);
 #pragma unroll
                             for (int v = 0; v < 4; ++v) {
-                                T dB[NT];
+                                T uB[NT];
 #pragma unroll
                                 for (int t = 0; t < NT; ++t)
-                                    dB[t] = muB[r][t] -
-                                            sz[(16 * J + Mm<T>::row(v, g)) * ZS +
-                                               (t < T16 ? 16 * t + c16 : 16 * T16 + 4 * (t - T16) + (lane & 3))];
+                                    uB[t] = sz[(16 * J + Mm<T>::row(v, g)) * ZS +
+                                               (t < T16 ? 16 * t + c16 : 16 * T16 + 4 * (t - T16) + (lane & 3))] -
+                                            cB[r][t];
 #pragma unroll
                                 for (int c = 0; c < NC; ++c) {
 #pragma unroll
                                     for (int t = 0; t < T16; ++t)
-                                        V16[r][c][t] = Mm<T>::mul(W[c][v], dB[t], V16[r][c][t]);
+                                        U16[r][c][t] = Mm<T>::mul(W[c][v], uB[t], U16[r][c][t]);
 #pragma unroll
                                     for (int t = 0; t < T4; ++t)
-                                        V4[r][c][t] = Mm<T>::fours(W[c][v], dB[T16 + t], V4[r][c][t]);
+                                        U4[r][c][t] = fours(W[c][v], uB[T16 + t], U4[r][c][t]);
                                 }
                             }
                         }
@@ -741,8 +776,8 @@ __global__ __launch_bounds__(512) void tiles_grad_kernel(
                     tiles(std::integral_constant<int, kGradC>{});
             }
         }
-        // epilogue: of a 16-wide tile t lane (g, c16) holds (m = 4 v + g, q = 16 t + c16),
-        // of a 4-wide one (m = (lane & 12) + g, q = 16 T16 + 4 t + (lane & 3))
+        // epilogue: of a 16-wide tile t lane (g, c16) holds (m = row(v, g),
+        // q = 16 t + c16), of a 4-wide one (m = (lane & 12) + g, q = 16 T16 + 4 t + (lane & 3))
         if (ncol > 0) {
             int le = lane;  // opaque: the epilogue's addresses are formed here, not kept over the tiles
             asm volatile("" : "+v"(le));
@@ -751,17 +786,17 @@ __global__ __launch_bounds__(512) void tiles_grad_kernel(
             for (int r = 0; r < R; ++r) {
                 if (r >= cnt) break;  // uniform
                 T *red = sred + (wv * R + r) * (3 * QP + 2);
-                T tc[kGradC];
-                v4 r16[kGradC];
-                T r4[kGradC], rt = T(0.0), tt = T(0.0);
+                v4 r16[kGradC], dm16[kGradC];
+                T r4[kGradC], dm4[kGradC], rt = T(0.0), tt = T(0.0);
 #pragma unroll
                 for (int c = 0; c < kGradC; ++c) {
-                    if (c >= ncol) rs[r][c] = T(0.0);
-                    tc[c] = __shfl(tval[r / 2], 32 * (r & 1) + 16 * c + ce);
-                    rt += rs[r][c];
-                    tt += tc[c];
+                    if (c >= ncol) rs[r][c] = rd[r][c] = T(0.0);
+                    rt += rs[r][c] + rd[r][c];
+                    tt += __shfl(tval[r / 2], 32 * (r & 1) + 16 * c + ce);
                     if (T16 > 0) r16[c] = Mm<T>::mul(rs[r][c], T(1.0), zero4<T>());
-                    if (T4 > 0) r4[c] = Mm<T>::fours(rs[r][c], T(1), T(0));
+                    if (T4 > 0) r4[c] = fours(rs[r][c], T(1.0), T(0.0));
+                    if (T16 > 0) dm16[c] = Mm<T>::mul(rd[r][c], T(1.0), zero4<T>());
+                    if (T4 > 0) dm4[c] = fours(rd[r][c], T(1.0), T(0.0));
                 }
                 rt = sum16(sum_groups(rt));
                 tt = sum16(tt);
@@ -773,8 +808,8 @@ __global__ __launch_bounds__(512) void tiles_grad_kernel(
                 for (int t = 0; t < NT; ++t) {
                     const bool wide = t < T16;
                     const int q = wide ? 16 * t + ce : 16 * T16 + 4 * (t - T16) + (le & 3);
-                    const T *row = srow + r * 4 * QP + q;
-                    const T xm = row[0], a1 = row[QP], a2 = row[2 * QP];
+                    const T *row = srow + r * RV * QP + q;
+                    const T xm = row[0], a1 = row[QP], a2 = row[2 * QP], cq = row[4 * QP];
                     const T il2 = shyp[q], l = shyp[QP + q], il3 = shyp[2 * QP + q];
                     T sp0 = T(0.0), st0 = T(0.0), su = T(0.0), sn = T(0.0), sx = T(0.0);
 #pragma unroll
@@ -786,9 +821,10 @@ __global__ __launch_bounds__(512) void tiles_grad_kernel(
                             const int m = min((cb0 + c) * 16 + ml, M - 1);
                             const T rm = wide ? r16[c][v] : r4[c];
                             const T tm = __shfl(tval[r / 2], 32 * (r & 1) + 16 * c + ml);
-                            const T Vq = wide ? V16[r][c][wide ? t : 0][v] : V4[r][c][wide ? 0 : t - T16];
-                            const T d = xm - zcol(m, q), dr = d * rm, td = tm * d;
-                            const T p = dr + Vq, n = dr - Vq;
+                            const T U = wide ? U16[r][c][wide ? t : 0][v] : U4[r][c][wide ? 0 : t - T16];
+                            const T rmm = wide ? dm16[c][v] : dm4[c];
+                            const T z = zcol(m, q), d = xm - z, dr = d * (rm + rmm), td = tm * d;
+                            const T n = fma(cq - z, rm, U), p = T(2.0) * dr - n;
                             sp0 += dr;
                             st0 += td;
                             su = fma(d, p, su);
@@ -829,7 +865,7 @@ __global__ __launch_bounds__(512) void tiles_grad_kernel(
                 Rt += red[3 * QP];
                 Tt += red[3 * QP + 1];
             }
-            const T *row = srow + r * 4 * QP + q;
+            const T *row = srow + r * RV * QP + q;
             const T a1 = row[QP], a2 = row[2 * QP], sv = row[3 * QP], il = T(1.0) / shyp[QP + q];
             const int64_t o = ((int64_t)blockIdx.x * 2 * N + base + r) * Q + q;
             dmu[o] = v0;
@@ -859,9 +895,9 @@ int ks_of(int64_t Q) {
 }
 
 size_t grad_lds(int ks, int nw, int wrows, size_t elem) {
-    // as in the kernel: fp32 V comes in tiles of 16 dimensions only
+    // as in the kernel: fp32 U comes in tiles of 16 dimensions only
     const int QP = elem == 8 ? 4 * ks : (ks + 3) / 4 * 16, R = grad_rows(ks, elem), wcols = nw * kGradC * 16;
-    const size_t d = (size_t)wrows * (QP + 1) + R * wrows + R * wcols + R * 4 * QP + R * 2 +
+    const size_t d = (size_t)wrows * (QP + 1) + R * wrows + R * wcols + R * 5 * QP + R * 2 +
                      (size_t)nw * R * (3 * QP + 2) + R * (QP + 1) + 3 * QP + (size_t)wcols * QP;
     return align_up(d * elem, 8) + 2 * R * 4 + 8;
 }
@@ -1027,8 +1063,8 @@ hipError_t tiles_psi2(const Shape &s, const T *mu, const T *Z, const T *w1, cons
     return hipGetLastError();
 }
 
-// Region: Gc = (G2 + G2^T)/2 o 2^C [Mp x Mp], row gradients [groups][2][N][Q] (only when groups > 1),
-// dZ slabs [chunks][M][Q], row sums [chunks][groups][Q + 1].
+// Region: Gc = (G2 + G2^T)/2 o 2^C [Mp x Mp], centre and variance of Z [2][Q], row gradients
+// [groups][2][N][Q] (only when groups > 1), dZ slabs [chunks][M][Q], row sums [chunks][groups][Q + 1].
 TilesGradPlan tiles_grad_plan(const Shape &s, size_t budget, size_t elem) {
     TilesGradPlan p{};
     GradGeo g = grad_geo(s, elem);
@@ -1037,6 +1073,7 @@ TilesGradPlan tiles_grad_plan(const Shape &s, size_t budget, size_t elem) {
     size_t o = 0;
     auto take = [&](size_t n) { size_t r = o; o = align_up(o + n * elem, 256); return r; };
     p.off_gc = take(Mp * Mp);
+    p.off_ref = take(2 * s.Q);
     p.off_rowg = take(g.groups > 1 ? (size_t)g.groups * 2 * s.N * s.Q : 0);
     // as many chunks as the region has room for
     const size_t per = (size_t)(s.M * s.Q + g.groups * (s.Q + 1)) * elem;
@@ -1080,7 +1117,8 @@ hipError_t tiles_psi2_grads(const Shape &s, const TilesGradPlan &p, const T *mu,
         if (e != hipSuccess) return e;                                                            \
         tiles_grad_kernel<T, KS><<<grid, p.nw * 64, p.lds, st>>>(                                 \
             gate, s.N, (int)s.M, (int)s.Q, nb, p.wrows, p.nwin, p.rows, mu, S, Z, w1, w2, lp1,    \
-            lp2, h, G1, Gc, om, os, at<T>(ws, p.off_colp), at<T>(ws, p.off_rowp));                \
+            lp2, h, G1, Gc, at<T>(ws, p.off_ref), om, os, at<T>(ws, p.off_colp),                  \
+            at<T>(ws, p.off_rowp));                                                               \
         break;                                                                                    \
     }
     switch (ks_of(s.Q)) {

@@ -1,0 +1,55 @@
+"""Precision of the 16 x 16 tile kernels where their sums could cancel or drift, against
+the fp64 oracle."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle  # noqa: E402
+import paper_1410_4984_amd as gpps  # noqa: E402
+from paper_1410_4984_amd import synth  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+def t(a, dtype):
+    return torch.tensor(a, dtype=dtype, device=DEV)
+
+
+def grads(inp, dtype):
+    g = gpps.psi_grads(t(inp["mu"], dtype), t(inp["S"], dtype), t(inp["Z"], dtype), inp["sigma_f2"], inp["l"],
+                       inp["dL_dpsi0"], t(inp["dL_dPsi1"], dtype), t(inp["dL_dPsi2"], dtype), path="generic")
+    torch.cuda.synchronize()
+    return {k: v.double().cpu().numpy() for k, v in g.items()}
+
+
+def rel(a, b):
+    a, b = np.ravel(a), np.ravel(np.asarray(b, np.float64))
+    return np.linalg.norm(a - b) / np.linalg.norm(b)
+
+
+# Variances far above l^2 and inducing inputs a lengthscale apart: dZ and dl are sums of
+# W (z_m' - z_m), sqrt(S) / l (up to 600 here) times smaller than the sums of W (mu - z)
+# whose difference they are.  The exponents are up to 6 log(1 + 2 S / l^2) = 85 in
+# magnitude, so their rounding leaves 85 2^-24 = 5e-6 of W in fp32 and 1e-14 in fp64; four
+# times that, and in fp64 the oracle's own 5e-14 besides.
+@pytest.mark.parametrize("dtype,tol", [(torch.float32, 2e-5), (torch.float64, 1e-13)])
+@pytest.mark.parametrize("Q,l,groups", [(10, 0.005, 1), (12, 0.002, 1), (10, 0.05, 16), (20, 0.05, 1)])
+def test_short_lengthscales_under_wide_variances(Q, l, groups, dtype, tol):
+    print(f"[Q={Q} l={l} groups={groups} {dtype}]", flush=True)
+    rng = np.random.default_rng(Q + groups)
+    N, M = 300, 64
+    c = 0.3 * rng.standard_normal((groups, Q)) if groups == 1 else rng.standard_normal((groups, Q))
+    Z = (c[:, None, :] + l * rng.standard_normal((groups, M // groups, Q))).reshape(M, Q)
+    A = rng.standard_normal((M, M))
+    inp = synth.to_f32({"mu": c.mean(0) + 0.7 * rng.standard_normal((N, Q)), "S": rng.uniform(0.5, 2.0, (N, Q)),
+                        "Z": Z[rng.permutation(M)], "l": np.full(Q, l), "sigma_f2": 1.25, "dL_dpsi0": 0.75,
+                        "dL_dPsi1": rng.standard_normal((N, M)), "dL_dPsi2": 0.5 * (A + A.T)})
+    ref = oracle.psi_grads(inp["mu"], inp["S"], inp["Z"], inp["sigma_f2"], inp["l"], inp["dL_dpsi0"],
+                           inp["dL_dPsi1"], inp["dL_dPsi2"])
+    got = grads(inp, dtype)
+    err = {k: rel(got[k], v) for k, v in ref.items()}
+    print({k: f"{e:.1e}" for k, e in err.items()}, flush=True)
+    assert max(err.values()) <= tol, err
