@@ -53,3 +53,27 @@ def test_short_lengthscales_under_wide_variances(Q, l, groups, dtype, tol):
     err = {k: rel(got[k], v) for k, v in ref.items()}
     print({k: f"{e:.1e}" for k, e in err.items()}, flush=True)
     assert max(err.values()) <= tol, err
+
+
+# Equal rows: every addition to dZ, dl and dsf2 may round the same way, the k-th of n by up
+# to k / n 2^-p of their sum, so n additions in one go by n / 2 2^-p.  The kernels add 128
+# rows, then the chunk's groups of 128 (at most 20 here), then the chunks (512 / 8 and 8):
+# below 128 2^-p with the terms' own scalings.  One row's gradient times N is the reference:
+# the terms are the same.
+@pytest.mark.parametrize("dtype,ulp", [(torch.float32, 2.0 ** -24), (torch.float64, 2.0 ** -53)])
+@pytest.mark.parametrize("N,M,Q", [(40000, 2048, 5), (65536, 300, 20), (131, 40, 6), (257, 200, 4)])
+def test_gradient_sums_of_many_equal_rows(N, M, Q, dtype, ulp):
+    print(f"[equal rows N={N} M={M} Q={Q} {dtype}]", flush=True)
+    rng = np.random.default_rng(N + M)
+    row = {"mu": 0.3 * rng.standard_normal((1, Q)), "S": rng.uniform(0.1, 0.5, (1, Q))}
+    Z, l = t(0.5 * rng.standard_normal((M, Q)), dtype), rng.uniform(0.8, 1.6, Q)
+    G1, G2 = t(rng.uniform(0.5, 1.0, (1, M)), dtype), t(rng.uniform(0.5, 1.0, (M, M)) / M, dtype)
+    out = []
+    for n in (1, N):
+        g = gpps.psi_grads(*(t(row[k], dtype).repeat(n, 1) for k in ("mu", "S")), Z, 1.25, l, 0.0,
+                           G1.repeat(n, 1), G2, path="generic")
+        torch.cuda.synchronize()
+        out.append({k: g[k].double().cpu().numpy() for k in ("dZ", "dl", "dsigma_f2")})
+    err = {k: np.abs(out[1][k] / (N * out[0][k]) - 1.0).max() / ulp for k in out[0]}
+    print({k: f"{e:.0f} ulp" for k, e in err.items()}, flush=True)
+    assert max(err.values()) <= 128, err
