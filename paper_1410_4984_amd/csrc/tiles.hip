@@ -11,7 +11,9 @@
 // (Gc = G2s o 2^C).  Both operands of the contraction are local differences, so
 // no term is larger than the exponents of the pairs that matter: where
 // d_m ~ -d_m' makes b_m cancel against the product, C is more negative than
-// either.
+// either.  The product is summed from zero and b_m + b_m' added last, so that its 4 k-steps
+// round at half of the exponent's size or less: started from b_m + b_m' they left 2.7e-15
+// of Psi2 in fp64 at Q = 30 (N = 200, M = 64), 1.2e-15 so (the vector kernels: 2.4e-15).
 //
 // What bounds these kernels is the SIMDs' issue rate.  In fp64 a 16 x 16 x 4 product occupies a SIMD for 64 cycles and no vector
 // instruction issues meanwhile (measured: 8 FMAs behind each product add 8 FMAs'
@@ -307,13 +309,11 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2) void tiles_fwd_kernel(
 #pragma unroll
                     for (int c = 0; c < kFwdC; ++c) {
                         if (cb + c > rb + a || cb + c >= nb) break;  // uniform: below the diagonal
-                        v4 e;
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) e[v] = br[v] + bc[c];
+                        v4 e = zero4<T>();
 #pragma unroll
                         for (int s = 0; s < KS; ++s) e = Mm<T>::mul(da[s], x[c][s], e);
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) acc[a][c][v] += exp2_fast(e[v]);
+                        for (int v = 0; v < 4; ++v) acc[a][c][v] += exp2_fast(e[v] + (br[v] + bc[c]));
                     }
                 } else {
                     const int64_t n = base + r;
@@ -574,16 +574,22 @@ __global__ __launch_bounds__(512) void tiles_grad_kernel(
         }
         if (tid < 2 * R) sslow[tid] = 0;
         __syncthreads();
-        // b of row r and inducing input m
-        auto b_of = [&](int r, const T *z) {
-            const T *xr = srow + r * RV * QP, *w = xr + 2 * QP;
-            T s = T(0.0);
-#pragma unroll 4
-            for (int q = 0; q < QK; ++q) {
-                const T d = xr[q] - z[min(q, Q - 1)];
-                s = fma(w[q] * d, d, s);
-            }
-            return kLog2 * (T(0.5) * slp[2 * r + 1] - T(0.25) * s);
+        // sum over q of w (x - z)^2, w the row's w1 or w2, as two sums side by side (rounding)
+        auto squares = [&](int r, int which, auto z) {
+            const T *xr = srow + r * RV * QP, *w = xr + which * QP;
+            T s[2] = {0, 0};
+#pragma unroll 2
+            for (int q = 0; q < QK / 2; ++q)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const T d = xr[2 * q + j] - z(2 * q + j);
+                    s[j] = fma(w[2 * q + j] * d, d, s[j]);
+                }
+            return s[0] + s[1];
+        };
+        // b of row r and an inducing input
+        auto b_of = [&](int r, auto z) {
+            return kLog2 * (T(0.5) * slp[2 * r + 1] - T(0.25) * squares(r, 2, z));
         };
         // place of row j in sb: row(v, g) of a block at 4 g + v, so that a lane's four
         // are contiguous
@@ -593,7 +599,8 @@ __global__ __launch_bounds__(512) void tiles_grad_kernel(
         if (nwin > 1)  // else the columns are among the rows of the one window
             for (int i = tid; i < R * wcols; i += nthr) {
                 const int r = i / wcols;
-                const T s = b_of(r, Z + (int64_t)min(m0 + i - r * wcols, M - 1) * Q);
+                const T *z = Z + (int64_t)min(m0 + i - r * wcols, M - 1) * Q;
+                const T s = b_of(r, [&](int q) { return z[min(q, Q - 1)]; });
                 sbc[i] = s;
                 if (!(fabs(s) < kLim)) sslow[r] = 1;
             }
@@ -606,16 +613,9 @@ __global__ __launch_bounds__(512) void tiles_grad_kernel(
         for (int u = 0; u < (R + 1) / 2; ++u) {
             tval[u] = 0;
             const int r = 2 * u + (lane >> 5), m = cb0 * 16 + (lane & 31);
-            if (G1 && r < cnt && m < M) {
-                const T *xr = srow + r * RV * QP, *w = xr + QP;
-                T s = 0;
-#pragma unroll 4
-                for (int q = 0; q < QK; ++q) {
-                    const T d = xr[q] - zcol(m, q);
-                    s = fma(w[q] * d, d, s);
-                }
-                tval[u] = G1[(base + r) * M + m] * dexp(slp[2 * r] - T(0.5) * s);
-            }
+            if (G1 && r < cnt && m < M)
+                tval[u] = G1[(base + r) * M + m] *
+                          dexp(slp[2 * r] - T(0.5) * squares(r, 1, [&](int q) { return zcol(m, q); }));
         }
 #pragma unroll
         for (int r = 0; r < R; ++r)
@@ -646,14 +646,7 @@ __global__ __launch_bounds__(512) void tiles_grad_kernel(
                 }
                 for (int i = tid; i < R * wrows; i += nthr) {
                     const int r = i / wrows, j = i - r * wrows;
-                    const T *xr = srow + r * RV * QP, *w = xr + 2 * QP, *z = sz + j * ZS;
-                    T s = T(0.0);
-#pragma unroll 4
-                    for (int q = 0; q < QK; ++q) {
-                        const T d = xr[q] - z[q];
-                        s = fma(w[q] * d, d, s);
-                    }
-                    s = kLog2 * (T(0.5) * slp[2 * r + 1] - T(0.25) * s);
+                    const T s = b_of(r, [&](int q) { return sz[j * ZS + q]; });
                     sb[r * wrows + b_at(j)] = s;
                     if (!(fabs(s) < kLim)) sslow[R + r] = 1;
                 }
@@ -703,11 +696,7 @@ __global__ __launch_bounds__(512) void tiles_grad_kernel(
                                 T dA[KS];
                                 v4 e[NC];
 #pragma unroll
-                                for (int v = 0; v < 4; ++v) {
-                                    const T b = sb[r * wrows + 16 * J + 4 * g + v];
-#pragma unroll
-                                    for (int c = 0; c < NC; ++c) e[c][v] = b + bi[r][c];
-                                }
+                                for (int c = 0; c < NC; ++c) e[c] = zero4<T>();
 #pragma unroll
                                 for (int s = 0; s < KS; ++s) dA[s] = muA[r][s] - zA[s];
 #pragma unroll
@@ -717,7 +706,10 @@ __global__ __launch_bounds__(512) void tiles_grad_kernel(
 #pragma unroll
                                 for (int c = 0; c < NC; ++c)
 #pragma unroll
-                                    for (int v = 0; v < 4; ++v) W[c][v] = G[c][v] * exp2_fast(e[c][v]);
+                                    for (int v = 0; v < 4; ++v) {
+                                        const T b = sb[r * wrows + 16 * J + 4 * g + v] + bi[r][c];
+                                        W[c][v] = G[c][v] * exp2_fast(e[c][v] + b);
+                                    }
                             } else {
                                 int l = lane;  // opaque: nothing of this branch is kept outside it
                                 asm volatile("" : "+v"(l));

@@ -77,3 +77,25 @@ def test_gradient_sums_of_many_equal_rows(N, M, Q, dtype, ulp):
     err = {k: np.abs(out[1][k] / (N * out[0][k]) - 1.0).max() / ulp for k in out[0]}
     print({k: f"{e:.0f} ulp" for k, e in err.items()}, flush=True)
     assert max(err.values()) <= 128, err
+
+
+# The exponent of Psi2 where few rows count, of a size of 32 .. 64 in powers of two here: it is
+# rounded once at that size, 0.29 ulp ln 2 = 1.4e-15 of Psi2, and the roundings at half of it
+# and below shall add no more than that again.  Reference in extended precision.
+def test_exponent_rounding_f64(Q=30, tol=2e-15):
+    N, M, L = 200, 64, np.longdouble
+    errs = []
+    for seed in range(6):
+        inp = synth.random_inputs(N, M, Q, seed=seed)
+        mu, S, Z, l = (inp[k].astype(L) for k in ("mu", "S", "Z", "l"))
+        C = -(((Z[:, None] - Z[None]) / l) ** 2).sum(-1) / 4
+        ref = np.zeros((M, M), L)
+        for n in range(N):
+            lp2 = 2 * np.log(L(inp["sigma_f2"])) - np.log1p(2 * S[n] / l**2).sum() / 2
+            d = mu[n] - (Z[:, None] + Z[None]) / 2
+            ref += np.exp(lp2 + C - (d * d / (l**2 + 2 * S[n])).sum(-1))
+        f64 = torch.float64
+        P2 = gpps.psi_stats(t(inp["mu"], f64), t(inp["S"], f64), t(inp["Z"], f64), inp["sigma_f2"], inp["l"])[2]
+        errs.append(float(np.linalg.norm(P2.cpu().numpy() - ref) / np.linalg.norm(ref)))
+    print([f"{e:.1e}" for e in errs], flush=True)
+    assert np.sqrt(np.mean(np.square(errs))) <= tol, errs
