@@ -81,13 +81,14 @@ typedef enum {
  * With neither path flag the call takes the fastest path that supports it: the
  * matrix-core path for F32 shapes within its limits (M rounded up to 32 at most
  * 512 with Q <= 31, or at most 256 with Q <= GPPS_MAX_Q_MFMA), the generic
- * path (whose arithmetic is the element type's own) otherwise and for the smallest calls (N (M^2 + 1000) (Q + 6) <= 1.5e7), whose
- * time is that of their launches.  GPPS_PATH_GENERIC forces the generic path; GPPS_PATH_MFMA
- * asks for the matrix-core path and fails with GPPS_ERR_PATH where it cannot
- * take the call.  The matrix-core path carries its operands as two-part fp16
- * values; a device-side range guard bounds them over every row first, and when a
- * bound leaves the fp16 range the call is computed by the generic kernels
- * instead, with either flag (see gpps_route_word_offset).  Calls with S = NULL
+ * path (whose arithmetic is the element type's own) otherwise and for the smallest
+ * calls (N (M^2 + 1000) (Q + 6) <= 1.5e7), whose time is that of their launches.
+ * GPPS_PATH_GENERIC forces the generic path; GPPS_PATH_MFMA asks for the matrix-core
+ * path and fails with GPPS_ERR_PATH where it cannot take the call.  The matrix-core
+ * path carries its operands as two-part fp16 values; a device-side range guard bounds
+ * them over every row first, and when a bound leaves the fp16 range the call is
+ * computed by the generic kernels instead, with either flag (see
+ * gpps_route_word_offset).  Calls with S = NULL
  * always take the known-input path. */
 #define GPPS_ACCUMULATE 1
 #define GPPS_PATH_GENERIC 2
@@ -129,8 +130,8 @@ gpps_status gpps_psi_stats_noalloc(gpps_dtype dt, int64_t N, int64_t M, int64_t 
  * Calls that take the matrix-core path (F32, S != NULL) write it: 0 when the
  * matrix cores computed the call, 1 when the range guard found an operand
  * outside the fp16 range and the generic kernels computed it.  Calls without a
- * path flag that were too small for the matrix-core path write 1.  Other calls
- * leave it unchanged.  Valid once the call's stream has been synchronised.
+ * path flag that were too small for the matrix-core path, whatever their operands,
+ * write 2.  Other calls leave it unchanged.  Valid once the call's stream has been synchronised.
  * SIZE_MAX for an invalid shape or dtype. */
 size_t gpps_route_word_offset(gpps_dtype dt, int64_t N, int64_t M, int64_t Q);
 

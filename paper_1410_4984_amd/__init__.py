@@ -126,9 +126,9 @@ def route_word_offset(dtype, N: int, M: int, Q: int) -> int:
 
 
 def route_taken(workspace, dtype, N: int, M: int, Q: int) -> int:
-    """The route word a matrix-core call left in ``workspace`` (synchronises):
-    0 = computed on the matrix cores, 1 = the range guard sent it to the
-    generic kernels."""
+    """The route word a call that could take the matrix-core path left in ``workspace``
+    (synchronises): 0 = computed on the matrix cores, 1 = the range guard sent it to
+    the generic kernels, 2 = without a path flag and too small for the matrix cores."""
     import torch
     off = route_word_offset(dtype, N, M, Q)
     torch.cuda.synchronize(workspace.device)

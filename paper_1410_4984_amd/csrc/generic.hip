@@ -165,7 +165,7 @@ __global__ __launch_bounds__(256) void pre_kernel(const int *__restrict__ gate, 
                                                   const T *__restrict__ Z, T *__restrict__ G2s,
                                                   unsigned sblocks, T *__restrict__ zref) {
     if (gate && gate[0] == 0) return;
-    if (mark && blockIdx.x == 0 && threadIdx.x == 0) mark[0] = 1;
+    if (mark && blockIdx.x == 0 && threadIdx.x == 0) mark[0] = 2;
     __shared__ T sl1[kPreElems], sl2[kPreElems];
     if (blockIdx.x >= rblocks + sblocks) {
         const int q = blockIdx.x - rblocks - sblocks;

@@ -54,7 +54,7 @@ class TimedScope {
 // matrix-core range guard rejects.  gate: NULL, or a device word; the kernels
 // then do their work only where it is nonzero (the matrix-core route word).  mark:
 // NULL, or the route word of a call that could have taken the matrix cores and was
-// too small for them, which gets 1.
+// too small for them, which gets 2.
 size_t generic_workspace_bytes(const Shape &s, size_t elem);
 
 template <typename T>

@@ -66,7 +66,7 @@ def dev(inp, dtype):
 
 def routes(ws, dtype, N, M, Q):
     """Route word of the last call on ws (0 matrix cores, 1 generic by the range
-    guard), or None where the call could not have taken the matrix-core path."""
+    guard, 2 too small), or None where the call could not have taken the matrix-core path."""
     if dtype != torch.float32 or gpps.get_path() == "generic":
         return None
     return gpps.route_taken(ws, dtype, N, M, Q)
@@ -631,14 +631,14 @@ def _range_case(name):
         l = rng.uniform(0.3, 0.6, Q)
         route = 0
     elif name == "tiny-l-trip":      # l ~ 1e-3, S ~ 1e-7: R / l ~ 2000
-        N, M, Q = 300, 20, 2
+        N, M, Q = 1500, 20, 2        # enough rows that a call without a path flag forms the guard
         mu = rng.standard_normal((N, Q))
         S = rng.uniform(1e-8, 1e-7, (N, Q))
         Z = mu[:M] + 1e-4 * rng.standard_normal((M, Q))
         l = np.array([1e-3, 2e-3])
         route = 1
     else:                            # "far-mu-trip": half the data 300 lengthscales away:
-        N, M, Q = 300, 24, 3         # the column bias and Gram operands leave the fp16 range
+        N, M, Q = 1200, 24, 3        # the column bias and Gram operands leave the fp16 range
         mu = rng.standard_normal((N, Q))
         mu[: N // 2] += 300.0
         S = rng.uniform(0.01, 0.5, (N, Q))
