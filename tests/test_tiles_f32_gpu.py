@@ -89,6 +89,7 @@ def test_f32_tiles_behind_the_range_guard():
     got, ref = call(inp, path=None), call(inp)
     for k, v in ref.items():
         assert np.array_equal(got[k], v), k
+    check(got, inp, "guard")
 
 
 def test_f32_far_rows():
