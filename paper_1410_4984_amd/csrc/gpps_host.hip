@@ -53,13 +53,14 @@ int requested_path(int flags, int allowed) {
 // cannot).  Calls without S (known inputs) always take the known-input path.
 constexpr int kPathKnown = 100;
 
-// Calls too small for the matrix-core path's launches (its seven or nine and the three
-// gated generic ones, against three): in us per call, matrix-core / generic, statistics
-// and gradients 42 / 27 and 51 / 31 at N = 200, M = 10, Q = 2, 43 / 26 and 64 / 31 at
-// N = 200, M = 50, Q = 10, 41 / 26 and 53 / 31 at N = 1,000, M = 32, Q = 2.  The
-// generic kernels stay ahead up to about ten times this work, but there the
-// matrix-core path, and the route word that tells whether its range guard passed,
-// is what calls without a path flag have always taken: only the smallest move.
+// Calls that take the generic kernels without a path flag because launches are all their time:
+// three of these against the matrix-core path's seven or nine and the three gated generic
+// ones.  In us per call, matrix-core / generic, statistics and gradients: 39 / 25 and 51 / 30
+// at N = 200, M = 10, Q = 2 (work 1.8e6), 48 / 25 and 60 / 32 at N = 1,704, M = 10, Q = 2
+// (1.5e7).  The line is not where the two cross: the generic kernels are ahead past it too, 42 / 25
+// and 58 / 30 at N = 1,000, M = 32, Q = 2 (1.6e7), 56 / 31 and 85 / 52 at N = 5,000, M = 50,
+// Q = 10 (2.8e8).  But calls past it keep the arithmetic and the route word (0 or 1) that they
+// have always had without a flag; GPPS_PATH_GENERIC gives them the time.
 constexpr double kSmallWork = 1.5e7;
 bool small_call(const gpps::Shape &s) {
     return (double)s.N * (double)(s.M * s.M + 1000) * (double)(s.Q + 6) <= kSmallWork;
