@@ -487,16 +487,16 @@ __device__ inline void g1_block(int64_t block, int64_t N, int M, int64_t D, doub
 
 // dL/dPsi2 (element type T, M x M), dL/dKmm (fp64, Mp x Mp) and, per row m, the
 // partial traces tr(A^-1 Psi2), tr(P Psi2), tr(Kmm^-1 Psi2) (all symmetric).  The workgroups
-// past the first Mp form dL/dPsi1.
+// past the first ones, Mp or none, form dL/dPsi1.
 template <typename T>
 __global__ __launch_bounds__(256) void bound_assemble_kernel(
-    int M, int Mp, int64_t D, double beta, const double *__restrict__ Kinv,
+    int first, int M, int Mp, int64_t D, double beta, const double *__restrict__ Kinv,
     const double *__restrict__ Ainv, const double *__restrict__ Pm, const double *__restrict__ KPK,
     const double *__restrict__ P2, T *__restrict__ G2, double *__restrict__ GK,
     double *__restrict__ tpart, int64_t N, const T *__restrict__ Y, const double *__restrict__ C,
     T *__restrict__ G1) {
     __shared__ double red[3][256];
-    if ((int)blockIdx.x >= Mp) return g1_block<T>(blockIdx.x - Mp, N, M, D, beta * beta, Y, C, G1);
+    if ((int)blockIdx.x >= first) return g1_block<T>(blockIdx.x - first, N, M, D, beta * beta, Y, C, G1);
     const int m = blockIdx.x;
     const double hd = 0.5 * (double)D;
     double ta = 0.0, tp = 0.0, tk = 0.0;
@@ -617,15 +617,15 @@ __global__ __launch_bounds__(64) void bound_kmm_grad_kernel(int M, int Q, int Mp
     if (q == 0) ksf[m] = sw / (double)h.sf2;
 }
 
-// Workgroup 0: dl[q] += sum_m kdl[m][q], dsigma_f2 += sum_m ksf[m] (fixed order).  The others:
-// the KL term's gradient, dmu -= mu, dS -= (1 - 1/S) / 2.
+// Workgroup 0 (if first is 1): dl[q] += sum_m kdl[m][q], dsigma_f2 += sum_m ksf[m] (fixed order).
+// The others: the KL term's gradient, dmu -= mu, dS -= (1 - 1/S) / 2.
 template <typename T>
 __global__ __launch_bounds__(256) void bound_tail_kernel(
-    int M, int Q, const double *__restrict__ kdl, const double *__restrict__ ksf, T *__restrict__ dl,
-    T *__restrict__ dsf2, int64_t NQ, const T *__restrict__ mu, const T *__restrict__ S, T *__restrict__ dmu,
+    int first, int M, int Q, const double *__restrict__ kdl, const double *__restrict__ ksf,
+    T *__restrict__ dl, T *__restrict__ dsf2, int64_t NQ, const T *__restrict__ mu, const T *__restrict__ S, T *__restrict__ dmu,
     T *__restrict__ dS) {
-    if (blockIdx.x > 0) {
-        const int64_t i = (int64_t)(blockIdx.x - 1) * 256 + threadIdx.x;
+    if ((int)blockIdx.x >= first) {
+        const int64_t i = (int64_t)(blockIdx.x - first) * 256 + threadIdx.x;
         if (i >= NQ) return;
         dmu[i] = dmu[i] - mu[i];
         dS[i] = dS[i] - (T)0.5 * ((T)1 - (T)1 / S[i]);
@@ -679,13 +679,23 @@ hipError_t bound_middle(const Shape &s, int64_t D, const T *mu, const T *S, cons
     // N = 3,000, M = 25, Q = 1, D = 2 went from 173 to 128 us).
     // Kmm, A; the row reductions; Psi1^T Y by chunks
     {
-        const unsigned kb = (unsigned)cdiv(mm, 256);
-        const unsigned parts = (unsigned)std::min<int64_t>(cdiv((int64_t)M * D, 256), 16);
+        const int64_t kb = cdiv(mm, 256);
+        int64_t parts = std::min<int64_t>(cdiv((int64_t)M * D, 256), 16);
         TimedScope ts(st, "bound_first");
-        bound_first_kernel<T><<<(unsigned)(kb + p.rblocks + p.ychunks * parts), 256, 0, st>>>(
-            s.N, M, Q, D, Mp, kb, (unsigned)p.rblocks, (unsigned)p.ychunks, parts, mu, S, Z, Y, h, jitter,
-            beta, Psi1, Psi2, K0, gj, gj + mm, P2, at<double>(ws, p.off_rpart),
-            at<double>(ws, p.off_ypart));
+        auto run = [&](int64_t k, int64_t r, int64_t y) {
+            bound_first_kernel<T><<<(unsigned)(k + r + y * parts), 256, 0, st>>>(
+                s.N, M, Q, D, Mp, (unsigned)k, (unsigned)r, (unsigned)p.ychunks, (unsigned)parts, mu, S, Z, Y, h,
+                jitter, beta, Psi1, Psi2, K0, gj, gj + mm, P2, at<double>(ws, p.off_rpart),
+                at<double>(ws, p.off_ypart));
+        };
+        if (kb + p.rblocks + p.ychunks * parts <= kMaxBlocks) {
+            run(kb, p.rblocks, p.ychunks);
+        } else {
+            parts = std::max<int64_t>(1, std::min(parts, kMaxBlocks / p.ychunks));
+            run(kb, 0, 0);
+            run(0, p.rblocks, 0);
+            run(0, 0, p.ychunks);
+        }
     }
     // Kmm = L_k L_k^T and A = L_a L_a^T (blocked Cholesky, in place), log determinants,
     // the triangular inverses and Kmm^-1 = L_k^-T L_k^-1, A^-1 = L_a^-T L_a^-1
@@ -724,8 +734,18 @@ hipError_t bound_middle(const Shape &s, int64_t D, const T *mu, const T *S, cons
     }
     {
         TimedScope ts(st, "bound_assemble");
-        bound_assemble_kernel<T><<<(unsigned)(p.Mp + cdiv(s.N * M, 256)), 256, 0, st>>>(
-            M, Mp, D, beta, Kinv, Ainv, Pm, KPK, P2, G2, GK, at<double>(ws, p.off_tpart), s.N, Y, C, Psi1);
+        auto run = [&](int64_t first, int64_t g1) {
+            bound_assemble_kernel<T><<<(unsigned)(first + g1), 256, 0, st>>>(
+                (int)first, M, Mp, D, beta, Kinv, Ainv, Pm, KPK, P2, G2, GK, at<double>(ws, p.off_tpart), s.N, Y,
+                C, Psi1);
+        };
+        const int64_t g1 = cdiv(s.N * M, 256);
+        if (p.Mp + g1 <= kMaxBlocks) {
+            run(p.Mp, g1);
+        } else {
+            run(p.Mp, 0);
+            run(0, g1);
+        }
         bound_scalar_kernel<T><<<1, 256, 0, st>>>(s.N, M, Mp, D, p.nbk, beta, (double)s.N * (double)h.sf2,
                                                  p.rblocks, at<double>(ws, p.off_rpart),
                                                  at<double>(ws, p.off_tpart), ld, Psi, C, L, dbeta);
@@ -742,8 +762,17 @@ hipError_t bound_tail(const Shape &s, int64_t D, const T *mu, const T *S, const 
     bound_kmm_grad_kernel<T><<<(unsigned)M, 64, 0, st>>>(M, Q, (int)p.Mp, Z, h, at<double>(ws, p.off_k0),
                                                         at<double>(ws, p.off_gk), dZ,
                                                         at<double>(ws, p.off_kdl), at<double>(ws, p.off_ksf));
-    bound_tail_kernel<T><<<(unsigned)(1 + (S ? cdiv(s.N * Q, 256) : 0)), 256, 0, st>>>(
-        M, Q, at<double>(ws, p.off_kdl), at<double>(ws, p.off_ksf), dl, dsf2, s.N * Q, mu, S, dmu, dS);
+    auto run = [&](int first, int64_t kl) {
+        bound_tail_kernel<T><<<(unsigned)(first + kl), 256, 0, st>>>(
+            first, M, Q, at<double>(ws, p.off_kdl), at<double>(ws, p.off_ksf), dl, dsf2, s.N * Q, mu, S, dmu, dS);
+    };
+    const int64_t kl = S ? cdiv(s.N * Q, 256) : 0;
+    if (1 + kl <= kMaxBlocks) {
+        run(1, kl);
+    } else {
+        run(1, 0);
+        run(0, kl);
+    }
     return hipGetLastError();
 }
 

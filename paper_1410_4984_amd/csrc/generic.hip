@@ -221,22 +221,24 @@ __global__ __launch_bounds__(256) void pre_kernel(const int *__restrict__ gate, 
         G2s[i] = v;
         return;
     }
-    const int64_t n0 = (int64_t)blockIdx.x * rows;
-    const int cnt = (int)min<int64_t>(rows, N - n0);
-    for (int i = threadIdx.x; i < cnt * Q; i += 256) {
-        const T s = S[n0 * Q + i], l2 = h.l2[i % Q];
-        w1[n0 * Q + i] = T(1) / (l2 + s);
-        w2[n0 * Q + i] = T(1) / (l2 + T(2) * s);
-        sl1[i] = dlog1p(s / l2);
-        sl2[i] = dlog1p(T(2) * s / l2);
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < 2 * cnt; i += 256) {
-        const int r = i >> 1;
-        const T *sl = (i & 1 ? sl2 : sl1) + r * Q;
-        T a = (i & 1 ? T(2) : T(1)) * h.log_sf2;
-        for (int q = 0; q < Q; ++q) a -= T(0.5) * sl[q];
-        (i & 1 ? lp2 : lp1)[n0 + r] = a;
+    for (int64_t n0 = (int64_t)blockIdx.x * rows; n0 < N; n0 += (int64_t)rblocks * rows) {
+        const int cnt = (int)min<int64_t>(rows, N - n0);
+        __syncthreads();
+        for (int i = threadIdx.x; i < cnt * Q; i += 256) {
+            const T s = S[n0 * Q + i], l2 = h.l2[i % Q];
+            w1[n0 * Q + i] = T(1) / (l2 + s);
+            w2[n0 * Q + i] = T(1) / (l2 + T(2) * s);
+            sl1[i] = dlog1p(s / l2);
+            sl2[i] = dlog1p(T(2) * s / l2);
+        }
+        __syncthreads();
+        for (int i = threadIdx.x; i < 2 * cnt; i += 256) {
+            const int r = i >> 1;
+            const T *sl = (i & 1 ? sl2 : sl1) + r * Q;
+            T a = (i & 1 ? T(2) : T(1)) * h.log_sf2;
+            for (int q = 0; q < Q; ++q) a -= T(0.5) * sl[q];
+            (i & 1 ? lp2 : lp1)[n0 + r] = a;
+        }
     }
 }
 
@@ -901,12 +903,13 @@ void pre(const Shape &s, const Plan &p, const T *S, const Hyp<T> &h, void *ws, c
          T *G2s = nullptr, T *zref = nullptr) {
     // few rows a workgroup where there are few: at least a workgroup per CU
     const int64_t rows = std::max<int64_t>(1, std::min(kPreElems / s.Q, cdiv(s.N, 256)));
-    const int64_t rb = cdiv(s.N, rows), Mp = cdiv(s.M, 16) * 16;
+    const int64_t Mp = cdiv(s.M, 16) * 16;
     const int64_t n = mode == kSymNone ? 0
                       : mode == kSymCirc ? (s.M / 2 + 1) * s.M
                       : mode == kSymPadded ? Mp * Mp : s.M * s.M;
     TimedScope ts(st, "generic_pre");
     const int64_t sb = cdiv(n, 256), zb = zref ? s.Q : 0;
+    const int64_t rb = std::min(cdiv(s.N, rows), kMaxBlocks - sb - zb);   // more row blocks: in turn
     pre_kernel<T><<<(unsigned)(rb + sb + zb), 256, 0, st>>>(
         gate, mark, s.N, (int)s.Q, (int)rows, (unsigned)rb, S, h, at<T>(ws, p.off_w1), at<T>(ws, p.off_w2),
         at<T>(ws, p.off_lp1), at<T>(ws, p.off_lp2), mode, (int)s.M, (int)Mp, G2, Z, G2s,

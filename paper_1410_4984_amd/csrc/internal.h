@@ -30,6 +30,11 @@ inline Shape make_shape(int64_t N, int64_t M, int64_t Q) {
     return Shape{N, M, Q, M * (M + 1) / 2};
 }
 
+// Workgroups of 256 threads that one launch takes along x (its threads are counted in 32
+// bits).  Kernels that do two jobs in one launch take the number of the first job's workgroups as
+// an argument: where the two don't fit together, they are launched one after the other.
+constexpr int64_t kMaxBlocks = (int64_t(1) << 24) - 1;
+
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // Brackets one kernel launch with HIP events on `st` while timing is enabled

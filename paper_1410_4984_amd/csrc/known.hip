@@ -191,7 +191,7 @@ __global__ __launch_bounds__(1024) void known_centre_kernel(int M, int Q, const 
 // the gradient GEMM streams).  Grid: (row blocks, column blocks); the
 // workgroups of the first column block also write xs.  Dynamic LDS: 2 * 64 * Q elements.
 // own: cz and zs are not there yet; each workgroup centres Z itself, and those of the first
-// row block write zs.  TRANS: the row blocks past the rows' own form the symmetric part
+// row block write zs.  TRANS: the row blocks past the rows' own rb form the symmetric part
 // of dL/dPsi2 (G2; NULL: none).
 template <typename T, bool TRANS>
 __global__ __launch_bounds__(256) void known_kfu_kernel(int64_t N, int M, int Q,
@@ -200,14 +200,14 @@ __global__ __launch_bounds__(256) void known_kfu_kernel(int64_t N, int M, int Q,
                                                         const T *__restrict__ cz,
                                                         T *__restrict__ zs, Hyp<T> h,
                                                         T *__restrict__ out, T *__restrict__ xs,
-                                                        const T *__restrict__ G2, T *__restrict__ G2s) {
+                                                        int64_t rb, const T *__restrict__ G2,
+                                                        T *__restrict__ G2s) {
     extern __shared__ double known_smem[];
     T *sx = reinterpret_cast<T *>(known_smem);  // [q][64] scaled rows
     T *sz = sx + Q * kEdge;                     // [q][64] scaled inducing inputs
     T *c0 = sz + Q * kEdge;                     // [Q] the centre (own only)
     const int tid = threadIdx.x;
     if (TRANS) {
-        const int64_t rb = (N + kEdge - 1) / kEdge;
         if ((int64_t)blockIdx.x >= rb) {
             const int64_t i = ((blockIdx.x - rb) * gridDim.y + blockIdx.y) * 256 + tid;
             if (i >= (int64_t)M * M) return;
@@ -845,15 +845,23 @@ void launch_centre_kfu(const Shape &s, const KPlan &p, const T *X, const T *Z, c
     }
     const int64_t rb = cdiv(s.N, kEdge), mb = cdiv(s.M, kEdge);
     const int64_t sym = G2 ? cdiv(cdiv(s.M * s.M, 256), mb) : 0;   // G2's workgroups, mb at a time
-    dim3 grid((unsigned)(rb + sym), (unsigned)mb);
     const size_t lds = (2 * kEdge + (own ? 1 : 0)) * s.Q * sizeof(T);
     TimedScope ts(st, "known_kfu");
-    if (trans)
-        known_kfu_kernel<T, true><<<grid, 256, lds, st>>>(s.N, (int)s.M, (int)s.Q, X, Z, own, cz, zs, h, out,
-                                                          xs, G2, at<T>(ws, p.off_g2s));
-    else
-        known_kfu_kernel<T, false><<<grid, 256, lds, st>>>(s.N, (int)s.M, (int)s.Q, X, Z, own, cz, zs, h, out,
-                                                           xs, nullptr, nullptr);
+    if (trans) {
+        auto run = [&](int64_t rows, int64_t all) {
+            known_kfu_kernel<T, true><<<dim3((unsigned)all, (unsigned)mb), 256, lds, st>>>(
+                s.N, (int)s.M, (int)s.Q, X, Z, own, cz, zs, h, out, xs, rows, G2, at<T>(ws, p.off_g2s));
+        };
+        if (rb + sym <= kMaxBlocks) {
+            run(rb, rb + sym);
+        } else {
+            run(rb, rb);
+            run(0, sym);
+        }
+    } else {
+        known_kfu_kernel<T, false><<<dim3((unsigned)rb, (unsigned)mb), 256, lds, st>>>(
+            s.N, (int)s.M, (int)s.Q, X, Z, own, cz, zs, h, out, xs, rb, nullptr, nullptr);
+    }
 }
 
 template <typename T, int QM>
@@ -878,9 +886,17 @@ hipError_t launch_chain(const Shape &s, const KPlan &p, const T *Et, const Hyp<T
             at<T>(ws, p.off_colp), at<T>(ws, p.off_ep));
     }
     TimedScope ts(st, "known_dx");
-    known_dx_reduce_kernel<T><<<(unsigned)(p.tiles + s.M), 256, 0, st>>>(
-        s.N, (int)s.M, (int)s.Q, (int)p.nb, p.tiles, G, at<T>(ws, p.off_dxp), h, dX, at<T>(ws, p.off_colp),
-        at<T>(ws, p.off_vc));
+    auto run = [&](int64_t tiles, int64_t all) {
+        known_dx_reduce_kernel<T><<<(unsigned)all, 256, 0, st>>>(
+            s.N, (int)s.M, (int)s.Q, (int)p.nb, tiles, G, at<T>(ws, p.off_dxp), h, dX,
+            at<T>(ws, p.off_colp), at<T>(ws, p.off_vc));
+    };
+    if (p.tiles + s.M <= kMaxBlocks) {
+        run(p.tiles, p.tiles + s.M);
+    } else {
+        run(p.tiles, p.tiles);
+        run(0, s.M);
+    }
     return hipGetLastError();
 }
 

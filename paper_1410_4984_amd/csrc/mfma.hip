@@ -2511,8 +2511,7 @@ void prepare(const MPlan &p, const Shape &s, const float *mu, const float *S, co
         mfma_guard_kernel<<<1, 256, 0, st>>>(gd, (int)s.Q, fat(ws, p.off_zc), h);
         gd.nparts = 0;
     }
-    const SymArgs sy{grad ? (int)cdiv(p.Mp * p.Mp, 256) : 0, G2, fat(ws, p.off_g2), fat(ws, p.off_smax)};
-    dim3 grid((unsigned)(cdiv(s.N, kRTRows) + sy.blocks), (unsigned)cdiv(p.Mp, 256));
+    SymArgs sy{grad ? (int)cdiv(p.Mp * p.Mp, 256) : 0, G2, fat(ws, p.off_g2), fat(ws, p.off_smax)};
     float *t1 = grad ? fat(ws, p.off_t1) : nullptr;
     TimedScope ts(st, "mfma_rowterm");
 #define GPPS_RT(QM)                                                                            \
@@ -2528,14 +2527,27 @@ void prepare(const MPlan &p, const Shape &s, const float *mu, const float *S, co
                 fat(ws, p.off_hl), fat(ws, p.off_w1), fat(ws, p.off_l1), G1, gd, sy, h,        \
                 fat(ws, p.off_bt), fat(ws, p.off_bc), psi1, nullptr, nullptr);                 \
     } while (0)
-    if (s.Q <= 8) GPPS_RT(8);
-    else if (s.Q <= 12) GPPS_RT(12);
-    else if (s.Q <= 16) GPPS_RT(16);
-    else if (s.Q <= 20) GPPS_RT(20);
-    else if (s.Q <= 24) GPPS_RT(24);
-    else if (s.Q <= 32) GPPS_RT(32);
-    else if (s.Q <= 48) GPPS_RT(48);
-    else GPPS_RT(64);
+    dim3 grid(1, (unsigned)cdiv(p.Mp, 256));
+    auto run = [&](int64_t rows, int syms) {
+        grid.x = (unsigned)(rows + syms);
+        sy.blocks = syms;
+        if (s.Q <= 8) GPPS_RT(8);
+        else if (s.Q <= 12) GPPS_RT(12);
+        else if (s.Q <= 16) GPPS_RT(16);
+        else if (s.Q <= 20) GPPS_RT(20);
+        else if (s.Q <= 24) GPPS_RT(24);
+        else if (s.Q <= 32) GPPS_RT(32);
+        else if (s.Q <= 48) GPPS_RT(48);
+        else GPPS_RT(64);
+    };
+    const int64_t rt = cdiv(s.N, kRTRows);
+    const int syms = sy.blocks;
+    if (rt + syms <= kMaxBlocks) {
+        run(rt, syms);
+    } else {
+        run(rt, 0);
+        run(0, syms);
+    }
 #undef GPPS_RT
 }
 
