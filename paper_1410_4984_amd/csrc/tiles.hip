@@ -144,8 +144,8 @@ __device__ inline void wave_lds_fence() {
 constexpr int kFwdMinRows = 4;   // rows per chunk of the smallest calls (a row takes a wave 2 us alone)
 constexpr int kFlush = 128;  // rows summed before they join the chunk's total (a multiple of grad_rows)
 
-// Row and column blocks of a task: as many as leave its z rows, x and sums within
-// 256 registers.
+// Row and column blocks of a task.  Its z rows, x and sums fill the 256 registers of two waves
+// per SIMD; in fp64 14 to 82 go to scratch from KS = 5 on (KS = 8: 82, 332 bytes a lane).
 __host__ __device__ constexpr int fwd_a(int ks) { return ks <= 8 ? 4 : 2; }
 __host__ __device__ constexpr int fwd_c(int ks) { return ks <= 12 ? 2 : 1; }
 // Rows n staged at a time, per wave in two buffers (eight waves share a CU's LDS).
@@ -945,10 +945,6 @@ GradGeo grad_geo(const Shape &s, size_t elem) {
             g.chunks = std::max(1, 256 * per_cu / groups);
         }
     }
-    if (best == 0.0) {
-        g.lds = SIZE_MAX;
-        return g;
-    }
     g.rows = cdiv(cdiv(s.N, g.chunks), R) * R;
     g.chunks = cdiv(s.N, g.rows);
     return g;
@@ -998,7 +994,6 @@ FwdGeo fwd_geo(const Shape &s, size_t budget, size_t elem) {
         });
         if (f.waves <= most || cmax == 1) break;
     }
-    if (f.waves > room) f.cmax = 0;
     int wave = 0, task = 0;
     each([&](int cb, int rb, int n) {
         if (rb == cb) {
@@ -1050,8 +1045,9 @@ hipError_t tiles_psi2(const Shape &s, const T *mu, const T *Z, const T *w1, cons
         TimedScope ts(st, "tiles_psi2_fwd");
 #define GPPS_TILES_FWD(KS)                                                                        \
     case KS:                                                                                      \
-        tiles_fwd_kernel<T, KS><<<grid, kFwdWaves * 64, 0, st>>>(                                 \
-            gate, s.N, (int)s.M, (int)s.Q, f.nb, f.waves, f.table, mu, Z, w2, lp2, partial);                \
+        if constexpr (KS > 1 || sizeof(T) == 8) /* fp32 comes here from Q = 5 on */               \
+            tiles_fwd_kernel<T, KS><<<grid, kFwdWaves * 64, 0, st>>>(                             \
+                gate, s.N, (int)s.M, (int)s.Q, f.nb, f.waves, f.table, mu, Z, w2, lp2, partial);  \
         break
         switch (ks_of(s.Q)) {
             GPPS_TILES_FWD(1); GPPS_TILES_FWD(2); GPPS_TILES_FWD(3); GPPS_TILES_FWD(4);
@@ -1074,7 +1070,6 @@ hipError_t tiles_psi2(const Shape &s, const T *mu, const T *Z, const T *w1, cons
 TilesGradPlan tiles_grad_plan(const Shape &s, size_t budget, size_t elem) {
     TilesGradPlan p{};
     GradGeo g = grad_geo(s, elem);
-    if (g.lds > kLdsMax) return p;
     const int64_t Mp = cdiv(s.M, 16) * 16;
     size_t o = 0;
     auto take = [&](size_t n) { size_t r = o; o = align_up(o + n * elem, 256); return r; };
