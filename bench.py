@@ -79,7 +79,7 @@ def algorithmic(kernel: str, N: int, M: int, Q: int):
     Per unique pair (m <= m') and datapoint, the Psi2 forward needs one FMA per
     latent dimension (the Gram term) and the Psi2 gradient three (Gram
     recompute plus W*d on both sides of the pair): 2 and 6 flops per
-    (n, pair, q).  Psi1 kernels are counted by their compulsory HBM bytes."""
+    (n, pair, q)."""
     P = M * (M + 1) // 2
     fwd, grad = 2.0 * Q * N * P, 6.0 * Q * N * P
     table = {
@@ -92,9 +92,6 @@ def algorithmic(kernel: str, N: int, M: int, Q: int):
         # flops are priced against the fp32 vector peak
         "mfma_psi2_fwd": ("alu", fwd, "flop"),
         "mfma_psi2_grad": ("alu", grad, "flop"),
-        "generic_psi1": ("hbm", 4.0 * (N * M + 2 * N * Q), "byte"),
-        "mfma_psi1_fwd": ("hbm", 4.0 * (N * M + 2 * N * Q), "byte"),
-        "mfma_psi1_grad": ("hbm", 4.0 * (N * M + 4 * N * Q), "byte"),
         # known inputs (S = 0): the rank-k update over the unique pairs, the
         # gradient GEMM over all M x M, Kfu, and the chain rule per (n, m, q):
         # rows a difference and an FMA, columns a difference, a product, a sum
@@ -105,6 +102,20 @@ def algorithmic(kernel: str, N: int, M: int, Q: int):
         "known_chain": ("alu", 8.0 * N * M * Q, "flop"),
     }
     return table.get(kernel)
+
+
+# Psi2 forward and gradient kernels with their reductions (F_alg's kernels), and the per-row
+# kernels that feed them or, like the generic path's Psi2 reduce, share a launch with Psi1
+PSI2_KERNELS = ("psi2_partial", "psi2_fwd", "psi2_grad", "grad_pairs",
+                "psi2_reduce", "psi2_finalize", "grad_reduce", "grad_finish")
+ROW_KERNELS = ("mfma_rows", "mfma_rowterm", "mfma_centre", "mfma_guard", "generic_pre", "_psi1")
+
+
+def kernel_class(kernel: str):
+    """'rows', 'psi2' or None (neither)."""
+    if any(c in kernel for c in ROW_KERNELS):
+        return "rows"
+    return "psi2" if any(c in kernel for c in PSI2_KERNELS) else None
 
 
 def traffic_for(kernel: str, workload: str):
@@ -594,14 +605,13 @@ def main():
                 "exp_executed_per_launch": c["SQ_INSTS_VALU_TRANS_F32"] * 64,
                 "exp_unique_pairs_per_launch": float(N) / len(chunks) * P,
                 "counters": f"profiles/counters_{dom}_{args.workload}.md"}
-    # Psi2 forward + gradient kernels with their reductions (F_alg's kernels), and
-    # beside them with the per-row kernels that feed them
-    core = ("psi2_partial", "psi2_fwd", "psi2_grad", "grad_pairs",
-            "psi2_reduce", "psi2_finalize", "grad_reduce", "grad_finish")
-    feed = ("mfma_rows", "mfma_rowterm", "mfma_centre", "mfma_guard", "generic_pre")
     per_step = {k: v["avg_ms"] * v["launches"] / args.kernel_steps for k, v in kernels.items()}
-    t_psi2 = sum(v for k, v in per_step.items() if any(c in k for c in core)) * 1e-3
-    t_feed = sum(v for k, v in per_step.items() if any(c in k for c in feed)) * 1e-3
+    t_psi2 = sum(v for k, v in per_step.items() if kernel_class(k) == "psi2") * 1e-3
+    t_feed = sum(v for k, v in per_step.items() if kernel_class(k) == "rows") * 1e-3
+    fp = "fp64" if f64 else "fp32"
+    generic = (f"generic path: Psi2 and its gradients in 16 x 16 tiles on the {fp} matrix instructions, the "
+               f"rest in {fp} on the vector ALU" if any(k.startswith("tiles_") for k in kernels) else
+               f"generic path: {fp} on the vector ALU")
     F_alg = 8.0 * Q * N * P
     rec = {
         "metric": METRIC, "value": terms / (ms * 1e-3), "unit": "terms/s", "n_gpus": 1,
@@ -618,8 +628,7 @@ def main():
                                    "v_mfma_f32_32x32x16_f16 with two-part fp16 operands (22 "
                                    "significant bits, three cross products) accumulated in fp32; "
                                    "exponentials, weighting and epilogues in fp32 on the vector "
-                                   "ALU") if on_mfma else
-                                  f"generic path: {'fp64' if f64 else 'fp32'} on the vector ALU")},
+                                   "ALU") if on_mfma else generic)},
         f"pct_{'fp64' if f64 else 'fp32'}_peak": (round(100.0 * F_alg / t_psi2 / PEAK_VALU, 2)
                                                   if t_psi2 > 0 else None),
         f"pct_{'fp64' if f64 else 'fp32'}_peak_with_row_kernels": (

@@ -168,8 +168,9 @@ __device__ inline void centre(int M, int Q, const T *__restrict__ Z, T *part, T 
     }
     __syncthreads();
 }
-// M Q and Q up to which every Kfu workgroup finds the centre itself, for one launch less:
-// 8 values a thread of a workgroup, and LDS within 64 KB.
+// M Q and Q up to which every Kfu workgroup finds the centre itself, for one launch less: 8
+// values a thread of a workgroup (at Q = 1, whose 64 groups are 64 threads, 32), and LDS
+// within 64 KB.
 constexpr int64_t kOwnCentre = 2048, kOwnQ = 32;
 
 // cz[q] = c[q], zs = (Z - cz) / l.

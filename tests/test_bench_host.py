@@ -46,3 +46,14 @@ def test_traffic_is_null_for_a_changed_source(tmp_path, monkeypatch):
     src.write_text("kernel v2\n")
     assert bench.traffic_for("k", "w") is None
     assert bench.traffic_for("missing", "w") is None
+
+
+def test_kernel_classes():
+    # the generic path's Psi2 reduce shares its launch with the N x M Psi1 pass, so it is not
+    # Psi2 time
+    want = {"mfma_psi2_fwd": "psi2", "mfma_psi2_reduce": "psi2", "mfma_grad_reduce": "psi2",
+            "tiles_psi2_grad": "psi2", "generic_grad_pairs": "psi2", "generic_grad_finish": "psi2",
+            "tiles_psi2_reduce_psi1": "rows", "generic_psi2_reduce_psi1": "rows", "generic_pre": "rows",
+            "mfma_rowterm": "rows", "known_kfu": None}
+    assert {k: bench.kernel_class(k) for k in want} == want
+    assert bench.algorithmic("generic_psi1", 10, 4, 2) is None
