@@ -946,7 +946,8 @@ hipError_t generic_psi_stats(const Shape &s, const T *mu, const T *S, const T *Z
     const T *lp1 = at<T>(ws, p.off_lp1), *lp2 = at<T>(ws, p.off_lp2);
     if (p.tstats)
         return tiles_psi2<T>(s, mu, Z, w1, w2, lp1, lp2, h, psi0, Psi1, Psi2, accumulate,
-                             at<char>(ws, p.off_p2), p.total - p.off_p2, gate, st);
+                             at<char>(ws, p.off_p2),
+                             std::max(p.total, known_workspace_bytes(s, sizeof(T))) - p.off_p2, gate, st);
     T *partial = at<T>(ws, p.off_p2);
     {
         const dim3 grid((unsigned)p.pblocks, (unsigned)p.nc2);

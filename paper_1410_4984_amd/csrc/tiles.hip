@@ -15,21 +15,21 @@
 // round at half of the exponent's size or less: started from b_m + b_m' they left 2.7e-15
 // of Psi2 in fp64 at Q = 30 (N = 200, M = 64), 1.2e-15 so (the vector kernels: 2.4e-15).
 //
-// What bounds these kernels is the SIMDs' issue rate.  In fp64 a 16 x 16 x 4 product occupies a SIMD for 64 cycles and no vector
-// instruction issues meanwhile (measured: 8 FMAs behind each product add 8 FMAs'
-// time), so matrix and vector work add up: a matrix FMA costs the same as a
-// vector one, but needs one operand load per 16 of them, no cross-lane sums and
+// What bounds these kernels is the SIMDs' issue rate.  In fp64 a 16 x 16 x 4 product
+// occupies a SIMD for 64 cycles and no vector instruction issues meanwhile (measured: 8 FMAs
+// behind each product add 8 FMAs' time), so matrix and vector work add up: a matrix FMA costs
+// the same as a vector one, but needs one operand load per 16 of them, no cross-lane sums and
 // no index arithmetic.  The exponential is 2^E' in 15 instructions (the table's
 // ln 2 is folded into x and b), against about 21 of exp().  In fp32 a product takes 32
 // cycles and the exponential is one instruction.
 //
-// Measured against the vector kernels (fp64, psi2 gradient + forward): 45.3 + 10.6 ms
-// -> 14.8 + 5.0 ms at N = 100,000, M = 256, Q = 20; 3.34 + 0.53 -> 1.43 + 0.48 ms at
-// N = 50,000, M = 100, Q = 10; 261 + 3.7 -> 3.3 + 1.2 ms at N = 4096, M = 512, Q = 30.
-// At the first shape the SIMDs' issue is 40% matrix and 30-40% vector instructions.
-// fp32, statistics + gradients: 4.06 -> 1.9 ms at N = 3001, M = 700, Q = 12; 54 -> 0.75 ms
-// at N = 1500, M = 300, Q = 40; 2.2 s -> 40 ms at N = 40,000, M = 700, Q = 31 (the vector
-// kernels' z table did not fit LDS there).
+// Measured against the vector kernels before them (fp64, gradient + forward): 45.3 + 10.6 ms
+// -> 15.1 + 5.0 ms at N = 100,000, M = 256, Q = 20, where the matrix cores are busy 46% of the
+// gradient's cycles and 42% of the forward's and vector instructions 37% and 49%, never at
+// once (SQ counters); 3.34 + 0.53 -> 1.46 + 0.49 ms at N = 50,000, M = 100, Q = 10; 261 + 3.7 ->
+// 3.5 + 1.2 ms at N = 4096, M = 512, Q = 30.  fp32, statistics + gradients: 4.06 -> 1.65 ms
+// at N = 3001, M = 700, Q = 12; 54 -> 0.67 ms at N = 1500, M = 300, Q = 40; 2.2 s -> 38 ms at
+// N = 40,000, M = 700, Q = 31 (the vector kernels' z table did not fit LDS there).
 //
 // Rows whose exponents leave the range in which that is exact (|b| < 2^26: means
 // thousands of lengthscales from an inducing input, infinities, NaN) take a
@@ -46,7 +46,7 @@ namespace gpps {
 namespace {
 
 constexpr size_t kLdsMax = 160 * 1024;
-constexpr int kSimds = 1024;   // 256 CUs x 4
+constexpr int kCus = 256, kSimds = 4 * kCus;
 constexpr double kLog2e = 1.4426950408889634074;
 // The largest |b| of the fast exponential (fp64: its integer part has to fit 32 bits;
 // fp32: beyond it b's rounding passes 0.1, and 2^E' of such a row is zero).
@@ -141,6 +141,7 @@ __device__ inline void wave_lds_fence() {
 // its blocks, x for its columns and b for all, which is shared by its
 // tiles.  b of a row block is summed over q by one product with ones,
 // which leaves it in the tile's own layout.
+constexpr int64_t kFwdMaxFew = 8;   // chunks per task up to which more than one round is tried
 constexpr int kFwdMinRows = 4;   // rows per chunk of the smallest calls (a row takes a wave 2 us alone)
 constexpr int kFlush = 128;  // rows summed before they join the chunk's total (a multiple of grad_rows)
 
@@ -955,7 +956,8 @@ struct FwdGeo {
     FwdTable table;
 };
 
-FwdGeo fwd_geo(const Shape &s, size_t budget, size_t elem) {
+// more: chunks past one round of workgroups, where the region has room for them.
+FwdGeo fwd_geo(const Shape &s, size_t budget, size_t elem, bool more) {
     FwdGeo f{};
     const int ks = ks_of(s.Q);
     f.nb = (int)cdiv(s.M, 16);
@@ -984,15 +986,34 @@ FwdGeo fwd_geo(const Shape &s, size_t budget, size_t elem) {
         work += (int64_t)n * (fwd_tiles(f.nb, f.a, f.c, cb, rb) + 1);
         f.tasks += n;
     });
-    int64_t cmax = std::max<int64_t>(1, std::min(most * full / work, cdiv(s.N, kFwdMinRows)));
-    for (;; --cmax) {
+    auto plan = [&](int64_t cmax) {
         f.cmax = (int)cmax;
         for (int t = 0; t <= 8; ++t) f.table.n[t] = (unsigned)std::min(s.N, cdiv(cmax * (t + 1), full));
         f.waves = 0;
         each([&](int cb, int rb, int n) {
             f.waves += n * f.table.n[fwd_tiles(f.nb, f.a, f.c, cb, rb)];
         });
-        if (f.waves <= most || cmax == 1) break;
+    };
+    const int64_t rows = cdiv(s.N, kFwdMinRows);
+    int64_t cmax = std::max<int64_t>(1, std::min(most * full / work, rows));
+    for (plan(cmax); f.waves > most && cmax > 1; plan(--cmax)) {}
+    // From about M = 1000 on one round is a few chunks per task, and the workgroups (a wave on
+    // every SIMD of a CU) that fill no whole round leave most CUs idle: 264 at M = 2048 in fp64
+    // take as long as 512 would.  Up to kFwdMaxFew chunks, then, as many as bring the CUs'
+    // largest share of the rows, workgroups per CU / chunks, within 3% of its least (fp64,
+    // N = 6,000: at M = 2048 25.1 -> 13.7 ms for Q = 5 and 22.2 -> 12.2 for Q = 3, the vector
+    // kernels 19.9 and 15.5; at M = 3000, Q = 3 33.9 -> 23.3, the vector kernels 30.2).
+    if (more && cmax < kFwdMaxFew) {
+        auto share = [&] { return (double)cdiv(cdiv(f.waves, kFwdWaves), kCus) / f.cmax; };
+        double least = share();
+        const int64_t last = std::min(kFwdMaxFew, rows);
+        auto fits = [&] { return f.waves <= std::min<int64_t>(room, 65536); };   // 16-bit wave numbers
+        for (int64_t c = cmax + 1; c <= last; ++c) {
+            plan(c);
+            if (fits()) least = std::min(least, share());
+        }
+        for (plan(cmax); f.cmax < last && !(fits() && share() <= 1.03 * least); plan(f.cmax + 1)) {}
+        if (!fits()) plan(cmax);
     }
     int wave = 0, task = 0;
     each([&](int cb, int rb, int n) {
@@ -1019,7 +1040,7 @@ bool tiles_grads_wanted(const Shape &s, size_t) { return s.Q > 2 && (s.Q > 4 || 
 TilesRegion tiles_region(const Shape &s, size_t elem) {
     TilesRegion r{0, 0};
     if (tiles_stats_wanted(s, elem)) {
-        const FwdGeo f = fwd_geo(s, SIZE_MAX, elem);
+        const FwdGeo f = fwd_geo(s, SIZE_MAX, elem, false);
         const size_t per = (size_t)f.a * f.c * 256 * elem;
         r.least = f.tasks * per;
         r.want = f.waves * per;
@@ -1038,7 +1059,7 @@ template <typename T>
 hipError_t tiles_psi2(const Shape &s, const T *mu, const T *Z, const T *w1, const T *w2, const T *lp1,
                       const T *lp2, const Hyp<T> &h, T *psi0, T *Psi1, T *Psi2, int accumulate, void *ws,
                       size_t budget, const int *gate, hipStream_t st) {
-    const FwdGeo f = fwd_geo(s, budget, sizeof(T));
+    const FwdGeo f = fwd_geo(s, budget, sizeof(T), true);
     T *partial = static_cast<T *>(ws);
     const unsigned grid = (unsigned)cdiv(f.waves, kFwdWaves);
     {

@@ -99,3 +99,20 @@ def test_exponent_rounding_f64(Q=30, tol=2e-15):
         errs.append(float(np.linalg.norm(P2.cpu().numpy() - ref) / np.linalg.norm(ref)))
     print([f"{e:.1e}" for e in errs], flush=True)
     assert np.sqrt(np.mean(np.square(errs))) <= tol, errs
+
+
+# Statistics of so many inducing inputs that the forward's tasks take a few chunks each and
+# more than one round of workgroups (M from about 1000 on, with the region's room for it or
+# without), against the oracle; tolerances of the parity tests.
+@pytest.mark.parametrize("dtype,tol", [(torch.float32, 1e-4), (torch.float64, 1e-12)])
+@pytest.mark.parametrize("N,M,Q", [(40, 2048, 5), (37, 1500, 6), (18, 3000, 9), (9, 1030, 33)])
+def test_statistics_in_several_rounds(N, M, Q, dtype, tol):
+    print(f"[several rounds N={N} M={M} Q={Q} {dtype}]", flush=True)
+    inp = synth.to_f32(synth.random_inputs(N, M, Q, seed=M))
+    ws = torch.full((gpps.workspace_bytes(dtype, N, M, Q),), 0x7F, dtype=torch.uint8, device=DEV)
+    got = gpps.psi_stats(t(inp["mu"], dtype), t(inp["S"], dtype), t(inp["Z"], dtype), inp["sigma_f2"], inp["l"],
+                         workspace=ws, path="generic")
+    ref = oracle.psi_stats(inp["mu"], inp["S"], inp["Z"], inp["sigma_f2"], inp["l"])
+    for k, a, b in zip(("psi0", "Psi1", "Psi2"), got, ref):
+        assert rel(a.double().cpu().numpy(), b) <= tol, k
+    assert torch.equal(got[2], got[2].T)
