@@ -79,14 +79,20 @@ hipError_t generic_psi_grads(const Shape &s, const T *mu, const T *S, const T *Z
 // per-row tables and reduces, and the part of its workspace behind the tables
 // (`budget` bytes at `ws`): the plans fit their chunks to it, so that the path
 // needs no more workspace than the vector kernels it replaces.
-// They are taken where they measured faster than the vector kernels (us per call at
-// N = 64,000 in fp64, vector / tiles): statistics 297 / 483 at M = 100, Q = 1, 458 / 489
-// at Q = 4 and 569 / 555 at Q = 5, but 1684 / 1425 at M = 200, Q = 4; gradients
-// 607 / 1098 at M = 100, Q = 1, 1041 / 1102 at Q = 2 and 1848 / 1108 at Q = 4, but
-// 5755 / 4365 at M = 256, Q = 2; at N = 30,000 in fp32 90 / 117, 141 / 138 (Q = 4, 5,
-// M = 100), 412 / 394 and 616 / 470 (M = 256); gradients 304 / 332 and 1453 / 1216 at
-// Q = 4, 855 / 366 and 4510 / 1348 at Q = 5.  Small Q pads the products' four dimensions,
-// and the vector kernels take one exponential per unordered pair.
+// Where they are taken, against the vector kernels, which need one exponential per unordered
+// pair but grow with Q, while small Q pads the tiles' four dimensions (us per call, vector / tiles,
+// fp64 at N = 64,000 and fp32 at N = 30,000 unless another N is given):
+//   statistics, fp64: from Q = 5 (569 / 555 at M = 100), from Q = 3 past M = 128 (447 / 487 at
+//     M = 100, 1635 / 1440 at M = 200, both at Q = 4); Q = 2 crosses at M = 256 (2089 / 2051);
+//   statistics, fp32: from Q = 5 (141 / 138 at M = 100; at Q = 4 86 / 121, and 396 / 380 at
+//     M = 256);
+//   gradients, fp64: from Q = 3 (1829 / 1192 at M = 100, 653 / 456 at M = 50; Q = 2 1035 / 1195
+//     and, past M = 170 only, 4534 / 3828 at M = 200);
+//   gradients, fp32: from Q = 5 (855 / 366 at M = 100).  At Q = 3 and 4 as the forms fit: the
+//     vector kernel holds three rows a workgroup up to M = 170 (685 / 1124 at M = 168, N = 5,000
+//     154 / 209) and two past it (1145 / 1126 at M = 176, N = 5,000 245 / 210); the tiles'
+//     workgroups are eight waves, one to a CU, from M = 385 to 512 (3552 / 2977 at M = 384,
+//     3542 / 4107 at 385, 4586 / 4737 at 480; 6800 / 6613 at 544, N = 5,000 1237 / 1147).
 bool tiles_stats_wanted(const Shape &s, size_t elem);
 bool tiles_grads_wanted(const Shape &s, size_t elem);
 struct TilesRegion {

@@ -1035,7 +1035,10 @@ T *at(void *p, size_t off) { return reinterpret_cast<T *>(static_cast<char *>(p)
 bool tiles_stats_wanted(const Shape &s, size_t elem) {
     return s.Q > 4 || (elem == 8 && s.Q > 2 && s.M > 128);
 }
-bool tiles_grads_wanted(const Shape &s, size_t) { return s.Q > 2 && (s.Q > 4 || s.M > 128); }
+bool tiles_grads_wanted(const Shape &s, size_t elem) {
+    if (s.Q <= 2 || s.Q > 4) return s.Q > 4;
+    return elem == 8 || (s.M > 170 && s.M <= 384) || s.M > 512;
+}
 
 TilesRegion tiles_region(const Shape &s, size_t elem) {
     TilesRegion r{0, 0};

@@ -116,3 +116,20 @@ def test_statistics_in_several_rounds(N, M, Q, dtype, tol):
     for k, a, b in zip(("psi0", "Psi1", "Psi2"), got, ref):
         assert rel(a.double().cpu().numpy(), b) <= tol, k
     assert torch.equal(got[2], got[2].T)
+
+
+# Both sides of the lines at which the gradients at Q = 3 and 4 go to the tile kernels or stay
+# with the vector ones (fp32: M = 170, 384 and 512; fp64: always tiles), and Q = 2, which
+# stays; upstream not symmetric; against the oracle, tolerances of the parity tests.
+@pytest.mark.parametrize("dtype,tol", [(torch.float32, 1e-4), (torch.float64, 1e-12)])
+@pytest.mark.parametrize("M", [7, 128, 129, 170, 171, 384, 385, 512, 513])
+@pytest.mark.parametrize("Q", [2, 3, 4])
+def test_gradients_around_the_dispatch_lines(M, Q, dtype, tol):
+    print(f"[dispatch lines M={M} Q={Q} {dtype}]", flush=True)
+    inp = synth.to_f32(synth.random_inputs(33, M, Q, seed=M + Q))
+    inp["dL_dPsi2"] = np.float32(inp["dL_dPsi2"] + np.triu(np.ones((M, M)), 1))
+    got = grads(inp, dtype)
+    ref = oracle.psi_grads(inp["mu"], inp["S"], inp["Z"], inp["sigma_f2"], inp["l"], inp["dL_dpsi0"],
+                           inp["dL_dPsi1"], inp["dL_dPsi2"])
+    for k, v in ref.items():
+        assert rel(got[k], v) <= tol, k
