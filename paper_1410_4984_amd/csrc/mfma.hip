@@ -115,6 +115,9 @@ static_assert(kGPF * 64 >= kRB * 32, "kGPF slots cover the [kRB][32 wpg] row tab
 static_assert(kFRB * kRowStride == kThreads, "one mu / kappa value per forward thread");
 constexpr int64_t kCUs = 256;          // compute units of one MI355X
 constexpr int64_t kLdsBytes = 160 * 1024;
+// A workgroup's LDS comes in multiples of this: of the 27,024 bytes of the gradient's at Q = 30,
+// M <= 32 five fit a CU and not six (N = 20,000: 183 us with chunks for five, 245 for six).
+constexpr size_t kLdsGrain = 1280;
 constexpr int kFinRows = 64;           // rows per block of the gradient finalize kernel
 constexpr int kRTRows = 32;            // rows per block of the row-term kernel
 // gradient: column blocks per wave task (the dL/dPsi2 tiles it holds in registers)
@@ -403,7 +406,14 @@ MPlan carve_mplan(const Shape &s, bool few_rows) {
     const int64_t fslots = p.fsym ? (fsym_ranges(p.nb) > 1 ? 2 : 1) * kCUs *
                                         std::min<int64_t>(2, std::max<int64_t>(1, kLdsBytes / p.lds_fwd))
                                   : kCUs * std::min<int64_t>(6, 2 * std::max<int64_t>(1, kLdsBytes / p.lds_fwd));
-    p.fchunks = std::max<int64_t>(1, std::min(fslots / p.fgroups, cdiv(s.N, fmin)));
+    // chunks shorter than 32 rows: the symmetric forward in one range any number, the others, whose
+    // workgroups stage more per chunk, only up to two per CU or, in two ranges, one (us, long
+    // chunks / short ones / these: Q = 31, M = 130, N = 3,000 119 / 137 / 107; Q = 25, M = 400,
+    // N = 1,000 150 / 174 / 139; but Q = 31, M = 130, N = 500 99 / 75)
+    const int64_t ffill = (p.fsym ? kCUs : 2 * kCUs) / p.fgroups;
+    const bool fany = p.fsym && fsym_ranges(p.nb) == 1;
+    p.fchunks = fany ? cdiv(s.N, fmin) : std::max(cdiv(s.N, 32), std::min(cdiv(s.N, fmin), ffill));
+    p.fchunks = std::max<int64_t>(1, std::min(fslots / p.fgroups, p.fchunks));
     p.frows = cdiv(s.N, p.fchunks);
     p.fchunks = cdiv(s.N, p.frows);
     // symmetric gradient kernel (one workgroup of nb waves per row chunk) where
@@ -468,11 +478,24 @@ MPlan carve_mplan(const Shape &s, bool few_rows) {
     // for eight-wave workgroups (which fill a CU alone), else two
     const int64_t gwaves = p.gsym ? 8 : grad_waves(p.nqb);
     const int64_t gslots = kCUs * std::max<int64_t>(
-                                      1, std::min<int64_t>(kLdsBytes / p.lds_grad,
+                                      1, std::min<int64_t>(kLdsBytes / (int64_t)align_up(p.lds_grad, kLdsGrain),
                                                            gwaves / p.wpg));
     const int64_t tgroups = p.gsplit ? 4 : p.ggroups;   // tile-kernel workgroups per chunk
     const int64_t gmin = few_rows ? (p.gsym && p.grb < kSymRBMax ? 4 : 8) : 16;
-    p.gchunks = std::max<int64_t>(1, std::min((p.gsym || p.wpg >= 8 ? 1 : 2) * gslots / tgroups, cdiv(s.N, gmin)));
+    const int64_t gmost = std::max<int64_t>(
+        1, std::min((p.gsym || p.wpg >= 8 ? 1 : 2) * gslots / tgroups, cdiv(s.N, gmin)));
+    p.gchunks = gmost;
+    // the tile kernel, where chunks of 16 rows don't fill its two rounds: of the most chunks, one or
+    // two full rounds and chunks of 16 rows the number with the least rounds times rows, two more
+    // per chunk for its start (us, chunks of 16 rows / the most / so, at Q = 62: N = 3,000, M = 60
+    // 258 / 286 / 215, N = 5,000, M = 60 395 / 314 / 262, N = 8,000, M = 32 310 / 366 / 283,
+    // N = 12,000, M = 32 521 / 454 / 373)
+    if (!p.gsym && few_rows && cdiv(s.N, 16) < gmost) {
+        const int64_t slots = std::max<int64_t>(1, gslots / tgroups);
+        auto cost = [&](int64_t c) { return cdiv(c, slots) * (cdiv(s.N, c) + 2); };
+        for (int64_t c : {2 * slots, cdiv(s.N, 16), slots})
+            if (c < gmost && cost(c) < cost(p.gchunks)) p.gchunks = c;
+    }
     p.grows = cdiv(s.N, p.gchunks);
     p.gchunks = cdiv(s.N, p.grows);
     p.dzslabs = p.gchunks * p.njr;
