@@ -54,9 +54,9 @@ class TimedScope {
 };
 
 // ---------------------------------------------------------------- generic path
-// Vector-ALU kernels templated on the element type; they serve F64, any F32
-// shape the matrix-core path does not take, and F32 calls whose operands the
-// matrix-core range guard rejects.  gate: NULL, or a device word; the kernels
+// Kernels in the element type's own arithmetic, on the vector unit or, but at small Q, in tiles
+// on its matrix instructions; they serve F64, any F32 shape the matrix-core path does not
+// take, its smallest calls, and F32 calls whose operands its range guard rejects.  gate: NULL, or a device word; the kernels
 // then do their work only where it is nonzero (the matrix-core route word).  mark:
 // NULL, or the route word of a call that could have taken the matrix cores and was
 // too small for them, which gets 2.
