@@ -3,8 +3,8 @@ GPPS_PARITY_LOG is set) as markdown: the five named workloads by path with the
 error of every output, the matrix-core range cases with the route the guard
 took, and the smallest margins (tolerance / error) over every comparison.
 
-    GPPS_PARITY_LOG=gpurun_out/parity_errors.jsonl python -m pytest tests -m gpu
-    python tests/parity_summary.py gpurun_out/parity_errors.jsonl > profiles/parity_errors.md
+    GPPS_PARITY_LOG=/tmp/parity_errors.jsonl python -m pytest tests -m gpu
+    python tests/parity_summary.py /tmp/parity_errors.jsonl > profiles/parity_errors.md
 """
 import argparse
 import json
@@ -33,7 +33,7 @@ def main():
           "(relative Frobenius norm per output; over the sampled entries or rows where the "
           "workload runs at full size).  Tolerances: 1e-5 (Psi1), 1e-4 (every other fp32 "
           "output), 1e-10 (fp64).  Produced by\n")
-    print("```\nGPPS_PARITY_LOG=gpurun_out/parity_errors.jsonl python -u -m pytest tests -m gpu\n"
+    print("```\nGPPS_PARITY_LOG=/tmp/parity_errors.jsonl python -u -m pytest tests -m gpu\n"
           f"python tests/parity_summary.py {a.log} > profiles/parity_errors.md\n```\n")
     print("## The five workloads\n")
     print("| workload | path | " + " | ".join(OUTPUTS) + " |")
