@@ -604,7 +604,7 @@ def main():
                                                    / PEAK_VALU_LANE_OPS, 4),
                 "exp_executed_per_launch": c["SQ_INSTS_VALU_TRANS_F32"] * 64,
                 "exp_unique_pairs_per_launch": float(N) / len(chunks) * P,
-                "counters": f"profiles/counters_{dom}_{args.workload}.md"}
+                "counters": cnt["summary"]}
     per_step = {k: v["avg_ms"] * v["launches"] / args.kernel_steps for k, v in kernels.items()}
     t_psi2 = sum(v for k, v in per_step.items() if kernel_class(k) == "psi2") * 1e-3
     t_feed = sum(v for k, v in per_step.items() if kernel_class(k) == "rows") * 1e-3

@@ -57,3 +57,10 @@ def test_kernel_classes():
             "mfma_rowterm": "rows", "known_kfu": None}
     assert {k: bench.kernel_class(k) for k in want} == want
     assert bench.algorithmic("generic_psi1", 10, 4, 2) is None
+
+
+@pytest.mark.parametrize("kernel", ["mfma_psi2_grad", "mfma_psi2_fwd"])
+def test_committed_counters_name_their_summary(kernel):
+    rec = bench.counters_for(kernel, "large")
+    assert rec is not None  # taken on the kernel's current source
+    assert os.path.isfile(os.path.join(bench.ROOT, rec["summary"]))
